@@ -387,8 +387,8 @@ wd_status wd_ptc_train_step(wd_ptc *n, const void *r, const void *e, int B,
  * (WD_TUNE_CACHED_STORE set in occ: cached stores), link preloading
  * (WD_TUNE_PRELOAD_LINKS, not FP64), LDS staging of the block's input tile
  * (WD_TUNE_STAGE_LDS, FP64 and FP32), sites per lane along x4
- * (WD_TUNE_SPL_SHIFT) and a cap on resident
- * blocks per CU (dynamic LDS in KiB << WD_TUNE_LDS_SHIFT).  Every candidate's output is
+ * (WD_TUNE_SPL_SHIFT), one wave per hop direction (WD_TUNE_SPLIT_DIRS) and a
+ * cap on resident blocks per CU (dynamic LDS in KiB << WD_TUNE_LDS_SHIFT).  Every candidate's output is
  * first compared byte for byte with the reference variant (256 threads,
  * linear, occ 0); matching candidates are timed with HIP events on
  * alternating even/odd hops and the fastest is kept in the handle.
@@ -446,11 +446,21 @@ enum { WD_TUNE_LDS_SHIFT = 16 };
  * storage; one site per lane, no link preloading, no LDS cap.  Same bytes as
  * every other variant. */
 enum { WD_TUNE_STAGE_LDS = 4096 };
+/* Bit of the occ value: one wave per hop direction.  Block 64: eight waves
+ * serve 64 output sites, each wave transports one of the eight neighbours and
+ * the contributions meet in LDS.  A shorter dependence chain and more waves
+ * in flight; no register budget, link preloading, LDS staging or cap, one
+ * site per lane.  Same bytes as every other variant. */
+enum { WD_TUNE_SPLIT_DIRS = 8192 };
+/* A groups value for WD_TUNE_SPLIT_DIRS, on any lattice: eight contiguous
+ * ranges of tiles, one per dispatch lane (per XCD). */
+enum { WD_ORDER_RANGES = -200 };
 
 /* Set / read the hop variant used for precision prec.  occ: 0 or 4, or'ed
  * with WD_TUNE_CACHED_STORE, WD_TUNE_PRELOAD_LINKS (not FP64),
  * WD_TUNE_STAGE_LDS (FP64, FP32), (0, 1, 2) << WD_TUNE_SPL_SHIFT and (KiB of
- * LDS << WD_TUNE_LDS_SHIFT).  WD_ERR_ARG if the variant does not fit the
+ * LDS << WD_TUNE_LDS_SHIFT); or WD_TUNE_SPLIT_DIRS (block 64), alone or with
+ * WD_TUNE_CACHED_STORE.  WD_ERR_ARG if the variant does not fit the
  * lattice (see wd_tune_dslash). */
 wd_status wd_set_dslash_variant(wd_gauge *g, wd_prec prec, int block, int groups,
                                 int occ);

@@ -132,15 +132,7 @@ wd_status wd_gauge_create(const double *U_host, const int dims[4], int t_bc, wd_
   g->prec = prec;
   g->stream = (hipStream_t)hip_stream;
   for (int p = 0; p < 4; ++p) {
-    // default hop variant: 256 threads, eight XCD regions when the lattice allows
-    g->hop_block[p] = 256;
-    g->hop_groups[p] = dslash_variant_ok(g->geom, 256, 8) ? 8 : 0;
-    g->hop_occ[p] = 0;
-    g->hop_ntst[p] = 1;
-    g->hop_lds[p] = 0;
-    g->hop_pre[p] = 0;
-    g->hop_spl[p] = 1;
-    g->hop_stage[p] = 0;
+    dslash_default_variant(g, p);
     g->mrhs_block[p] = (p == WD_F64) ? 16 : 128;
     g->mrhs_rpl[p] = 4;
     g->mrhs_groups[p] = dslash_variant_ok(g->geom, g->mrhs_block[p], 4) ? 4 : 0;

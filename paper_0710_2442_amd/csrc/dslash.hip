@@ -96,6 +96,19 @@ __global__ __launch_bounds__(512) void k_dslash_stage(KDslash k) {
   }
 }
 
+// One wave per hop direction (see wd_hop.h).
+template <int P, bool DAG, int EPI, bool NORM>
+__global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dslash_split(KDslash k) {
+  __shared__ SplitLds<P> lds;
+  if (k.skip && *k.skip) return;
+  const int tile = split_tile_of(k, (int)blockIdx.x);
+  if (tile * SPLIT_SITES >= k.g.vpad) return;
+  const double nrm = dslash_split_tile<P, DAG, EPI, NORM>(k, tile, lds);
+  if constexpr (NORM) {
+    if (threadIdx.x == 0) k.partials[tile] = nrm;
+  }
+}
+
 // A block size fits LDS staging when its tile is k >= 2 whole x1 rows of one
 // x3 plane (k | L2) or whole planes (L2 | k; then every x2 neighbour is in
 // the tile), and the tiles cover the slots exactly.
@@ -127,6 +140,10 @@ static KDslash make_k(const wd_gauge *g, wd_prec prec, int parity) {
 // smaller set of neighbour spinors the L2 must hold for reuse.
 template <int P, bool DAG, int EPI, bool NORM>
 static void launch_t(const KDslash &k, unsigned nblk, unsigned bs, unsigned lds, hipStream_t st) {
+  if (k.split) {
+    hipLaunchKernelGGL((k_dslash_split<P, DAG, EPI, NORM>), dim3(nblk), dim3(SPLIT_BS), 0, st, k);
+    return;
+  }
   if constexpr (P == WD_F64 || P == WD_F32) {
     if (k.stage) {
       const unsigned sb = (bs + 2 * (unsigned)k.g.L1h) * 12 * (unsigned)sizeof(cplx<RealOf<P>>);
@@ -197,6 +214,34 @@ bool dslash_variant_ok(const Geom &G, int bs, int groups, int spl) {
   return tps % groups == 0;
 }
 
+// The variant of a new handle: one wave per hop direction.  Kernel times
+// against 256-site blocks of one site per lane (regions of a slice where they
+// fit, else linear order), us per launch of alternating even and odd hops:
+//   8^4 FP64 4.1 against 7.0, 12^3x24 8.2 / 13.6, 16^3x32 16.5 / 18.2,
+//   24^3x48 68 / 102, 32^3x64 223 / 241 (5.4 TB/s algorithmic); FP32 3.2 / 5.4,
+//   4.6 / 8.6, 9.3 / 12.7, 34 / 51, 98 / 114; BF16 3.2 / 5.4, 4.5 / 8.8,
+//   7.9 / 11.3, 30 / 38, 80 / 90.
+// Order: a contiguous range of tiles per XCD keeps a tile's neighbours in one
+// L2 (linear against ranges: 12^3x24 FP64 11.5 / 8.2, 20^3x40 42 / 35,
+// 28^3x56 158 / 126).  From 2^18 sites on, eight regions of each slice, side
+// by side in memory, win where they fit: 16^3x128 FP64 52.6 against 53.8,
+// 32^3x64 225 / 239, 16x32x32x96 162 / 175; below, they lose: 16^4 FP32
+// 6.3 / 5.6.  Stores: cached with ranges, where the next kernel finds a small
+// field in the caches (12^3x24 FP32 4.6 against 4.8), streaming else (no
+// difference measured).
+void dslash_default_variant(wd_gauge *g, int p) {
+  const bool regions = g->geom.vh >= (1 << 18) && dslash_variant_ok(g->geom, SPLIT_SITES, 8);
+  g->hop_block[p] = SPLIT_SITES;
+  g->hop_groups[p] = regions ? 8 : SPLIT_RANGES;
+  g->hop_occ[p] = 0;
+  g->hop_ntst[p] = regions ? 1 : 0;
+  g->hop_lds[p] = 0;
+  g->hop_pre[p] = 0;
+  g->hop_spl[p] = 1;
+  g->hop_stage[p] = 0;
+  g->hop_split[p] = 1;
+}
+
 wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hipStream_t st) {
   KDslash k = make_k(g, prec, a.parity);
   k.in = (const char *)a.in;
@@ -214,24 +259,31 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
   if (norm && !k.partials) return set_error(WD_ERR_ARG, "dslash norm: no reduction buffer");
   const int pi = (int)prec;
   int bs = g->hop_block[pi], groups = g->hop_groups[pi], spl = g->hop_spl[pi];
-  if (!dslash_variant_ok(g->geom, bs, groups, spl)) { bs = 256; groups = 0; spl = 1; }
+  const bool ranges = groups == SPLIT_RANGES && bs == SPLIT_SITES && spl == 1 && g->hop_split[pi];
+  if (!ranges && !dslash_variant_ok(g->geom, bs, groups, spl)) { bs = 256; groups = 0; spl = 1; }
   k.groups = groups;
   k.spl = spl;
   k.occ = g->hop_occ[pi];
   k.nt_store = g->hop_ntst[pi];
   k.preload = (prec != WD_F64) ? g->hop_pre[pi] : 0;
-  k.stage = (prec == WD_F64 || prec == WD_F32) && spl == 1 && !k.preload && dslash_stage_ok(g->geom, bs) &&
+  k.split = (bs == SPLIT_SITES && spl == 1) ? g->hop_split[pi] : 0;
+  k.stage = (prec == WD_F64 || prec == WD_F32) && spl == 1 && !k.preload && !k.split && dslash_stage_ok(g->geom, bs) &&
                     dslash_stage_lds_bytes(g->geom, bs, prec) + (size_t)g->hop_lds[pi] <= (size_t)g->lds_per_block
                 ? g->hop_stage[pi]
                 : 0;
   k.tiles_per_slice = (groups || spl > 1) ? (int)((long)g->geom.vh / g->geom.L[3] / bs) : 0;
   const unsigned nblk = (unsigned)((g->geom.vpad + bs - 1) / bs) / (unsigned)spl;
+  unsigned grid = nblk;
+  if (ranges) {
+    k.tiles_per_slice = (int)((nblk + 7) / 8);  // tiles per range
+    grid = 8u * (unsigned)k.tiles_per_slice;
+  }
   const unsigned lds = (unsigned)g->hop_lds[pi];
   switch (prec) {
-    case WD_F64: launch_prec<WD_F64>(k, a.dagger, epi, norm, nblk, bs, lds, st); break;
-    case WD_F32: launch_prec<WD_F32>(k, a.dagger, epi, norm, nblk, bs, lds, st); break;
-    case WD_F16: launch_prec<WD_F16>(k, a.dagger, epi, norm, nblk, bs, lds, st); break;
-    case WD_BF16: launch_prec<WD_BF16>(k, a.dagger, epi, norm, nblk, bs, lds, st); break;
+    case WD_F64: launch_prec<WD_F64>(k, a.dagger, epi, norm, grid, bs, lds, st); break;
+    case WD_F32: launch_prec<WD_F32>(k, a.dagger, epi, norm, grid, bs, lds, st); break;
+    case WD_F16: launch_prec<WD_F16>(k, a.dagger, epi, norm, grid, bs, lds, st); break;
+    case WD_BF16: launch_prec<WD_BF16>(k, a.dagger, epi, norm, grid, bs, lds, st); break;
     default: return set_error(WD_ERR_PREC, "dslash: unknown precision %d", (int)prec);
   }
   WD_TRY(hip_check(hipGetLastError(), "dslash launch"));

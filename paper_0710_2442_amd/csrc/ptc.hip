@@ -729,18 +729,8 @@ __device__ __forceinline__ f4v mfma_bf16(bf8v a, bf8v b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// q = n / d for n < 2^31 (umulhi(n, m) + n cannot overflow), with
-// m = floor(2^32 (2^s - d) / d) + 1 and s = ceil(log2 d): the round-up
-// multiplier of Granlund and Montgomery (PLDI 1994), exact for n < 2^32 / d * 2^s.
-struct FDiv {
-  uint32_t m;
-  int s;
-};
-__device__ __forceinline__ int fdiv(int n, FDiv d) { return (int)((__umulhi((uint32_t)n, d.m) + (uint32_t)n) >> d.s); }
-
 struct KPtcB {
   Geom g;
-  FDiv dl1h, dl2, dl3;   // division by L1/2, L2, L3
   const uint2 *links;    // BF16 hop links, parity 0 then 1 (rows 0, 1 as (re, im) pairs; links16 layout)
   size_t link_par;       // uint2 per parity
   const char *x;         // BF16 even half (the network input)
@@ -760,11 +750,11 @@ struct NbMu {
 };
 __device__ __forceinline__ NbMu nb_mu(const KPtcB &k, int i, int p, int mu) {
   const Geom &g = k.g;
-  const int rest = fdiv(i, k.dl1h);
+  const int rest = fdiv(i, g.dl1h);
   const int x1h = i - rest * g.L1h;
-  const int r2 = fdiv(rest, k.dl2);
+  const int r2 = fdiv(rest, g.dl2);
   const int x2 = rest - r2 * g.L[1];
-  const int x4 = fdiv(r2, k.dl3);
+  const int x4 = fdiv(r2, g.dl3);
   const int x3 = r2 - x4 * g.L[2];
   NbMu n;
   // mu = 0
@@ -1328,13 +1318,6 @@ wd_status ptc_apply_even_h(const wd_ptc *nc, const void *in_even, void *out_even
   return hip_check(hipGetLastError(), "ptc fp16 layer 2");
 }
 
-static FDiv make_fdiv(int d) {
-  int s = 0;
-  while ((1u << s) < (unsigned)d) ++s;
-  const uint64_t m = (((uint64_t)1 << 32) * (((uint64_t)1 << s) - (uint64_t)d)) / (uint64_t)d + 1;
-  return FDiv{(uint32_t)m, s};
-}
-
 // [N (x_e, 0)]_e on the matrix cores: x_e an even half field in pin (FP32
 // input is first rounded to BF16 in the handle's x0 buffer), output in pout
 // (FP32 or BF16).  Needs BF16 activations (the hidden channels are the
@@ -1361,9 +1344,6 @@ wd_status ptc_apply_even_b(const wd_ptc *nc, const void *in_even, wd_prec pin, v
   }
   KPtcB k{};
   k.g = G;
-  k.dl1h = make_fdiv(G.L1h);
-  k.dl2 = make_fdiv(G.L[1]);
-  k.dl3 = make_fdiv(G.L[2]);
   k.links = n->linksb;
   k.link_par = par;
   k.x = (const char *)in_even;

@@ -74,25 +74,29 @@ static void cache_append(const char *path, const std::string &key, int bs, int g
 }
 
 // occ value: bits 0..7 register budget (0 or 4), WD_TUNE_CACHED_STORE,
-// WD_TUNE_PRELOAD_LINKS, log2 of the sites per lane at WD_TUNE_SPL_SHIFT and
-// the dynamic LDS per block in KiB at WD_TUNE_LDS_SHIFT (0..64)
-static wd_status decode_occ(int occ, int &o, int &nts, int &lkb, int &pre, int &spl, int &stage) {
+// WD_TUNE_PRELOAD_LINKS, WD_TUNE_STAGE_LDS, WD_TUNE_SPLIT_DIRS, log2 of the
+// sites per lane at WD_TUNE_SPL_SHIFT and the dynamic LDS per block in KiB at
+// WD_TUNE_LDS_SHIFT (0..64)
+static wd_status decode_occ(int occ, int &o, int &nts, int &lkb, int &pre, int &spl, int &stage, int &split) {
   o = occ & 0xff;
   nts = (occ & WD_TUNE_CACHED_STORE) ? 0 : 1;
   pre = (occ & WD_TUNE_PRELOAD_LINKS) ? 1 : 0;
   stage = (occ & WD_TUNE_STAGE_LDS) ? 1 : 0;
+  split = (occ & WD_TUNE_SPLIT_DIRS) ? 1 : 0;
   lkb = (occ >> WD_TUNE_LDS_SHIFT) & 0xff;
   const int sp = (occ >> WD_TUNE_SPL_SHIFT) & 3;
   spl = 1 << sp;
   const int rest = occ & ~(0xff | WD_TUNE_CACHED_STORE | WD_TUNE_PRELOAD_LINKS | WD_TUNE_STAGE_LDS |
-                           (3 << WD_TUNE_SPL_SHIFT) | (0xff << WD_TUNE_LDS_SHIFT));
+                           WD_TUNE_SPLIT_DIRS | (3 << WD_TUNE_SPL_SHIFT) | (0xff << WD_TUNE_LDS_SHIFT));
   if ((o != 0 && o != 4) || rest || lkb > 64 || sp == 3)
     return set_error(WD_ERR_ARG,
                      "occ = 0x%x: register budget 0 or 4, | WD_TUNE_CACHED_STORE, | WD_TUNE_PRELOAD_LINKS, "
-                     "| WD_TUNE_STAGE_LDS, | (0, 1, 2) << WD_TUNE_SPL_SHIFT, | KiB << %d (<= 64)",
+                     "| WD_TUNE_STAGE_LDS, | WD_TUNE_SPLIT_DIRS, | (0, 1, 2) << WD_TUNE_SPL_SHIFT, | KiB << %d (<= 64)",
                      occ, WD_TUNE_LDS_SHIFT);
   if (stage && (pre || spl != 1))
     return set_error(WD_ERR_ARG, "occ = 0x%x: LDS staging takes one site per lane and no link preloading", occ);
+  if (split && (o || pre || stage || lkb || spl != 1))
+    return set_error(WD_ERR_ARG, "occ = 0x%x: one wave per hop direction combines with the store policy only", occ);
   return WD_OK;
 }
 
@@ -105,7 +109,7 @@ static int log2i(int v) {
 static int encode_occ(const wd_gauge *g, wd_prec prec) {
   return g->hop_occ[prec] | (g->hop_ntst[prec] ? 0 : WD_TUNE_CACHED_STORE) |
          (g->hop_pre[prec] ? WD_TUNE_PRELOAD_LINKS : 0) | (g->hop_stage[prec] ? WD_TUNE_STAGE_LDS : 0) |
-         (log2i(g->hop_spl[prec]) << WD_TUNE_SPL_SHIFT) | ((g->hop_lds[prec] / 1024) << WD_TUNE_LDS_SHIFT);
+         (g->hop_split[prec] ? WD_TUNE_SPLIT_DIRS : 0) | (log2i(g->hop_spl[prec]) << WD_TUNE_SPL_SHIFT) | ((g->hop_lds[prec] / 1024) << WD_TUNE_LDS_SHIFT);
 }
 
 // *differ = 1 if the n 16-byte words of a and b are not all equal (vector
@@ -140,11 +144,14 @@ extern "C" {
 wd_status wd_set_dslash_variant(wd_gauge *g, wd_prec prec, int block, int groups, int occ) {
   if (!g) return set_error(WD_ERR_ARG, "gauge handle is NULL");
   if ((int)prec < 0 || (int)prec > 3) return set_error(WD_ERR_PREC, "prec = %d", (int)prec);
-  if (block < 64 || !dslash_variant_ok(g->geom, block, groups))
+  const bool ranges = groups == WD_ORDER_RANGES && block == 64 && (occ & WD_TUNE_SPLIT_DIRS);
+  if (block < 64 || (!ranges && !dslash_variant_ok(g->geom, block, groups)))
     return set_error(WD_ERR_ARG, "variant (block %d, groups %d) does not fit this lattice", block, groups);
-  int o, nts, lkb, pre, spl, stage;
-  WD_TRY(decode_occ(occ, o, nts, lkb, pre, spl, stage));
-  if (!dslash_variant_ok(g->geom, block, groups, spl))
+  int o, nts, lkb, pre, spl, stage, split;
+  WD_TRY(decode_occ(occ, o, nts, lkb, pre, spl, stage, split));
+  if (split && block != 64)
+    return set_error(WD_ERR_ARG, "one wave per hop direction takes blocks of 64 sites (block %d)", block);
+  if (!ranges && !dslash_variant_ok(g->geom, block, groups, spl))
     return set_error(WD_ERR_ARG, "variant (block %d, groups %d, %d sites per lane) does not fit this lattice", block,
                      groups, spl);
   if (pre && prec == WD_F64) return set_error(WD_ERR_ARG, "link preloading is for FP32-arithmetic hops");
@@ -164,6 +171,7 @@ wd_status wd_set_dslash_variant(wd_gauge *g, wd_prec prec, int block, int groups
   g->hop_pre[prec] = pre;
   g->hop_spl[prec] = spl;
   g->hop_stage[prec] = stage;
+  g->hop_split[prec] = split;
   return WD_OK;
 }
 
@@ -217,7 +225,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
   int bs = 256, groups = 0, occ = 0;
   double best_us = -1.0;
   if (cache_path && !force && cache_lookup(cache_path, key, bs, groups, occ, best_us) &&
-      dslash_variant_ok(g->geom, bs, groups) && wd_set_dslash_variant(g, prec, bs, groups, occ) == WD_OK) {
+      wd_set_dslash_variant(g, prec, bs, groups, occ) == WD_OK) {
   } else {
     const Geom &G = g->geom;
     const size_t hb = half_bytes(G, prec);
@@ -250,18 +258,20 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
       if ((rc = hip_check(hipEventCreate(&e1), "event")) != WD_OK) break;
       const int save_b = g->hop_block[prec], save_g = g->hop_groups[prec], save_o = g->hop_occ[prec];
       const int save_n = g->hop_ntst[prec], save_l = g->hop_lds[prec], save_p = g->hop_pre[prec];
-      const int save_s = g->hop_spl[prec], save_t = g->hop_stage[prec];
+      const int save_s = g->hop_spl[prec], save_t = g->hop_stage[prec], save_d = g->hop_split[prec];
       DslashArgs a;
       a.in = in; a.a = 1.0; a.parity = WD_EVEN;
       // reference variant
       g->hop_block[prec] = 256; g->hop_groups[prec] = 0; g->hop_occ[prec] = 0; g->hop_ntst[prec] = 1;
       g->hop_lds[prec] = 0; g->hop_pre[prec] = 0; g->hop_spl[prec] = 1; g->hop_stage[prec] = 0;
+      g->hop_split[prec] = 0;
       a.out = ref;
       if ((rc = launch_dslash(g, prec, a, st)) != WD_OK) break;
       const int blocks[] = {64, 128, 256, 512};
       const int grps[] = {0, 2, 4, 8, 16, -8, -16, -101, -102, -104, -108};
       best_us = 1e30;
       int nbest_b = 256, nbest_g = 0, nbest_o = 0, nbest_n = 1, nbest_l = 0, nbest_p = 0, nbest_s = 1, nbest_t = 0;
+      int nbest_d = 0;
       size_t lds_max = 65536;
       {
         hipDeviceProp_t prop;
@@ -269,8 +279,13 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
       }
       // the candidates, listed first so that one loop runs them and a failure
       // ends the whole search
-      struct Cand { int spl, pre, lkb, nts, oc, b, gr, stg; };
+      struct Cand { int spl, pre, lkb, nts, oc, b, gr, stg, spd; };
       std::vector<Cand> cands;
+      for (int nts : {1, 0}) {
+        cands.push_back({1, 0, 0, nts, 0, 64, WD_ORDER_RANGES, 0, 1});
+        for (int gr : grps)
+          if (dslash_variant_ok(G, 64, gr, 1)) cands.push_back({1, 0, 0, nts, 0, 64, gr, 0, 1});
+      }
       for (int stg : {0, 1})
         for (int spl : {1, 2, 4})
           for (int pre : {0, 1})
@@ -286,7 +301,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
                       if (stg && (spl != 1 || pre || lkb || (prec != WD_F64 && prec != WD_F32))) continue;
                       if (stg && (!dslash_stage_ok(G, b) || dslash_stage_lds_bytes(G, b, prec) > (size_t)g->lds_per_block))
                         continue;
-                      cands.push_back({spl, pre, lkb, nts, oc, b, gr, stg});
+                      cands.push_back({spl, pre, lkb, nts, oc, b, gr, stg, 0});
                     }
       for (const Cand &c : cands) {
         const int spl = c.spl, pre = c.pre, lkb = c.lkb, nts = c.nts, oc = c.oc, b = c.b, gr = c.gr;
@@ -295,6 +310,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
         g->hop_pre[prec] = pre;
         g->hop_spl[prec] = spl;
         g->hop_stage[prec] = c.stg;
+        g->hop_split[prec] = c.spd;
         if ((rc = launch_pack_spinor(g, canon, in, WD_ODD, prec, st)) != WD_OK) break;
         a.out = cand;
         if ((rc = hip_check(hipMemsetAsync(cand, 0xff, hb, st), "memset")) != WD_OK) break;
@@ -317,11 +333,11 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
         (void)hipEventElapsedTime(&ms, e0, e1);
         const double us = 1e3 * ms / (2 * reps);
         if (getenv("WD_TUNE_VERBOSE"))
-          fprintf(stderr, "tune %s: block %d groups %d occ %d ntstore %d lds %dK preload %d spl %d stage %d: %.2f us\n",
-                  key.c_str(), b, gr, oc, nts, lkb, pre, spl, c.stg, us);
+          fprintf(stderr, "tune %s: block %d groups %d occ %d ntstore %d lds %dK preload %d spl %d stage %d split %d: %.2f us\n",
+                  key.c_str(), b, gr, oc, nts, lkb, pre, spl, c.stg, c.spd, us);
         if (us < best_us) {
           best_us = us; nbest_b = b; nbest_g = gr; nbest_o = oc; nbest_n = nts; nbest_l = lkb; nbest_p = pre;
-          nbest_s = spl; nbest_t = c.stg;
+          nbest_s = spl; nbest_t = c.stg; nbest_d = c.spd;
         }
       }
       if (rc != WD_OK) {
@@ -331,6 +347,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
         g->hop_pre[prec] = save_p;
         g->hop_spl[prec] = save_s;
         g->hop_stage[prec] = save_t;
+        g->hop_split[prec] = save_d;
         break;
       }
       g->hop_block[prec] = nbest_b;
@@ -341,6 +358,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path, int 
       g->hop_pre[prec] = nbest_p;
       g->hop_spl[prec] = nbest_s;
       g->hop_stage[prec] = nbest_t;
+      g->hop_split[prec] = nbest_d;
       bs = nbest_b; groups = nbest_g;
       occ = encode_occ(g, prec);
       if (cache_path) cache_append(cache_path, key, bs, groups, occ, best_us);

@@ -432,6 +432,9 @@ __device__ __forceinline__ void reconstruct_add(cplx<T> (&acc)[12], const cplx<T
   }
 }
 
+// n / d (see FDiv; umulhi(n, m) + n cannot overflow for n < 2^31)
+__device__ __forceinline__ int fdiv(int n, FDiv d) { return (int)((__umulhi((uint32_t)n, d.m) + (uint32_t)n) >> d.s); }
+
 // ------------------------------------------------------------- reductions
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

@@ -2,6 +2,8 @@
 // single-lattice, multi-RHS and batched multi-lattice kernels.
 #pragma once
 
+#include <utility>
+
 #include "wd_device.h"
 
 namespace wd {
@@ -29,6 +31,7 @@ struct KDslash {
   int nt_store;         // 1: streaming output stores; 0: cached stores
   int preload;          // 1: load all 8 links before the first hop (FP32 arithmetic only), host side
   int stage;            // 1: stage the tile's input spinors in LDS (FP64, FP32), host side
+  int split;            // 1: one wave per hop direction, host side
   int spl;              // sites per lane along x4 (1, 2, 4): lane covers tiles t, t + T, ... of consecutive slices
 };
 
@@ -81,12 +84,12 @@ struct Coords {
 };
 __device__ __forceinline__ Coords coords_of(const Geom &g, int i, int parity) {
   Coords c;
-  const int x1h = i % g.L1h;
-  c.rest = i / g.L1h;
-  c.x2 = c.rest % g.L[1];
-  const int r2 = c.rest / g.L[1];
-  c.x3 = r2 % g.L[2];
-  c.x4 = r2 / g.L[2];
+  c.rest = fdiv(i, g.dl1h);
+  const int x1h = i - c.rest * g.L1h;
+  const int r2 = fdiv(c.rest, g.dl2);
+  c.x2 = c.rest - r2 * g.L[1];
+  c.x4 = fdiv(r2, g.dl3);
+  c.x3 = r2 - c.x4 * g.L[2];
   c.x1 = 2 * x1h + ((parity + c.x2 + c.x3 + c.x4) & 1);
   return c;
 }
@@ -446,6 +449,295 @@ __device__ __forceinline__ double dslash_site(const KDslash &k, int i, Stage<Rea
 #pragma unroll
     for (int c = 0; c < 12; ++c) z[c] = {(T)0, (T)0};
     Spinor<P>::store(k.out, i, z);
+  }
+  return nrm;
+}
+
+// ---------------------------------------------- one wave per hop direction
+// A block of 8 waves serves 64 output sites: wave d takes hop d of every
+// site (link and neighbour spinor loaded, projected, multiplied) and leaves
+// the transported half spinor in LDS; after one barrier a few waves add the
+// eight contributions of each output component in hop order, with the same
+// arithmetic as hop_all, so the result is the same bit for bit.
+//
+// A lane's chain is one load latency and one link multiply instead of eight,
+// and a CU holds 16 to 24 waves (one hop's operands fit 80 to 128 registers)
+// instead of 8 to 12.
+//
+// LDS: component c of hop d at site s is element (6 d + c) 64 + s, so the
+// lanes of a wave touch consecutive words: 48 KiB in FP64, 24 KiB else.
+constexpr int SPLIT_SITES = 64;
+constexpr int SPLIT_BS = 512;
+template <int P>
+struct SplitLds {
+  cplx<RealOf<P>> g[8 * 6 * SPLIT_SITES];
+  // |component C|^2 of an output (norm epilogue): in the time-hop element that
+  // only component C adds up, free once it has
+  template <bool DAG, int C>
+  __device__ __forceinline__ double &n2(int lane) {
+    constexpr int d = ((C < 6) != DAG) ? 3 : 7;
+    return *(double *)&g[(6 * d + C % 6) * SPLIT_SITES + lane];
+  }
+};
+// waves per SIMD the register budget is held to (whole blocks: 2 a block and SIMD)
+constexpr int split_occ(int prec, int epi) {
+  return prec == WD_F64 ? 6 : prec == WD_F16 ? (epi == 2 ? 4 : 6) : (prec == WD_BF16 && epi == 2) ? 6 : 8;
+}
+
+// Checkerboard index of the neighbour of site i (parity p) in direction MU,
+// forward or backward; edge: the hop crosses the time boundary.
+template <int MU, bool FWD>
+__device__ __forceinline__ int neighbour_of(const Geom &g, int i, int p, bool &edge) {
+  edge = false;
+  const int rest = fdiv(i, g.dl1h);
+  const int r2 = fdiv(rest, g.dl2);
+  const int x4 = fdiv(r2, g.dl3);
+  if constexpr (MU == 0) {
+    const int x1h = i - rest * g.L1h;
+    // the extents are even: x2 and x3 have the parities of rest and r2
+    const int odd = (p + rest + r2 + x4) & 1;
+    int y = x1h;
+    if (FWD && odd) y = (x1h + 1 == g.L1h) ? 0 : x1h + 1;
+    if (!FWD && !odd) y = (x1h == 0) ? g.L1h - 1 : x1h - 1;
+    return y + g.L1h * rest;
+  } else {
+    const int x = (MU == 1) ? rest - r2 * g.L[1] : (MU == 2) ? r2 - x4 * g.L[2] : x4;
+    const int s = (MU == 1) ? g.s2 : (MU == 2) ? g.s3 : g.s4;
+    const int last = g.L[MU] - 1;
+    if (FWD) {
+      edge = MU == 3 && x == last;
+      return i + ((x == last) ? -last * s : s);
+    }
+    edge = MU == 3 && x == 0;
+    return i + ((x == 0) ? last * s : -s);
+  }
+}
+
+// Hop D of site i: the transported half spinor into LDS.
+template <int P, bool DAG, int D>
+__device__ __forceinline__ void split_hop(const KDslash &k, int i, int lane, SplitLds<P> &lds) {
+  using T = RealOf<P>;
+  constexpr int MU = D & 3;
+  constexpr bool FWD = D < 4;
+  constexpr int S = (FWD != DAG) ? 1 : -1;
+  bool edge;
+  const int nb = neighbour_of<MU, FWD>(k.g, i, k.parity, edge);
+  cplx<T> u[6], h[6], r2[3];
+  Link<T>::load(k.links, D, i, u);
+  if constexpr (MU == 3) {
+    Spinor<P>::template load_half<(S < 0)>(k.in, nb, h);
+    const T f = (T)2 * (edge ? (T)k.g.tbc : (T)1);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) h[c] = f * h[c];
+  } else {
+    cplx<T> psi[12];
+    Spinor<P>::load(k.in, nb, psi);
+    project<MU, S>(psi, h);
+  }
+  cplx<T> *q = lds.g + D * 6 * SPLIT_SITES + lane;
+  // rows 0 and 1 first, the rebuilt row last: the spinor is dead before the
+  // products start and the stored rows before the last two are (FP64: 72
+  // registers of operands of the 80 that three blocks a CU leave each lane)
+  if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      cplx<T> y = u[3 * a] * h[3 * s];
+      cfma(y, u[3 * a + 1], h[3 * s + 1]);
+      cfma(y, u[3 * a + 2], h[3 * s + 2]);
+      q[(3 * s + a) * SPLIT_SITES] = y;
+    }
+  if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
+  rebuild_row2(u, r2);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    cplx<T> y = r2[0] * h[3 * s];
+    cfma(y, r2[1], h[3 * s + 1]);
+    cfma(y, r2[2], h[3 * s + 2]);
+    q[(3 * s + 2) * SPLIT_SITES] = y;
+  }
+}
+
+template <int P, bool DAG>
+__device__ __forceinline__ void split_hops(const KDslash &k, int i, int w, int lane, SplitLds<P> &lds) {
+  switch (w) {
+    case 0: split_hop<P, DAG, 0>(k, i, lane, lds); break;
+    case 1: split_hop<P, DAG, 1>(k, i, lane, lds); break;
+    case 2: split_hop<P, DAG, 2>(k, i, lane, lds); break;
+    case 3: split_hop<P, DAG, 3>(k, i, lane, lds); break;
+    case 4: split_hop<P, DAG, 4>(k, i, lane, lds); break;
+    case 5: split_hop<P, DAG, 5>(k, i, lane, lds); break;
+    case 6: split_hop<P, DAG, 6>(k, i, lane, lds); break;
+    default: split_hop<P, DAG, 7>(k, i, lane, lds); break;
+  }
+}
+
+// Output component C of the lane's site: the sum over the hops, in hop order,
+// of what reconstruct_add adds to it.
+template <int P, bool DAG, int C>
+__device__ __forceinline__ cplx<RealOf<P>> split_sum(const SplitLds<P> &lds, int lane) {
+  using T = RealOf<P>;
+  constexpr int sp = C / 3, a = C % 3;
+  const cplx<T> *g = lds.g + lane;
+  cplx<T> acc = {(T)0, (T)0};
+#pragma unroll
+  for (int d = 0; d < 8; ++d) {
+    const int mu = d & 3, S = ((d < 4) != DAG) ? 1 : -1;
+    const T s = (T)S;
+    if (mu == 3 && (sp < 2) != (S > 0)) continue;
+    const int h = (sp < 2 || mu == 3) ? (sp & 1) : (mu == 2 ? sp - 2 : 3 - sp);  // which spin row of g
+    const cplx<T> v = g[(6 * d + 3 * h + a) * SPLIT_SITES];
+    if (sp < 2 || mu == 3) acc = acc + v;
+    else if (mu == 0) acc = acc + s * mul_i(v);
+    else if (mu == 1) acc = (sp == 2) ? acc - s * v : acc + s * v;
+    else acc = (sp == 2) ? acc + s * mul_i(v) : acc - s * mul_i(v);
+  }
+  if constexpr (P == WD_F16) __builtin_amdgcn_sched_barrier(0);  // one component's operands at a time
+  return acc;
+}
+
+// Components [0, 12) are summed by NW waves, CW components each: whole
+// 16-byte packets of the storage format (FP16 needs the site's largest
+// component for its scale, so one wave takes them all).
+template <int P>
+struct SplitOut {
+  static constexpr int CW = (P == WD_F64 || P == WD_F32) ? 2 : (P == WD_BF16 ? 4 : 12);
+  static constexpr int NW = 12 / CW;
+};
+
+// Components W CW .. of a stored spinor.
+template <int P, int W>
+__device__ __forceinline__ void split_load(const char *base, int i, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
+  if constexpr (P == WD_F64) {
+    const v2d *p = (const v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * W;
+    const v2d a = p[0], b = p[64];
+    x[0] = {a.x, a.y};
+    x[1] = {b.x, b.y};
+  } else if constexpr (P == WD_F32) {
+    const v4f v = *((const v4f *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
+    x[0] = {v.x, v.y};
+    x[1] = {v.z, v.w};
+  } else if constexpr (P == WD_BF16) {
+    const v4u v = *((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = {bf16_to_f32((uint16_t)(w[j] & 0xffffu)), bf16_to_f32((uint16_t)(w[j] >> 16))};
+  } else {
+    Spinor<P>::load(base, i, x);
+  }
+}
+
+// Stores them; on return x holds the stored (rounded) values when NORM.
+template <int P, int W, bool NT, bool NORM>
+__device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
+  if constexpr (P == WD_F64) {
+    v2d *p = (v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * W;
+    st_policy<NT>(v2d{x[0].re, x[0].im}, p);
+    st_policy<NT>(v2d{x[1].re, x[1].im}, p + 64);
+  } else if constexpr (P == WD_F32) {
+    st_policy<NT>(v4f{x[0].re, x[0].im, x[1].re, x[1].im},
+                  (v4f *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
+  } else if constexpr (P == WD_BF16) {
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)f32_to_bf16(x[j].re) | ((uint32_t)f32_to_bf16(x[j].im) << 16);
+    st_policy<NT>(v4u{w[0], w[1], w[2], w[3]}, (v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
+    if constexpr (NORM) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[j] = {bf16_to_f32((uint16_t)(w[j] & 0xffffu)), bf16_to_f32((uint16_t)(w[j] >> 16))};
+    }
+  } else {
+    Spinor<P>::template store<NT>(base, i, x);
+    if constexpr (NORM) Spinor<P>::load(base, i, x);
+  }
+}
+
+// The epilogue of wave W's components of site i (see dslash_site).
+template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
+__device__ __forceinline__ void split_finish_w(const KDslash &k, int i, int lane, SplitLds<P> &lds,
+                                               const cplx<RealOf<P>> (&x)[SplitOut<P>::CW],
+                                               const cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
+                                               std::integer_sequence<int, J...>) {
+  using T = RealOf<P>;
+  constexpr int CW = SplitOut<P>::CW;
+  cplx<T> o[CW];
+  if (i < k.g.vh) {
+    const T a = (T)k.a;
+    ((o[J] = split_sum<P, DAG, W * CW + J>(lds, lane)), ...);
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+      o[j] = a * o[j];
+      if constexpr (EPI >= 1) o[j] = o[j] + x[j];
+      if constexpr (EPI == 2) o[j] = o[j] - y[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
+  }
+  if (k.nt_store) split_store<P, W, true, NORM>(k.out, i, o);
+  else split_store<P, W, false, NORM>(k.out, i, o);
+  if constexpr (NORM)
+    ((lds.template n2<DAG, W * CW + J>(lane) = (double)o[J].re * o[J].re + (double)o[J].im * o[J].im), ...);
+}
+
+template <int P, bool DAG, int EPI, bool NORM, int W>
+__device__ __forceinline__ void split_wave(const KDslash &k, int i, int lane, SplitLds<P> &lds) {
+  using T = RealOf<P>;
+  constexpr int CW = SplitOut<P>::CW;
+  // the epilogue operands are loaded before the barrier
+  cplx<T> x[CW], y[CW];
+  if constexpr (EPI >= 1)
+    if (i < k.g.vh) split_load<P, W>(k.X, i, x);
+  if constexpr (EPI == 2)
+    if (i < k.g.vh) split_load<P, W>(k.Y, i, y);
+  __syncthreads();
+  split_finish_w<P, DAG, EPI, NORM, W>(k, i, lane, lds, x, y, std::make_integer_sequence<int, CW>{});
+}
+
+template <int P, bool DAG, int... C>
+__device__ __forceinline__ double split_norm(SplitLds<P> &lds, int lane, std::integer_sequence<int, C...>) {
+  double nrm = 0.0;
+  ((nrm += lds.template n2<DAG, C>(lane)), ...);
+  return nrm;
+}
+
+// Tile of block b in the order SPLIT_RANGES: dispatch lane b % 8 (one per
+// XCD) takes the b % 8-th of eight contiguous ranges of tiles, on any
+// lattice, so a tile's x1..x3 neighbours and most x4 ones are fetched into
+// one L2.  The grid is 8 ceil(ntiles / 8); a tile >= ntiles is empty.
+constexpr int SPLIT_RANGES = WD_ORDER_RANGES;
+__device__ __forceinline__ int split_tile_of(const KDslash &k, int b) {
+  if (k.groups == SPLIT_RANGES) return (b & 7) * k.tiles_per_slice + (b >> 3);
+  return tile_of(k, b);
+}
+
+// 64 output sites of the hop by a block of SPLIT_BS threads: sites 64 tile ..
+// Returns the tile's |out|^2 in thread 0 when NORM (the same sum as a 64-site
+// block of dslash_site), else 0.
+template <int P, bool DAG, int EPI, bool NORM>
+__device__ __forceinline__ double dslash_split_tile(const KDslash &k, int tile, SplitLds<P> &lds) {
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int i = tile * SPLIT_SITES + lane;
+  if (i < k.g.vh) split_hops<P, DAG>(k, i, w, lane, lds);
+  constexpr int NW = SplitOut<P>::NW;
+  switch (w) {
+    case 0: split_wave<P, DAG, EPI, NORM, 0>(k, i, lane, lds); break;
+    case 1: if constexpr (NW > 1) { split_wave<P, DAG, EPI, NORM, 1>(k, i, lane, lds); break; }
+    case 2: if constexpr (NW > 1) { split_wave<P, DAG, EPI, NORM, 2>(k, i, lane, lds); break; }
+    case 3: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 3>(k, i, lane, lds); break; }
+    case 4: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 4>(k, i, lane, lds); break; }
+    case 5: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 5>(k, i, lane, lds); break; }
+    default: __syncthreads(); break;
+  }
+  double nrm = 0.0;
+  if constexpr (NORM) {
+    __syncthreads();
+    if (w == 0) {
+      if (i < k.g.vh) nrm = split_norm<P, DAG>(lds, lane, std::make_integer_sequence<int, 12>{});
+      nrm = wave_sum(nrm);
+    }
   }
   return nrm;
 }

@@ -9,6 +9,20 @@
 
 namespace wd {
 
+// q = n / d for 0 <= n < 2^31 by a multiply and a shift (fdiv in wd_device.h):
+// m = floor(2^32 (2^s - d) / d) + 1, s = ceil(log2 d), the round-up multiplier
+// of Granlund and Montgomery (PLDI 1994).
+struct FDiv {
+  uint32_t m;
+  int s;
+};
+inline FDiv make_fdiv(int d) {
+  int s = 0;
+  while ((1u << s) < (unsigned)d) ++s;
+  const uint64_t m = (((uint64_t)1 << 32) * (((uint64_t)1 << s) - (uint64_t)d)) / (uint64_t)d + 1;
+  return FDiv{(uint32_t)m, s};
+}
+
 // Lattice geometry of one handle, passed by value to kernels.
 struct Geom {
   int L[4];     // L1..L4
@@ -17,6 +31,7 @@ struct Geom {
   int vpad;     // slots per half field
   int s2, s3, s4;  // checkerboard strides of x2, x3, x4: L1h, L1h*L2, L1h*L2*L3
   float tbc;    // time-boundary factor (+1 / -1)
+  FDiv dl1h, dl2, dl3;  // division by L1 / 2, L2, L3
 };
 
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
@@ -32,6 +47,9 @@ inline Geom make_geom(const int dims[4], int tbc) {
   g.s3 = g.L1h * dims[1];
   g.s4 = g.L1h * dims[1] * dims[2];
   g.tbc = (float)tbc;
+  g.dl1h = make_fdiv(g.L1h);
+  g.dl2 = make_fdiv(dims[1]);
+  g.dl3 = make_fdiv(dims[2]);
   return g;
 }
 
@@ -87,6 +105,7 @@ struct wd_gauge {
   int hop_pre[4];          // per precision: 1 = links loaded before the first hop (not FP64)
   int hop_spl[4];          // per precision: output sites per lane along x4 (1, 2, 4)
   int hop_stage[4];        // per precision: 1 = x1/x2 neighbours from an LDS-staged tile (FP64, FP32)
+  int hop_split[4];        // per precision: 1 = one wave per hop direction (64-site blocks)
   double *scratch_red;     // reduction partials / scalars for the BLAS entry points
   wd::Workspace *ws;
   void *fg_mem;            // mixed FGCR: vectors + scalars + partials, kept between solves
@@ -174,6 +193,8 @@ wd_status launch_dslash_slab(const wd_gauge *g, const void *in_slab, const void 
                              hipStream_t st);
 unsigned dslash_grid_blocks(const wd_gauge *g);
 bool dslash_variant_ok(const Geom &G, int bs, int groups, int spl = 1);
+// the hop variant of precision index p that a new handle uses
+void dslash_default_variant(wd_gauge *g, int p);
 // LDS staging of the input tile fits block size bs (whole x1 rows of one plane)
 bool dslash_stage_ok(const Geom &G, int bs);
 // its dynamic LDS per block (FP64 or FP32 storage)

@@ -1,0 +1,75 @@
+"""The hop with one wave per direction (WD_TUNE_SPLIT_DIRS, the variant of a
+new handle): the same bytes as the one-site-per-lane hop in every storage
+precision, order and epilogue.  Sizes: one slot tile mostly padding (2^4: 8
+sites), fewer tiles than XCDs, padding in the last tile, ranges whose last
+blocks are empty, extents of 2 (forward and backward neighbours coincide)."""
+import pytest
+import torch
+
+import paper_0710_2442_amd as wd
+import synthetic as syn
+from gpu_util import to_field
+
+pytestmark = pytest.mark.gpu
+
+ORDERS = (0, 2, 8, -2, -8, -101, -108, wd.WD_ORDER_RANGES)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 6, 10), (2, 6, 2, 34), (8, 8, 8, 8), (16, 16, 8, 16)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+def test_split_hop_is_bitwise_the_one_lane_hop(dims, prec):
+    g = wd.Gauge(syn.gauge_field(dims, 0.3, 61), dims, -1, prec)
+    default = wd.wd_get_dslash_variant(g, prec)
+    assert default[0] == 64 and default[2] & wd.WD_TUNE_SPLIT_DIRS
+    psi = syn.gaussian_spinor(dims, 62)
+    n = 0
+    for parity in (wd.WD_EVEN, wd.WD_ODD):
+        src = to_field(g, psi, prec, 1 - parity)
+        for flags in (0, wd.WD_DAGGER):
+            wd.wd_set_dslash_variant(g, prec, 256, 0, 0)
+            ref = wd.wd_new_field(dims, prec, 1, parity)
+            wd.wd_dslash_ex(g, src, ref, 0.7, parity, prec, flags)
+            for variant in [default] + [(64, o, wd.WD_TUNE_SPLIT_DIRS | c) for o in ORDERS
+                                        for c in (0, wd.WD_TUNE_CACHED_STORE)]:
+                try:
+                    wd.wd_set_dslash_variant(g, prec, *variant)
+                except wd.WdError:
+                    assert variant[1] not in (0, wd.WD_ORDER_RANGES)
+                    continue
+                assert wd.wd_get_dslash_variant(g, prec) == variant
+                out = wd.wd_new_field(dims, prec, 1, parity)
+                out.fill_(0xAB)
+                wd.wd_dslash_ex(g, src, out, 0.7, parity, prec, flags)
+                torch.cuda.synchronize()
+                assert torch.equal(out, ref), (variant, parity, flags)
+                n += 1
+    assert n >= 4 * 5
+    bit = wd.WD_TUNE_SPLIT_DIRS
+    for bad in ((128, 0, bit), (64, 0, bit | 4), (64, 0, bit | wd.WD_TUNE_PRELOAD_LINKS),
+                (64, 0, bit | wd.WD_TUNE_STAGE_LDS), (64, 0, bit | (1 << wd.WD_TUNE_SPL_SHIFT)),
+                (64, wd.WD_ORDER_RANGES, 0), (64, 5, bit)):
+        with pytest.raises(wd.WdError):
+            wd.wd_set_dslash_variant(g, prec, *bad)
+    g.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 6, 10), (8, 8, 8, 8)])
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16", "bf16"])
+def test_split_hop_in_a_solve_is_bitwise_the_one_lane_hop(dims, inner):
+    """Every epilogue and norm a solver fuses into the hop (64-site blocks on
+    both sides, so the norm partials are the same sums)."""
+    g = wd.Gauge(syn.gauge_field(dims, 0.3, 63), dims, -1, "f64")
+    b = to_field(g, syn.gaussian_spinor(dims, 64))
+    p = wd.wd_solve_params_default(solver=wd.WD_SOLVER_CG) if inner == "f64" else wd.wd_solve_params_default(
+        solver=wd.WD_SOLVER_DEFECT_CG, inner_prec=inner, inner_tol=1e-2)
+    outs = []
+    for groups, occ in ((0, 0), (0, wd.WD_TUNE_SPLIT_DIRS), (wd.WD_ORDER_RANGES, wd.WD_TUNE_SPLIT_DIRS)):
+        for prec in ("f64", "f32", "f16", "bf16"):
+            wd.wd_set_dslash_variant(g, prec, 64, groups, occ)
+        x = wd.wd_new_field(dims, "f64")
+        rc, info = wd.wd_solve(g, b, x, 0.12, 1e-10, p)
+        assert rc == 0
+        outs.append((x, info["iters"], info["outer_iters"]))
+    for o in outs[1:]:
+        assert o[1:] == outs[0][1:] and torch.equal(o[0], outs[0][0])
+    g.close()
