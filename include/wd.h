@@ -84,15 +84,16 @@ enum { WD_EVEN = 0, WD_ODD = 1, WD_FULL = 2 };
 
 /* flags of wd_dslash_ex.  WD_DAGGER: apply H^dag (D_W^dag).  WD_ONE_PASS
  * (parity WD_FULL only): compute D_W in one full-lattice launch that takes
- * each site's backward links from its neighbours' forward links (each link
- * is needed once per application) instead of two single-parity launches.
- * That launch marches along x4 through ranges of time slices, one spatial
- * site per lane, the way Sec. 5 streams a lattice held in main memory a
- * slice at a time: the time link, the backward time hop and the partial
- * output pass from one slice to the next in registers, so each link and
- * spinor is fetched once (768 B per site in FP64).  The full-lattice
- * solvers (WD_SOLVER_CGLS_FULL, WD_SOLVER_FGCR) apply D_W this way when its
- * work items fill the device. */
+ * each site's backward links from its neighbours' forward links, so each link
+ * is needed once per application (768 B per site in FP64).  WD_FULL runs this
+ * way with and without the flag, in one of two forms of the same arithmetic
+ * (wd_tune_dirac):
+ * marching along x4 through ranges of time slices, one spatial site per lane,
+ * the way Sec. 5 streams a lattice held in main memory a slice at a time (the
+ * time link, the backward time hop and the partial output pass from one slice
+ * to the next in registers, so each link and spinor is fetched once), for
+ * lattices whose ranges fill the device; and one wave per hop direction, for
+ * the others. */
 enum { WD_DAGGER = 1, WD_ONE_PASS = 2 };
 
 typedef struct wd_gauge wd_gauge;
@@ -475,7 +476,9 @@ wd_status wd_get_dslash_variant(const wd_gauge *g, wd_prec prec, int *block,
  * with the spinors of each slice of the brick and of its four side faces
  * staged in LDS at every step, so the spatial neighbours are read from LDS
  * (FP64 and FP32 storage; (256 + 2 L1 (n2 + 2)) x 192 or 96 bytes of LDS
- * per block); 0: 256 consecutive sites, x1 fastest).  Every candidate is checked byte for byte against the
+ * per block); 0: 256 consecutive sites, x1 fastest; 4: no march: blocks of
+ * eight waves on 64 sites, one hop direction per wave, any lattice; slices
+ * has no meaning there).  Every candidate is checked byte for byte against the
  * current variant, then timed on a random field; the fastest is kept in the
  * handle.  cache_path and force as for wd_tune_dslash (key
  * "<arch>/dirac/p<prec>/<L1>x<L2>x<L3>x<L4>"; the cache line's "block" is
@@ -486,8 +489,10 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
 
 /* Set / read the one-launch D_W variant of precision prec: slices 0 (the
  * default: the shortest range of 8, 16, ... for which every work item is
- * resident on the device at once) or 1..L4, tile 0, 2 or 3 as above (the
- * default: 3 where it fits, else 2 where bricks fit, else 0).
+ * resident on the device at once) or 1..L4, tile 0, 2, 3 or 4 as above (the
+ * default: 3 where it fits, else 2 where bricks fit, else 0).  While neither
+ * was set nor tuned, the default runs as tile 4 on lattices whose tile-3
+ * ranges do not fill the device.
  * WD_ERR_ARG for a value outside these or a brick that does not fit the
  * lattice.  The variants compute the same bytes; only the time differs. */
 wd_status wd_set_dirac_variant(wd_gauge *g, wd_prec prec, int slices, int tile);

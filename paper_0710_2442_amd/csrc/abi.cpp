@@ -277,22 +277,9 @@ static wd_status dslash_common(const wd_gauge *U, const void *in, void *out, dou
   const size_t ob = (const char *)out > (const char *)in ? (size_t)((const char *)out - (const char *)in)
                                                           : (size_t)((const char *)in - (const char *)out);
   if (ob < 2 * hb) return set_error(WD_ERR_ARG, "dslash: full fields overlap");
-  if (flags & WD_ONE_PASS) {
-    DiracArgs a;
-    a.in = in; a.out = out; a.X = in; a.a = -kappa; a.dagger = dag;
-    return launch_dirac(U, prec, a, U->stream);
-  }
-  for (int p = 0; p < 2; ++p) {
-    DslashArgs a;
-    a.in = (const char *)in + (1 - p) * hb;
-    a.out = (char *)out + p * hb;
-    a.X = (const char *)in + p * hb;
-    a.a = -kappa;
-    a.parity = p;
-    a.dagger = dag;
-    WD_TRY(launch_dslash(U, prec, a, U->stream));
-  }
-  return WD_OK;
+  DiracArgs a;
+  a.in = in; a.out = out; a.X = in; a.a = -kappa; a.dagger = dag;
+  return launch_dirac(U, prec, a, U->stream);
 }
 
 wd_status wd_dslash(const wd_gauge *U, const void *psi_in, void *psi_out, double kappa, const int dims[4],

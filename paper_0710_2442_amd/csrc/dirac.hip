@@ -482,6 +482,195 @@ __global__ __launch_bounds__(DM_BS) void k_dirac_march(KDirac k) {
   }
 }
 
+// ------------------------------------------ one wave per hop direction
+// Tile 4: a block of eight waves serves 64 checkerboard sites of one parity,
+// one hop direction per wave, as k_dslash_split does, with the backward hops
+// on the neighbours' forward links (U^dag), so each link is fetched from HBM
+// for one of its two uses and found in the caches for the other: the two
+// parities' tiles of the same sites follow each other on one XCD.  Same
+// products and the same order of additions as the march, hence the same
+// bytes.
+template <int P, bool DAG, int D>
+__device__ __forceinline__ void dirac_split_hop(const KDirac &k, int i, int p, int lane, SplitLds<P> &lds) {
+  using T = RealOf<P>;
+  constexpr int MU = D & 3;
+  constexpr bool FWD = D < 4;
+  constexpr int S = (FWD != DAG) ? 1 : -1;
+  bool edge;
+  const int nb = neighbour_of<MU, FWD>(k.g, i, p, edge);
+  const char *in = k.in + (size_t)(1 - p) * k.half;
+  cplx<T> u[6], h[6], r2[3];
+  if constexpr (FWD) Link<T>::template load<false>(k.links[p], MU, i, u);
+  else Link<T>::template load<false>(k.links[1 - p], MU, nb, u);
+  T f = (T)k.a;
+  if constexpr (MU == 3) {
+    Spinor<P>::template load_half<(S < 0)>(in, nb, h);
+    f = (T)2 * (edge ? (T)k.g.tbc : (T)1) * (T)k.a;
+  } else {
+    cplx<T> psi[12];
+    Spinor<P>::load(in, nb, psi);
+    project<MU, S>(psi, h);
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) h[c] = f * h[c];
+  cplx<T> *q = lds.g + D * 6 * SPLIT_SITES + lane;
+  // (the order keeps few registers live, see split_hop)
+  if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (FWD) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        cplx<T> y = u[3 * a] * h[3 * s];
+        cfma(y, u[3 * a + 1], h[3 * s + 1]);
+        cfma(y, u[3 * a + 2], h[3 * s + 2]);
+        q[(3 * s + a) * SPLIT_SITES] = y;
+      }
+    if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
+    rebuild_row2(u, r2);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      cplx<T> y = r2[0] * h[3 * s];
+      cfma(y, r2[1], h[3 * s + 1]);
+      cfma(y, r2[2], h[3 * s + 2]);
+      q[(3 * s + 2) * SPLIT_SITES] = y;
+    }
+  } else {
+    rebuild_row2(u, r2);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        cplx<T> y = cjmul(u[a], h[3 * s]);
+        cfma(y, conj(u[3 + a]), h[3 * s + 1]);
+        cfma(y, conj(r2[a]), h[3 * s + 2]);
+        q[(3 * s + a) * SPLIT_SITES] = y;
+      }
+      if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// Output component C: acc0 = X - Y plus the hops in the march's order
+// (backward time, then both of x1, x2, x3, then forward time).
+template <int P, bool DAG, int C>
+__device__ __forceinline__ cplx<RealOf<P>> dirac_split_sum(const SplitLds<P> &lds, int lane, cplx<RealOf<P>> acc) {
+  using T = RealOf<P>;
+  constexpr int sp = C / 3, a = C % 3;
+  constexpr int order[8] = {7, 0, 4, 1, 5, 2, 6, 3};
+  const cplx<T> *g = lds.g + lane;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int d = order[j], mu = d & 3, S = ((d < 4) != DAG) ? 1 : -1;
+    const T s = (T)S;
+    if (mu == 3 && (sp < 2) != (S > 0)) continue;
+    const int h = (sp < 2 || mu == 3) ? (sp & 1) : (mu == 2 ? sp - 2 : 3 - sp);
+    const cplx<T> v = g[(6 * d + 3 * h + a) * SPLIT_SITES];
+    if (sp < 2 || mu == 3) acc = acc + v;
+    else if (mu == 0) acc = acc + s * mul_i(v);
+    else if (mu == 1) acc = (sp == 2) ? acc - s * v : acc + s * v;
+    else acc = (sp == 2) ? acc + s * mul_i(v) : acc - s * mul_i(v);
+  }
+  if constexpr (P == WD_F16) __builtin_amdgcn_sched_barrier(0);
+  return acc;
+}
+
+template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
+__device__ __forceinline__ void dirac_split_finish(const KDirac &k, int i, char *out, int lane, SplitLds<P> &lds,
+                                                   cplx<RealOf<P>> (&o)[SplitOut<P>::CW],
+                                                   std::integer_sequence<int, J...>) {
+  using T = RealOf<P>;
+  constexpr int CW = SplitOut<P>::CW;
+  if (i < k.g.vh) {
+    ((o[J] = dirac_split_sum<P, DAG, W * CW + J>(lds, lane, o[J])), ...);
+  } else {
+#pragma unroll
+    for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
+  }
+  split_store<P, W, true, NORM>(out, i, o);
+  if constexpr (NORM)
+    ((lds.template n2<DAG, W * CW + J>(lane) = (double)o[J].re * o[J].re + (double)o[J].im * o[J].im), ...);
+}
+
+template <int P, bool DAG, int EPI, bool NORM, int W>
+__device__ __forceinline__ void dirac_split_wave(const KDirac &k, int i, int p, int lane, SplitLds<P> &lds) {
+  using T = RealOf<P>;
+  constexpr int CW = SplitOut<P>::CW;
+  const size_t off = (size_t)p * k.half;
+  cplx<T> o[CW];
+#pragma unroll
+  for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
+  if (i < k.g.vh) {
+    if constexpr (EPI >= 1) split_load<P, W>(k.X + off, i, o);
+    if constexpr (EPI == 2) {
+      cplx<T> y[CW];
+      split_load<P, W>(k.Y + off, i, y);
+#pragma unroll
+      for (int j = 0; j < CW; ++j) o[j] = o[j] - y[j];
+    }
+  }
+  __syncthreads();
+  dirac_split_finish<P, DAG, EPI, NORM, W>(k, i, k.out + off, lane, lds, o, std::make_integer_sequence<int, CW>{});
+}
+
+template <int P, bool DAG, int EPI, bool NORM>
+__global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDirac k) {
+  __shared__ SplitLds<P> lds;
+  if (k.skip && *k.skip) return;
+  const int b = (int)blockIdx.x, r = b & 7, q = b >> 3, p = q & 1;
+  // nt tiles a parity; S = 0: range r of per tiles; S > 0: region r of every
+  // slice (S tiles), slice by slice
+  int tile;
+  if (k.S == 0) {
+    tile = r * k.per + (q >> 1);
+    if ((q >> 1) >= k.per || tile >= k.nt) return;
+  } else {
+    const int w = k.S / 8;
+    tile = ((q >> 1) / w) * k.S + r * w + (q >> 1) % w;
+  }
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int i = tile * SPLIT_SITES + lane;
+  if (i < k.g.vh) {
+    switch (w) {
+      case 0: dirac_split_hop<P, DAG, 0>(k, i, p, lane, lds); break;
+      case 1: dirac_split_hop<P, DAG, 1>(k, i, p, lane, lds); break;
+      case 2: dirac_split_hop<P, DAG, 2>(k, i, p, lane, lds); break;
+      case 3: dirac_split_hop<P, DAG, 3>(k, i, p, lane, lds); break;
+      case 4: dirac_split_hop<P, DAG, 4>(k, i, p, lane, lds); break;
+      case 5: dirac_split_hop<P, DAG, 5>(k, i, p, lane, lds); break;
+      case 6: dirac_split_hop<P, DAG, 6>(k, i, p, lane, lds); break;
+      default: dirac_split_hop<P, DAG, 7>(k, i, p, lane, lds); break;
+    }
+  }
+  constexpr int NW = SplitOut<P>::NW;
+  switch (w) {
+    case 0: dirac_split_wave<P, DAG, EPI, NORM, 0>(k, i, p, lane, lds); break;
+    case 1: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, 1>(k, i, p, lane, lds); break; }
+    case 2: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, 2>(k, i, p, lane, lds); break; }
+    case 3: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 3>(k, i, p, lane, lds); break; }
+    case 4: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 4>(k, i, p, lane, lds); break; }
+    case 5: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 5>(k, i, p, lane, lds); break; }
+    default: __syncthreads(); break;
+  }
+  if constexpr (NORM) {
+    __syncthreads();
+    if (w == 0) {
+      double nrm = 0.0;
+      if (i < k.g.vh) nrm = split_norm<P, DAG>(lds, lane, std::make_integer_sequence<int, 12>{});
+      nrm = wave_sum(nrm);
+      if (lane == 0) k.partials[p * k.nt + tile] = nrm;
+    }
+  }
+}
+
+template <int P, bool DAG>
+void launch_split(const KDirac &k, int epi, bool norm, unsigned nblk, hipStream_t st) {
+#define WD_DS(E, N) \
+  if (epi == E && norm == N) hipLaunchKernelGGL((k_dirac_split<P, DAG, E, N>), dim3(nblk), dim3(SPLIT_BS), 0, st, k);
+  WD_DS(0, false) WD_DS(1, false) WD_DS(2, false) WD_DS(0, true) WD_DS(1, true) WD_DS(2, true)
+#undef WD_DS
+}
+
 template <int P, bool DAG, bool LDS>
 void launch_p(const KDirac &k, int epi, bool xin, bool norm, unsigned nblk, size_t lds, hipStream_t st) {
 #define WD_DR(E, XI, N)                    \
@@ -562,7 +751,7 @@ MarchGrid march_grid_of(const wd_gauge *g, wd_prec prec) {
 bool dirac_variant_ok(const wd_gauge *g, wd_prec prec, int slices, int tile) {
   const Geom &G = g->geom;
   if (slices < 0 || slices > G.L[3]) return false;
-  if (tile == 0) return true;
+  if (tile == 0 || tile == 4) return true;
   if (tile == 2) return march_brick_n2(G) > 0;
   if (tile == 3)
     return march_brick_n2(G) > 0 && (prec == WD_F64 || prec == WD_F32) &&
@@ -573,6 +762,7 @@ bool dirac_variant_ok(const wd_gauge *g, wd_prec prec, int slices, int tile) {
 wd_status dirac_init(wd_gauge *g) {
   // default tiles: bricks staged in LDS where they fit (FP64, FP32), else bricks, else consecutive sites
   for (int p = 0; p < 4; ++p) {
+    g->dirac_auto[p] = 1;
     g->dirac_slices[p] = 0;
     g->dirac_tile[p] = march_brick_n2(g->geom) ? 2 : 0;
   }
@@ -590,9 +780,16 @@ wd_status dirac_init(wd_gauge *g) {
   return WD_OK;
 }
 
-bool dirac_fills_device(const wd_gauge *g, wd_prec prec) {
-  const int cap = march_capacity(g, prec);
-  return 2 * march_grid_of(g, prec).items >= cap;
+// A handle whose variant was neither set nor tuned runs tile 4 unless the
+// staged bricks fit and fill the device (one block on at least 95% of the
+// resident slots): then the march, which fetches nothing twice, is ahead.
+// us per launch, tile 4 against the march's default: FP64 8^3x16 4.5 / 64,
+// 16^3x32 23 / 69, 24^3x48 127 / 175 (no bricks), 16x32x32x96 274 / 321 (192
+// of 256 slots), 32^3x32 189 / 180 and 32^3x64 373 / 349 (all slots); FP32
+// 24^3x48 55 / 82, 32^3x64 185 / 174; BF16 (no staging) 32^3x64 143 / 213.
+static bool dirac_uses_split(const wd_gauge *g, wd_prec prec) {
+  if (!g->dirac_auto[prec]) return g->dirac_tile[prec] == 4;
+  return g->dirac_tile[prec] != 3 || march_grid_of(g, prec).items < 0.95 * march_capacity(g, prec);
 }
 
 wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipStream_t st) {
@@ -615,6 +812,29 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
   k.partials = a.red.partials;
   k.skip = a.skip;
   if ((int)prec < 0 || (int)prec > 3) return set_error(WD_ERR_PREC, "dirac: unknown precision %d", (int)prec);
+  const int epi = a.Y ? 2 : (a.X ? 1 : 0);
+  if (dirac_uses_split(g, prec)) {
+    k.nt = g->geom.vpad / SPLIT_SITES;
+    k.per = (k.nt + 7) / 8;
+    // the order of the single-parity hop, for the same reasons: us with
+    // regions against ranges, FP64 32^3x64 373 / 402, FP32 16^3x32 13.6 / 12.8
+    const bool regions = g->geom.vh >= (1 << 18) && dslash_variant_ok(g->geom, SPLIT_SITES, 8);
+    k.S = regions ? g->geom.vh / g->geom.L[3] / SPLIT_SITES : 0;
+    const unsigned grid = regions ? 2u * (unsigned)k.nt : 16u * (unsigned)k.per;
+#define WD_DP(PR) \
+  if (a.dagger) launch_split<PR, true>(k, epi, norm, grid, st); else launch_split<PR, false>(k, epi, norm, grid, st);
+    switch (prec) {
+      case WD_F64: WD_DP(WD_F64) break;
+      case WD_F32: WD_DP(WD_F32) break;
+      case WD_F16: WD_DP(WD_F16) break;
+      case WD_BF16: WD_DP(WD_BF16) break;
+    }
+#undef WD_DP
+    WD_TRY(hip_check(hipGetLastError(), "dirac launch"));
+    if (norm)
+      return launch_finish_sums(k.partials, 2u * (unsigned)k.nt, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
+    return WD_OK;
+  }
   const MarchGrid mg = march_grid_of(g, prec);
   k.nsp = mg.nsp;
   k.nt = mg.nt;
@@ -629,7 +849,6 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
     return set_error(WD_ERR_ARG, "dirac: the LDS-staged variant does not fit this lattice / precision");
   k.nslot = staged ? march_nslot(g->geom, mg.n2) : 0;
   const size_t lds = staged ? march_lds_bytes(g->geom, prec) : 0;
-  const int epi = a.Y ? 2 : (a.X ? 1 : 0);
   const bool xin = a.X && a.X == a.in;
   const unsigned nblk = 8u * (unsigned)mg.per;
   // the reduction buffers hold at least this many partials (sized for the hop and level-1 grids)

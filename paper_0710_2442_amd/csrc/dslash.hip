@@ -8,8 +8,9 @@
 // backward link U^dag_{x-mu,mu} is kept at x), so all 8 link loads are
 // aligned, coalesced, read-once streams; neighbour spinors are the only
 // gathered, reused data.  A tuning variant stages each block's input tile in
-// LDS for the x1 and x2 neighbours.  The epilogue fuses out = a*H in + X - Y
-// and an FP64 |out|^2 reduction.
+// LDS for the x1 and x2 neighbours; the default gives every hop direction a
+// wave of its own.  The epilogue fuses out = a*H in + X and an FP64 |out|^2
+// reduction.
 //
 // Flop count per output site: 1320 (Sec. 5), plus 8 x 42 for rebuilding the
 // third link rows.  Algorithmic bytes per output site: 8 x 12 link reals +
@@ -21,7 +22,7 @@
 
 namespace wd {
 
-// EPI: 0 -> out = a H in;  1 -> out = X + a H in;  2 -> out = X - Y + a H in
+// EPI: 0 -> out = a H in;  1 -> out = X + a H in
 // OCC > 0 asks the compiler for at least OCC waves per SIMD (fewer registers,
 // possibly a few spills); OCC = 0 leaves the register budget to the compiler.
 #define WD_OCC_KERNEL(OCCV, ATTR)                                                   \
@@ -167,12 +168,10 @@ static void launch_epi(const KDslash &k, int epi, bool norm, unsigned nblk, unsi
                        hipStream_t st) {
   if (norm) {
     if (epi == 0) launch_t<P, DAG, 0, true>(k, nblk, bs, lds, st);
-    else if (epi == 1) launch_t<P, DAG, 1, true>(k, nblk, bs, lds, st);
-    else launch_t<P, DAG, 2, true>(k, nblk, bs, lds, st);
+    else launch_t<P, DAG, 1, true>(k, nblk, bs, lds, st);
   } else {
     if (epi == 0) launch_t<P, DAG, 0, false>(k, nblk, bs, lds, st);
-    else if (epi == 1) launch_t<P, DAG, 1, false>(k, nblk, bs, lds, st);
-    else launch_t<P, DAG, 2, false>(k, nblk, bs, lds, st);
+    else launch_t<P, DAG, 1, false>(k, nblk, bs, lds, st);
   }
 }
 
@@ -247,14 +246,11 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
   k.in = (const char *)a.in;
   k.out = (char *)a.out;
   k.X = (const char *)a.X;
-  k.Y = (const char *)a.Y;
   k.a = a.a;
   k.norm_out = a.norm_out;
-  k.norm_accumulate = a.norm_accumulate;
   k.skip = a.skip;
   k.partials = a.red.partials;
-  const int epi = a.Y ? 2 : (a.X ? 1 : 0);
-  if (a.Y && !a.X) return set_error(WD_ERR_ARG, "dslash epilogue: Y given without X");
+  const int epi = a.X ? 1 : 0;
   const bool norm = a.norm_out != nullptr;
   if (norm && !k.partials) return set_error(WD_ERR_ARG, "dslash norm: no reduction buffer");
   const int pi = (int)prec;
@@ -287,7 +283,7 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
     default: return set_error(WD_ERR_PREC, "dslash: unknown precision %d", (int)prec);
   }
   WD_TRY(hip_check(hipGetLastError(), "dslash launch"));
-  if (norm) return launch_finish_sums(k.partials, nblk, 1, k.norm_out, 1, k.norm_accumulate, k.skip, 1, st);
+  if (norm) return launch_finish_sums(k.partials, nblk, 1, k.norm_out, 1, 0, k.skip, 1, st);
   return WD_OK;
 }
 

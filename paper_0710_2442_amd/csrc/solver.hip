@@ -1,7 +1,7 @@
 // Solvers for D_W x = b built on the single-parity hop kernels.
 //
 // * FP64 full-lattice CGLS: CG on D^dag D x = D^dag b on full fields, each
-//   operator application one hop launch per parity (no even-odd reduction).
+//   operator application one launch of D_W (no even-odd reduction).
 // * FP64 even-odd CGLS: CG on the normal equations of the Schur operator
 //   M = 1 - k^2 H_eo H_oe (M^dag = 1 - k^2 H^dag_eo H^dag_oe), right-hand
 //   side b_e + k H_eo b_o, odd sites x_o = b_o + k H_oe x_e.  The paper
@@ -130,42 +130,23 @@ struct CglsVecs {
 
 // out = A in (dagger: A^dag in), |out|^2 -> norm: A = M = 1 - k^2 H_eo H_oe on
 // even halves (two hops, the first into t), or A = D_W = 1 - k H on full
-// fields (the one-launch marching kernel where it fills the device, else one
-// hop per parity with the norm summed over both).
+// fields.
 static wd_status apply_op(const wd_gauge *g, const CglsVecs &v, double kappa, const void *in, void *out, int dagger,
                           double *norm, const int *skip, RedBuf red, hipStream_t st) {
   if (!v.full) {
     WD_TRY(hop(g, v.pv, v.nsys, HopCall{in, v.t, nullptr, 1.0, 1, dagger, nullptr, skip}, red, st));
     return hop(g, v.pv, v.nsys, HopCall{v.t, out, in, -kappa * kappa, 0, dagger, norm, skip}, red, st);
   }
-  if (dirac_fills_device(g, v.pv)) {
-    DiracArgs a;
-    a.in = in;
-    a.out = out;
-    a.X = in;
-    a.a = -kappa;
-    a.dagger = dagger;
-    a.norm_out = norm;
-    a.skip = skip;
-    a.red = red;
-    return launch_dirac(g, v.pv, a, st);
-  }
-  const size_t hb = half_bytes(g->geom, v.pv);
-  for (int par = 0; par < 2; ++par) {
-    DslashArgs a;
-    a.in = (const char *)in + (1 - par) * hb;
-    a.out = (char *)out + par * hb;
-    a.X = (const char *)in + par * hb;
-    a.a = -kappa;
-    a.parity = par;
-    a.dagger = dagger;
-    a.norm_out = norm;
-    a.norm_accumulate = par;
-    a.skip = skip;
-    a.red = red;
-    WD_TRY(launch_dslash(g, v.pv, a, st));
-  }
-  return WD_OK;
+  DiracArgs a;
+  a.in = in;
+  a.out = out;
+  a.X = in;
+  a.a = -kappa;
+  a.dagger = dagger;
+  a.norm_out = norm;
+  a.skip = skip;
+  a.red = red;
+  return launch_dirac(g, v.pv, a, st);
 }
 
 // q = A p -> qq;  cg_update;  r = A^dag s -> rr[1-j];  p = r + beta p
@@ -254,34 +235,16 @@ wd_status true_residual64(const wd_gauge *g, const void *b, const void *x, void 
                           double kappa, CgScalars *sc, RedBuf red, hipStream_t st) {
   const size_t hb = half_bytes(g->geom, WD_F64);
   if (nsys == 1) {
-    // r = b - x + kappa H x with |r|^2: the one-launch marching D_W where its
-    // work items fill the device (each link and spinor fetched once), else
-    // two single-parity launches with the xpay and norm epilogues
-    if (dirac_fills_device(g, WD_F64)) {
-      DiracArgs a;
-      a.in = x;
-      a.out = r;
-      a.X = b;
-      a.Y = x;
-      a.a = kappa;
-      a.norm_out = &sc->rnorm2;
-      a.red = red;
-      return launch_dirac(g, WD_F64, a, st);
-    }
-    for (int par = 0; par < 2; ++par) {
-      DslashArgs a;
-      a.in = (const char *)x + (1 - par) * hb;
-      a.out = (char *)r + par * hb;
-      a.X = (const char *)b + par * hb;
-      a.Y = (const char *)x + par * hb;
-      a.a = kappa;
-      a.parity = par;
-      a.norm_out = &sc->rnorm2;
-      a.norm_accumulate = par;
-      a.red = red;
-      WD_TRY(launch_dslash(g, WD_F64, a, st));
-    }
-    return WD_OK;
+    // r = b - x + kappa H x with |r|^2 in one launch of D_W
+    DiracArgs a;
+    a.in = x;
+    a.out = r;
+    a.X = b;
+    a.Y = x;
+    a.a = kappa;
+    a.norm_out = &sc->rnorm2;
+    a.red = red;
+    return launch_dirac(g, WD_F64, a, st);
   }
   for (int par = 0; par < 2; ++par) {
     MrhsArgs m;

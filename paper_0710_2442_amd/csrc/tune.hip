@@ -510,6 +510,7 @@ wd_status wd_set_dirac_variant(wd_gauge *g, wd_prec prec, int slices, int tile) 
                      tile, g->dims[0], g->dims[1], g->dims[2], g->dims[3]);
   g->dirac_slices[prec] = slices;
   g->dirac_tile[prec] = tile;
+  g->dirac_auto[prec] = 0;
   return WD_OK;
 }
 
@@ -545,7 +546,7 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
   hipEvent_t e0 = nullptr, e1 = nullptr;
   wd_status rc = WD_OK;
   int *flag = nullptr;
-  const int save_s = g->dirac_slices[prec], save_t = g->dirac_tile[prec];
+  const int save_s = g->dirac_slices[prec], save_t = g->dirac_tile[prec], save_a = g->dirac_auto[prec];
   int best_s = save_s, best_t = save_t;
   double best_us = 1e30;
   DiracArgs a;
@@ -574,6 +575,7 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
     a.out = ref;
     if ((rc = launch_dirac(g, prec, a, st)) != WD_OK) break;
     std::vector<std::array<int, 2>> cands;
+    cands.push_back({0, 4});
     for (int tile : {3, 2, 0})
       for (int sl = 8;; sl *= 2) {
         const int S = std::min(sl, G.L[3]);
@@ -584,6 +586,7 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
     for (const auto &c : cands) {
       g->dirac_slices[prec] = c[0];
       g->dirac_tile[prec] = c[1];
+      g->dirac_auto[prec] = 0;
       if ((rc = hip_check(hipMemsetAsync(cand, 0xff, fb, st), "memset")) != WD_OK) break;
       if ((rc = launch_dirac(g, prec, a, st)) != WD_OK) break;
       bool same = false;
@@ -605,6 +608,7 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
   } while (0);
   g->dirac_slices[prec] = (rc == WD_OK) ? best_s : save_s;
   g->dirac_tile[prec] = (rc == WD_OK) ? best_t : save_t;
+  g->dirac_auto[prec] = (rc == WD_OK) ? 0 : save_a;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (in) (void)hipFree(in);

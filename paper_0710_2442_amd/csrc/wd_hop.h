@@ -479,7 +479,7 @@ struct SplitLds {
     return *(double *)&g[(6 * d + C % 6) * SPLIT_SITES + lane];
   }
 };
-// waves per SIMD the register budget is held to (whole blocks: 2 a block and SIMD)
+// waves per SIMD the register budget is held to (a block adds 2 to each SIMD)
 constexpr int split_occ(int prec, int epi) {
   return prec == WD_F64 ? 6 : prec == WD_F16 ? (epi == 2 ? 4 : 6) : (prec == WD_BF16 && epi == 2) ? 6 : 8;
 }

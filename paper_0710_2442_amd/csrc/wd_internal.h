@@ -90,6 +90,7 @@ struct wd_gauge {
   int dirac_bpc_lds[2];    // FP64, FP32: the same for its LDS-staged form (0: does not fit)
   int dirac_slices[4];     // per precision: time slices per range of the one-launch D_W (0: from occupancy)
   int dirac_tile[4];       // per precision: its tiles, 2 = bricks of L1 x n2 x 2 sites, 0 = consecutive sites
+  int dirac_auto[4];       // per precision: 1 = variant neither set nor tuned (tile 4 by the lattice's size)
   hipStream_t stream;      // caller's stream for dslash / pack
   hipStream_t own_stream;  // library stream for synchronous solves (default priority)
   void *links64;
@@ -135,8 +136,8 @@ wd_status hip_check(hipError_t e, const char *what);
 // All launchers are asynchronous on `st`.
 
 // Eq. 3 on one checkerboard with fused epilogue:
-//   out = a * H_{p,1-p} in  +  (X ? X : 0)  -  (Y ? Y : 0)
-// X, Y, out are half fields of parity p; `in` is a half field of parity 1-p.
+//   out = a * H_{p,1-p} in  +  (X ? X : 0)
+// X, out are half fields of parity p; `in` is a half field of parity 1-p.
 // All fields in precision `prec`; links in double for WD_F64, float otherwise.
 // If norm_out != NULL the FP64 |out|^2 is written there (device).  If skip !=
 // NULL and *skip != 0 the launch does nothing.
@@ -149,12 +150,10 @@ struct DslashArgs {
   const void *in = nullptr;
   void *out = nullptr;
   const void *X = nullptr;
-  const void *Y = nullptr;
   double a = 1.0;
   int parity = 0;
   int dagger = 0;
   double *norm_out = nullptr;  // device
-  int norm_accumulate = 0;     // add to *norm_out instead of overwriting
   const int *skip = nullptr;   // device flag
   RedBuf red{nullptr};
 };
@@ -175,8 +174,6 @@ struct DiracArgs {
 wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &args, hipStream_t st);
 // one-launch D_W: occupancy of its kernels, queried once per handle (dirac.hip)
 wd_status dirac_init(wd_gauge *g);
-// whether the one-launch D_W has work items for at least half of the device's resident blocks
-bool dirac_fills_device(const wd_gauge *g, wd_prec prec);
 // whether (time slices per range, tile shape) is a valid one-launch D_W variant for the lattice
 bool dirac_variant_ok(const wd_gauge *g, wd_prec prec, int slices, int tile);
 // out[j * ostride] = (accumulate ? out[j * ostride] : 0) + sum over b of

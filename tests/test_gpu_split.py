@@ -1,6 +1,7 @@
-"""The hop with one wave per direction (WD_TUNE_SPLIT_DIRS, the variant of a
-new handle): the same bytes as the one-site-per-lane hop in every storage
-precision, order and epilogue.  Sizes: one slot tile mostly padding (2^4: 8
+"""The hop and D_W with one wave per hop direction (WD_TUNE_SPLIT_DIRS and
+one-launch tile 4, what a new handle runs): the same bytes as the
+one-site-per-lane hop and as the march in every storage precision, order and
+epilogue.  Sizes: one slot tile mostly padding (2^4: 8
 sites), fewer tiles than XCDs, padding in the last tile, ranges whose last
 blocks are empty, extents of 2 (forward and backward neighbours coincide)."""
 import pytest
@@ -72,4 +73,35 @@ def test_split_hop_in_a_solve_is_bitwise_the_one_lane_hop(dims, inner):
         outs.append((x, info["iters"], info["outer_iters"]))
     for o in outs[1:]:
         assert o[1:] == outs[0][1:] and torch.equal(o[0], outs[0][0])
+    g.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 6, 10), (2, 6, 2, 34), (16, 8, 8, 16), (16, 32, 32, 32)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+def test_split_dirac_is_bitwise_the_march(dims, prec):
+    """Tile 4, set and as a new handle chooses it (16x32^3: 2^18 sites per
+    parity, the order of slice regions), against consecutive marching tiles."""
+    gen = torch.Generator().manual_seed(65)
+    L1, L2, L3, L4 = dims
+    if L1 * L2 * L3 * L4 > 100000:  # links from one block repeated along x4
+        U = syn.gauge_field((L1, L2, L3, 2), 0.3, 66)
+        U = U.repeat(L4 // 2, axis=0)
+    else:
+        U = syn.gauge_field(dims, 0.3, 66)
+    g = wd.Gauge(U, dims, -1, prec)
+    canon = torch.randn(L1 * L2 * L3 * L4 * 24, generator=gen, dtype=torch.float64)
+    src = to_field(g, torch.view_as_complex(canon.reshape(-1, 2)).numpy(), prec)
+    for flags in (0, wd.WD_DAGGER):
+        outs = []
+        for variant in (None, (0, 4), (0, 0)):
+            if variant:
+                wd.wd_set_dirac_variant(g, prec, *variant)
+                assert wd.wd_get_dirac_variant(g, prec) == variant
+            for one in (wd.WD_ONE_PASS, 0):
+                out = wd.wd_new_field(dims, prec)
+                out.fill_(0xAB)
+                wd.wd_dslash_ex(g, src, out, 0.124, wd.WD_FULL, prec, flags | one)
+                torch.cuda.synchronize()
+                outs.append(out)
+        assert all(torch.equal(o, outs[0]) for o in outs[1:]), flags
     g.close()
