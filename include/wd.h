@@ -83,17 +83,17 @@ typedef enum { WD_F64 = 0, WD_F32 = 1, WD_F16 = 2, WD_BF16 = 3 } wd_prec;
 enum { WD_EVEN = 0, WD_ODD = 1, WD_FULL = 2 };
 
 /* flags of wd_dslash_ex.  WD_DAGGER: apply H^dag (D_W^dag).  WD_ONE_PASS
- * (parity WD_FULL only): compute D_W in one full-lattice launch that takes
- * each site's backward links from its neighbours' forward links, so each link
- * is needed once per application (768 B per site in FP64).  WD_FULL runs this
- * way with and without the flag, in one of two forms of the same arithmetic
- * (wd_tune_dirac):
- * marching along x4 through ranges of time slices, one spatial site per lane,
- * the way Sec. 5 streams a lattice held in main memory a slice at a time (the
- * time link, the backward time hop and the partial output pass from one slice
- * to the next in registers, so each link and spinor is fetched once), for
- * lattices whose ranges fill the device; and one wave per hop direction, for
- * the others. */
+ * (parity WD_FULL only): compute D_W by the one-launch scheme that marches
+ * along x4 through ranges of time slices, one spatial site per lane, the way
+ * Sec. 5 streams a lattice held in main memory a slice at a time: the time
+ * link, the backward time hop and the partial output (which starts from
+ * psi_in) pass from one slice to the next in registers, so each link and
+ * spinor is fetched once (768 B per site in FP64).  The same arithmetic with
+ * one wave per hop direction instead of the march is another variant of it
+ * (wd_tune_dirac), used where the ranges do not fill the device.  Without the
+ * flag WD_FULL adds the hops first, as two single-parity hops would, also in
+ * one launch with one wave per hop direction; backward links are the
+ * neighbours' forward links in either case. */
 enum { WD_DAGGER = 1, WD_ONE_PASS = 2 };
 
 typedef struct wd_gauge wd_gauge;

@@ -278,6 +278,7 @@ static wd_status dslash_common(const wd_gauge *U, const void *in, void *out, dou
                                                           : (size_t)((const char *)in - (const char *)out);
   if (ob < 2 * hb) return set_error(WD_ERR_ARG, "dslash: full fields overlap");
   DiracArgs a;
+  a.form = (flags & WD_ONE_PASS) ? DiracArgs::ONE_PASS : DiracArgs::HOPS;
   a.in = in; a.out = out; a.X = in; a.a = -kappa; a.dagger = dag;
   return launch_dirac(U, prec, a, U->stream);
 }

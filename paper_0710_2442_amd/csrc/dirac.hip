@@ -487,10 +487,12 @@ __global__ __launch_bounds__(DM_BS) void k_dirac_march(KDirac k) {
 // one hop direction per wave, as k_dslash_split does, with the backward hops
 // on the neighbours' forward links (U^dag), so each link is fetched from HBM
 // for one of its two uses and found in the caches for the other: the two
-// parities' tiles of the same sites follow each other on one XCD.  Same
-// products and the same order of additions as the march, hence the same
-// bytes.
-template <int P, bool DAG, int D>
+// parities' tiles of the same sites follow each other on one XCD.  LATE =
+// false: the march's products and order of additions, hence its bytes.  LATE
+// = true: the single-parity hop's, out = X + a (sum of the hops) - Y, as
+// WD_FULL without WD_ONE_PASS and the solvers take it: in FP32 its error
+// against 64 bits is 4.7e-8, where adding a times each hop to X gives 7.2e-8.
+template <int P, bool DAG, bool LATE, int D>
 __device__ __forceinline__ void dirac_split_hop(const KDirac &k, int i, int p, int lane, SplitLds<P> &lds) {
   using T = RealOf<P>;
   constexpr int MU = D & 3;
@@ -502,17 +504,19 @@ __device__ __forceinline__ void dirac_split_hop(const KDirac &k, int i, int p, i
   cplx<T> u[6], h[6], r2[3];
   if constexpr (FWD) Link<T>::template load<false>(k.links[p], MU, i, u);
   else Link<T>::template load<false>(k.links[1 - p], MU, nb, u);
-  T f = (T)k.a;
+  T f = LATE ? (T)1 : (T)k.a;
   if constexpr (MU == 3) {
     Spinor<P>::template load_half<(S < 0)>(in, nb, h);
-    f = (T)2 * (edge ? (T)k.g.tbc : (T)1) * (T)k.a;
+    f = (T)2 * (edge ? (T)k.g.tbc : (T)1) * f;
   } else {
     cplx<T> psi[12];
     Spinor<P>::load(in, nb, psi);
     project<MU, S>(psi, h);
   }
+  if constexpr (!LATE || MU == 3) {
 #pragma unroll
-  for (int c = 0; c < 6; ++c) h[c] = f * h[c];
+    for (int c = 0; c < 6; ++c) h[c] = f * h[c];
+  }
   cplx<T> *q = lds.g + D * 6 * SPLIT_SITES + lane;
   // (the order keeps few registers live, see split_hop)
   if constexpr (P == WD_F64) __builtin_amdgcn_sched_barrier(0);
@@ -551,13 +555,15 @@ __device__ __forceinline__ void dirac_split_hop(const KDirac &k, int i, int p, i
   }
 }
 
-// Output component C: acc0 = X - Y plus the hops in the march's order
-// (backward time, then both of x1, x2, x3, then forward time).
-template <int P, bool DAG, int C>
+// Output component C: LATE = false: acc = X - Y plus the scaled hops in the
+// march's order (backward time, then both of x1, x2, x3, then forward time).
+// LATE = true: the sum of the hops in the single-parity hop's order.
+template <int P, bool DAG, bool LATE, int C>
 __device__ __forceinline__ cplx<RealOf<P>> dirac_split_sum(const SplitLds<P> &lds, int lane, cplx<RealOf<P>> acc) {
   using T = RealOf<P>;
   constexpr int sp = C / 3, a = C % 3;
-  constexpr int order[8] = {7, 0, 4, 1, 5, 2, 6, 3};
+  constexpr int order[8] = {LATE ? 0 : 7, LATE ? 1 : 0, LATE ? 2 : 4, LATE ? 3 : 1,
+                            LATE ? 4 : 5, LATE ? 5 : 2, 6, LATE ? 7 : 3};
   const cplx<T> *g = lds.g + lane;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -575,14 +581,21 @@ __device__ __forceinline__ cplx<RealOf<P>> dirac_split_sum(const SplitLds<P> &ld
   return acc;
 }
 
-template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
+template <int P, bool DAG, bool LATE, bool NORM, int W, int... J>
 __device__ __forceinline__ void dirac_split_finish(const KDirac &k, int i, char *out, int lane, SplitLds<P> &lds,
                                                    cplx<RealOf<P>> (&o)[SplitOut<P>::CW],
+                                                   const cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
                                                    std::integer_sequence<int, J...>) {
   using T = RealOf<P>;
   constexpr int CW = SplitOut<P>::CW;
   if (i < k.g.vh) {
-    ((o[J] = dirac_split_sum<P, DAG, W * CW + J>(lds, lane, o[J])), ...);
+    if constexpr (LATE) {
+      const T a = (T)k.a;
+      const cplx<T> z = {(T)0, (T)0};
+      ((o[J] = (a * dirac_split_sum<P, DAG, true, W * CW + J>(lds, lane, z) + o[J]) - y[J]), ...);
+    } else {
+      ((o[J] = dirac_split_sum<P, DAG, false, W * CW + J>(lds, lane, o[J])), ...);
+    }
   } else {
 #pragma unroll
     for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
@@ -592,28 +605,31 @@ __device__ __forceinline__ void dirac_split_finish(const KDirac &k, int i, char 
     ((lds.template n2<DAG, W * CW + J>(lane) = (double)o[J].re * o[J].re + (double)o[J].im * o[J].im), ...);
 }
 
-template <int P, bool DAG, int EPI, bool NORM, int W>
+template <int P, bool DAG, int EPI, bool NORM, bool LATE, int W>
 __device__ __forceinline__ void dirac_split_wave(const KDirac &k, int i, int p, int lane, SplitLds<P> &lds) {
   using T = RealOf<P>;
   constexpr int CW = SplitOut<P>::CW;
   const size_t off = (size_t)p * k.half;
-  cplx<T> o[CW];
+  cplx<T> o[CW], y[CW];
 #pragma unroll
-  for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
+  for (int j = 0; j < CW; ++j) o[j] = y[j] = {(T)0, (T)0};
   if (i < k.g.vh) {
-    if constexpr (EPI >= 1) split_load<P, W>(k.X + off, i, o);
+    split_load<P, W>(k.X + off, i, o);
     if constexpr (EPI == 2) {
-      cplx<T> y[CW];
       split_load<P, W>(k.Y + off, i, y);
+      if constexpr (!LATE) {
 #pragma unroll
-      for (int j = 0; j < CW; ++j) o[j] = o[j] - y[j];
+        for (int j = 0; j < CW; ++j) o[j] = o[j] - y[j];
+      }
     }
   }
   __syncthreads();
-  dirac_split_finish<P, DAG, EPI, NORM, W>(k, i, k.out + off, lane, lds, o, std::make_integer_sequence<int, CW>{});
+  dirac_split_finish<P, DAG, LATE, NORM, W>(k, i, k.out + off, lane, lds, o, y,
+                                            std::make_integer_sequence<int, CW>{});
 }
 
-template <int P, bool DAG, int EPI, bool NORM>
+// EPI 1: out = X + a H in;  2: out = X - Y + a H in.
+template <int P, bool DAG, int EPI, bool NORM, bool LATE>
 __global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDirac k) {
   __shared__ SplitLds<P> lds;
   if (k.skip && *k.skip) return;
@@ -632,24 +648,24 @@ __global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDi
   const int i = tile * SPLIT_SITES + lane;
   if (i < k.g.vh) {
     switch (w) {
-      case 0: dirac_split_hop<P, DAG, 0>(k, i, p, lane, lds); break;
-      case 1: dirac_split_hop<P, DAG, 1>(k, i, p, lane, lds); break;
-      case 2: dirac_split_hop<P, DAG, 2>(k, i, p, lane, lds); break;
-      case 3: dirac_split_hop<P, DAG, 3>(k, i, p, lane, lds); break;
-      case 4: dirac_split_hop<P, DAG, 4>(k, i, p, lane, lds); break;
-      case 5: dirac_split_hop<P, DAG, 5>(k, i, p, lane, lds); break;
-      case 6: dirac_split_hop<P, DAG, 6>(k, i, p, lane, lds); break;
-      default: dirac_split_hop<P, DAG, 7>(k, i, p, lane, lds); break;
+      case 0: dirac_split_hop<P, DAG, LATE, 0>(k, i, p, lane, lds); break;
+      case 1: dirac_split_hop<P, DAG, LATE, 1>(k, i, p, lane, lds); break;
+      case 2: dirac_split_hop<P, DAG, LATE, 2>(k, i, p, lane, lds); break;
+      case 3: dirac_split_hop<P, DAG, LATE, 3>(k, i, p, lane, lds); break;
+      case 4: dirac_split_hop<P, DAG, LATE, 4>(k, i, p, lane, lds); break;
+      case 5: dirac_split_hop<P, DAG, LATE, 5>(k, i, p, lane, lds); break;
+      case 6: dirac_split_hop<P, DAG, LATE, 6>(k, i, p, lane, lds); break;
+      default: dirac_split_hop<P, DAG, LATE, 7>(k, i, p, lane, lds); break;
     }
   }
   constexpr int NW = SplitOut<P>::NW;
   switch (w) {
-    case 0: dirac_split_wave<P, DAG, EPI, NORM, 0>(k, i, p, lane, lds); break;
-    case 1: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, 1>(k, i, p, lane, lds); break; }
-    case 2: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, 2>(k, i, p, lane, lds); break; }
-    case 3: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 3>(k, i, p, lane, lds); break; }
-    case 4: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 4>(k, i, p, lane, lds); break; }
-    case 5: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, 5>(k, i, p, lane, lds); break; }
+    case 0: dirac_split_wave<P, DAG, EPI, NORM, LATE, 0>(k, i, p, lane, lds); break;
+    case 1: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 1>(k, i, p, lane, lds); break; }
+    case 2: if constexpr (NW > 1) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 2>(k, i, p, lane, lds); break; }
+    case 3: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 3>(k, i, p, lane, lds); break; }
+    case 4: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 4>(k, i, p, lane, lds); break; }
+    case 5: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 5>(k, i, p, lane, lds); break; }
     default: __syncthreads(); break;
   }
   if constexpr (NORM) {
@@ -664,10 +680,12 @@ __global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDi
 }
 
 template <int P, bool DAG>
-void launch_split(const KDirac &k, int epi, bool norm, unsigned nblk, hipStream_t st) {
-#define WD_DS(E, N) \
-  if (epi == E && norm == N) hipLaunchKernelGGL((k_dirac_split<P, DAG, E, N>), dim3(nblk), dim3(SPLIT_BS), 0, st, k);
-  WD_DS(0, false) WD_DS(1, false) WD_DS(2, false) WD_DS(0, true) WD_DS(1, true) WD_DS(2, true)
+void launch_split(const KDirac &k, int epi, bool norm, bool late, unsigned nblk, hipStream_t st) {
+#define WD_DS(E, N, L)                            \
+  if (epi == E && norm == N && late == L)         \
+    hipLaunchKernelGGL((k_dirac_split<P, DAG, E, N, L>), dim3(nblk), dim3(SPLIT_BS), 0, st, k);
+  WD_DS(1, false, false) WD_DS(1, false, true)
+  if constexpr (P == WD_F64) { WD_DS(1, true, true) WD_DS(2, true, true) }
 #undef WD_DS
 }
 
@@ -813,7 +831,12 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
   k.skip = a.skip;
   if ((int)prec < 0 || (int)prec > 3) return set_error(WD_ERR_PREC, "dirac: unknown precision %d", (int)prec);
   const int epi = a.Y ? 2 : (a.X ? 1 : 0);
-  if (dirac_uses_split(g, prec)) {
+  if (a.form == DiracArgs::HOPS || dirac_uses_split(g, prec)) {
+    const bool late = a.form != DiracArgs::ONE_PASS;
+    // the forms that launch_split has
+    if (epi == 0 || ((epi == 2 || norm) && (prec != WD_F64 || !late)) || (epi == 2 && !norm))
+      return set_error(WD_ERR_ARG, "dirac: epilogue %d, norm %d in precision %d is not a one-wave-per-hop form", epi,
+                       (int)norm, (int)prec);
     k.nt = g->geom.vpad / SPLIT_SITES;
     k.per = (k.nt + 7) / 8;
     // the order of the single-parity hop, for the same reasons: us with
@@ -822,7 +845,8 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
     k.S = regions ? g->geom.vh / g->geom.L[3] / SPLIT_SITES : 0;
     const unsigned grid = regions ? 2u * (unsigned)k.nt : 16u * (unsigned)k.per;
 #define WD_DP(PR) \
-  if (a.dagger) launch_split<PR, true>(k, epi, norm, grid, st); else launch_split<PR, false>(k, epi, norm, grid, st);
+  if (a.dagger) launch_split<PR, true>(k, epi, norm, late, grid, st); \
+  else launch_split<PR, false>(k, epi, norm, late, grid, st);
     switch (prec) {
       case WD_F64: WD_DP(WD_F64) break;
       case WD_F32: WD_DP(WD_F32) break;

@@ -76,6 +76,7 @@ wd_status scale(FgcrCtx &c, void *x, double s) {
 wd_status apply_D(FgcrCtx &c, const void *in, void *out, double kappa) {
   c.dslash_calls += 2;
   DiracArgs a;
+  a.form = DiracArgs::SOLVER;
   a.in = in;
   a.out = out;
   a.X = in;

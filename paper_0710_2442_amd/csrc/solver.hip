@@ -138,6 +138,7 @@ static wd_status apply_op(const wd_gauge *g, const CglsVecs &v, double kappa, co
     return hop(g, v.pv, v.nsys, HopCall{v.t, out, in, -kappa * kappa, 0, dagger, norm, skip}, red, st);
   }
   DiracArgs a;
+  a.form = DiracArgs::SOLVER;
   a.in = in;
   a.out = out;
   a.X = in;
@@ -237,6 +238,7 @@ wd_status true_residual64(const wd_gauge *g, const void *b, const void *x, void 
   if (nsys == 1) {
     // r = b - x + kappa H x with |r|^2 in one launch of D_W
     DiracArgs a;
+    a.form = DiracArgs::SOLVER;
     a.in = x;
     a.out = r;
     a.X = b;

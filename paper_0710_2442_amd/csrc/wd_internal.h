@@ -160,6 +160,11 @@ struct DslashArgs {
 // Full-lattice D_W in one launch (dirac.hip): full fields in, out, X, Y;
 // out = a H in (+ X (- Y)), optional FP64 |out|^2 over both parities.
 struct DiracArgs {
+  // ONE_PASS: the arithmetic of the march, in whichever variant the handle
+  // uses; SOLVER: the march where the handle uses it, else the hop's
+  // arithmetic; HOPS: the arithmetic of the single-parity hop
+  enum Form { ONE_PASS, SOLVER, HOPS };
+  Form form = ONE_PASS;
   const void *in = nullptr;
   void *out = nullptr;
   const void *X = nullptr;
