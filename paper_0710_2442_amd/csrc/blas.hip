@@ -6,6 +6,8 @@
 // y's vectors start at y * sys_stride bytes and it owns its own scalar block
 // and reduction slots, so a batch of right-hand sides shares each launch.
 // A vector is `nhalf` half fields of vh valid sites (half_stride bytes apart).
+#include <algorithm>
+
 #include "wd_blas.h"
 #include "wd_device.h"
 
@@ -38,6 +40,13 @@ struct KBlas {
   int j;  // ping-pong slot of the CG iteration
   double *partials;
   double *result;  // reductions: per-system result (N doubles each)
+  // CG recurrences: the hop's norm partials, nparts per system (0: the sum is
+  // already in the scalars), and the |s|^2 partials of the update, nss per system
+  const double *parts;
+  unsigned nparts;
+  const double *ss_parts;
+  unsigned nss;
+  size_t npk;  // packets of a vector (all halves)
 };
 
 __device__ __forceinline__ bool site_of(const VecGeom &v, long f, int &h, int &i) {
@@ -211,101 +220,197 @@ __global__ __launch_bounds__(BLAS_BS) void k_accum(KBlas k) {
 }
 
 // ------------------------------------------------------------ CG recurrences
+// The scalars of a step are sums of the norm partials that the hop before it
+// left behind.  Where these are few, every block of the step adds them up
+// itself (sum_partials); else a finishing launch came first.  The vectors are
+// walked packet by packet (FP64, FP32, BF16), padding zeros included: small
+// fields spread over more threads than sites, and every access is contiguous.
+
+// Packets a thread has in flight at a time (the fields may alias for the
+// compiler, so the loads are grouped by hand).
+constexpr int CG_UNROLL = 2;
+
+// |M p|^2 of system sys: done = breakdown on a value that is no norm.
+__device__ __forceinline__ bool cg_alpha(const KBlas &k, int sys, double &alpha) {
+  CgScalars *sc = k.sc + sys;
+  double qq;
+  if (k.nparts) {
+    qq = sum_partials(k.parts + (size_t)sys * k.nparts, k.nparts);
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->qq = qq;
+  } else {
+    qq = sc->qq;
+  }
+  const double rr = sc->rr[k.j];
+  if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->done = 2;  // breakdown / non-finite
+    return false;
+  }
+  alpha = rr / qq;
+  return true;
+}
+
 // alpha = rr[j] / qq;  X += alpha P;  S -= alpha Q;  ss = |S|^2.
 // x = X (precision PX), y = P, out = S, out2 = Q (precision PV) -- Q is read only.
+// FP16 storage (a scale per site): one site per thread.
 template <int PX, int PV>
 __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
   using TV = RealOf<PV>;
   using TX = RealOf<PX>;
   const int sys = blockIdx.y;
-  CgScalars *sc = k.sc + sys;
-  if (sc->done) return;
-  const double qq = sc->qq;
-  if (!(qq > 0.0) || !(qq < 1e300) || !(sc->rr[k.j] < 1e300)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->done = 2;  // breakdown / non-finite
-    return;
-  }
-  const double alpha = sc->rr[k.j] / qq;
-  const long n = (long)k.v.vh * k.v.nhalf;
+  if (k.sc[sys].done) return;
+  double alpha;
+  if (!cg_alpha(k, sys, alpha)) return;
+  const TV a = (TV)alpha;
+  const TX ax = (TX)alpha;
+  char *X = (char *)k.x + sys * k.sx;
+  const char *Pv = k.y + sys * k.sy;
+  char *S = k.out + sys * k.so;
+  const char *Q = k.out2 + sys * k.so2;
   double acc = 0.0;
-  for (long f = (long)blockIdx.x * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
-    int h, i;
-    site_of(k.v, f, h, i);
-    cplx<TV> p[12], s[12], q[12];
-    cplx<TX> x[12];
-    char *X = (char *)k.x + sys * k.sx + h * k.hx;
-    const char *Pp = k.y + sys * k.sy + h * k.hy;
-    char *S = k.out + sys * k.so + h * k.ho;
-    const char *Q = k.out2 + sys * k.so2 + h * k.ho2;
-    Spinor<PV>::load(Pp, i, p);
-    Spinor<PV>::load(Q, i, q);
-    Spinor<PV>::load(S, i, s);
-    Spinor<PX>::load(X, i, x);
-    const TV a = (TV)alpha;
-    const TX ax = (TX)alpha;
+  if constexpr (PV == WD_F16) {
+    const long n = (long)k.v.vh * k.v.nhalf;
+    for (long f = (long)blockIdx.x * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
+      int h, i;
+      site_of(k.v, f, h, i);
+      cplx<TV> p[12], s[12], q[12];
+      cplx<TX> x[12];
+      Spinor<PV>::load(Pv + h * k.hy, i, p);
+      Spinor<PV>::load(Q + h * k.ho2, i, q);
+      Spinor<PV>::load(S + h * k.ho, i, s);
+      Spinor<PX>::load(X + h * k.hx, i, x);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      x[c].re = fma(ax, (TX)p[c].re, x[c].re);
-      x[c].im = fma(ax, (TX)p[c].im, x[c].im);
-      s[c].re = fma(-a, q[c].re, s[c].re);
-      s[c].im = fma(-a, q[c].im, s[c].im);
-    }
-    Spinor<PX>::store(X, i, x);
-    Spinor<PV>::store(S, i, s);
-    if constexpr (PV == WD_F64 || PV == WD_F32) {
+      for (int c = 0; c < 12; ++c) {
+        x[c].re = fma(ax, (TX)p[c].re, x[c].re);
+        x[c].im = fma(ax, (TX)p[c].im, x[c].im);
+        s[c].re = fma(-a, q[c].re, s[c].re);
+        s[c].im = fma(-a, q[c].im, s[c].im);
+      }
+      Spinor<PX>::store(X + h * k.hx, i, x);
+      Spinor<PV>::store(S + h * k.ho, i, s);
+      Spinor<PV>::load(S + h * k.ho, i, s);  // norm of the stored (rounded) residual
 #pragma unroll
       for (int c = 0; c < 12; ++c) acc += (double)s[c].re * s[c].re + (double)s[c].im * s[c].im;
-    } else {  // norm of the stored (rounded) residual
-      cplx<TV> r[12];
-      Spinor<PV>::load(S, i, r);
+    }
+  } else {
+    using KV = Packet<PV>;
+    using KX = Packet<PX>;
+    constexpr int R = KV::CW / KX::CW;  // X packets per V packet
+    const size_t step = (size_t)k.nblk * BLAS_BS;
+    for (size_t f0 = (size_t)blockIdx.x * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
+      cplx<TV> p[CG_UNROLL][KV::CW], s[CG_UNROLL][KV::CW], q[CG_UNROLL][KV::CW];
+      cplx<TX> x[CG_UNROLL][KV::CW];
+      size_t fx[CG_UNROLL];
 #pragma unroll
-      for (int c = 0; c < 12; ++c) acc += (double)r[c].re * r[c].re + (double)r[c].im * r[c].im;
+      for (int e = 0; e < CG_UNROLL; ++e) {
+        const size_t f = min(f0 + e * step, k.npk - 1);  // (past the end: loaded, not stored)
+        KV::load(Pv, f, p[e]);
+        KV::load(Q, f, q[e]);
+        KV::load(S, f, s[e]);
+        // packet k of a site is X packets R k .. R k + R - 1 of the same site
+        const size_t chunk = f / (64 * KV::NP), r = f - chunk * (64 * KV::NP);
+        fx[e] = chunk * (64 * KX::NP) + (r >> 6) * (64 * R) + (r & 63);
+#pragma unroll
+        for (int w = 0; w < R; ++w) {
+          cplx<TX> t[KX::CW];
+          KX::load(X, fx[e] + 64 * w, t);
+#pragma unroll
+          for (int c = 0; c < KX::CW; ++c) x[e][w * KX::CW + c] = t[c];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < CG_UNROLL; ++e) {
+        const size_t f = f0 + e * step;
+        if (f >= k.npk) break;
+#pragma unroll
+        for (int w = 0; w < R; ++w) {
+          cplx<TX> t[KX::CW];
+#pragma unroll
+          for (int c = 0; c < KX::CW; ++c) {
+            const int b = w * KX::CW + c;
+            t[c] = {fma(ax, (TX)p[e][b].re, x[e][b].re), fma(ax, (TX)p[e][b].im, x[e][b].im)};
+          }
+          KX::store(X, fx[e] + 64 * w, t);
+        }
+#pragma unroll
+        for (int c = 0; c < KV::CW; ++c) {
+          s[e][c].re = fma(-a, q[e][c].re, s[e][c].re);
+          s[e][c].im = fma(-a, q[e][c].im, s[e][c].im);
+        }
+        KV::store(S, f, s[e]);
+#pragma unroll
+        for (int c = 0; c < KV::CW; ++c)
+          acc += (double)s[e][c].re * s[e][c].re + (double)s[e][c].im * s[e][c].im;
+      }
     }
   }
   double v[1] = {acc};
   block_sum_store<1>(v, k.partials + (size_t)sys * k.nblk, k.nblk, blockIdx.x);
 }
 
-// Second stage of the CG update: ss = sum of the block partials (block
-// order), iteration count and convergence flags.  Systems that were done, or
-// broke down in the update, are left alone.
-__global__ __launch_bounds__(FIN_BS) void k_cg_update_finish(const double *partials, unsigned nblk, CgScalars *scs) {
-  CgScalars *sc = scs + blockIdx.x;
-  if (sc->done) return;
-  double v[1] = {0.0};
-  for (unsigned b = threadIdx.x; b < nblk; b += FIN_BS) v[0] += partials[(size_t)blockIdx.x * nblk + b];
-  block_sum_n<1>(v);
-  if (threadIdx.x == 0) {
-    sc->ss = v[0];
-    sc->iters += 1;
-    if (v[0] <= sc->stop2) sc->done = 1;
-    else if (sc->iters >= sc->max_iters) sc->done = 3;
-  }
-}
-
-// beta = rr[1-j] / rr[j];  P = R + beta P.   x = R, out = P.
+// beta = rr[1-j] / rr[j];  P = R + beta P.   x = R, out = P.  One more block
+// per system (blockIdx.x = 0) ends the iteration: rr[1-j], ss = sum of the
+// update's partials, iteration count and convergence flag.  A system that
+// converged in this iteration still gets its P here, which nothing reads.
 template <int PV>
 __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   using TV = RealOf<PV>;
   const int sys = blockIdx.y;
-  const CgScalars *sc = k.sc + sys;
+  CgScalars *sc = k.sc + sys;
   if (sc->done) return;
-  const double beta = sc->rr[1 - k.j] / sc->rr[k.j];
-  const TV b = (TV)beta;
-  const long n = (long)k.v.vh * k.v.nhalf;
-  for (long f = (long)blockIdx.x * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
-    int h, i;
-    site_of(k.v, f, h, i);
-    cplx<TV> r[12], p[12];
-    char *Pp = k.out + sys * k.so + h * k.ho;
-    Spinor<PV>::load(k.x + sys * k.sx + h * k.hx, i, r);
-    Spinor<PV>::load(Pp, i, p);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      p[c].re = fma(b, p[c].re, r[c].re);
-      p[c].im = fma(b, p[c].im, r[c].im);
+  double rrn;
+  if (k.nparts) rrn = sum_partials(k.parts + (size_t)sys * k.nparts, k.nparts);
+  else rrn = sc->rr[1 - k.j];
+  if (blockIdx.x == 0) {
+    const double ss = sum_partials(k.ss_parts + (size_t)sys * k.nss, k.nss);
+    if (threadIdx.x == 0) {
+      if (k.nparts) sc->rr[1 - k.j] = rrn;
+      sc->ss = ss;
+      sc->iters += 1;
+      if (ss <= sc->stop2) sc->done = 1;
+      else if (sc->iters >= sc->max_iters) sc->done = 3;
     }
-    Spinor<PV>::store(Pp, i, p);
+    return;
+  }
+  const TV b = (TV)(rrn / sc->rr[k.j]);
+  const char *R = k.x + sys * k.sx;
+  char *Pp = k.out + sys * k.so;
+  if constexpr (PV == WD_F16) {
+    const long n = (long)k.v.vh * k.v.nhalf;
+    for (long f = (long)(blockIdx.x - 1) * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
+      int h, i;
+      site_of(k.v, f, h, i);
+      cplx<TV> r[12], p[12];
+      Spinor<PV>::load(R + h * k.hx, i, r);
+      Spinor<PV>::load(Pp + h * k.ho, i, p);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        p[c].re = fma(b, p[c].re, r[c].re);
+        p[c].im = fma(b, p[c].im, r[c].im);
+      }
+      Spinor<PV>::store(Pp + h * k.ho, i, p);
+    }
+  } else {
+    using KV = Packet<PV>;
+    const size_t step = (size_t)k.nblk * BLAS_BS;
+    for (size_t f0 = (size_t)(blockIdx.x - 1) * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
+      cplx<TV> r[CG_UNROLL][KV::CW], p[CG_UNROLL][KV::CW];
+#pragma unroll
+      for (int e = 0; e < CG_UNROLL; ++e) {
+        const size_t f = min(f0 + e * step, k.npk - 1);  // (past the end: loaded, not stored)
+        KV::load(R, f, r[e]);
+        KV::load(Pp, f, p[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < CG_UNROLL; ++e) {
+        if (f0 + e * step >= k.npk) break;
+#pragma unroll
+        for (int c = 0; c < KV::CW; ++c) {
+          p[e][c].re = fma(b, p[e][c].re, r[e][c].re);
+          p[e][c].im = fma(b, p[e][c].im, r[e][c].im);
+        }
+        KV::store(Pp, f0 + e * step, p[e]);
+      }
+    }
   }
 }
 
@@ -415,47 +520,56 @@ wd_status blas_accum(const Geom &g, wd_prec pe, const VecRef &e, const VecRef &x
   return hip_check(hipGetLastError(), "accum launch");
 }
 
-template <int PX>
-static void launch_cgu(wd_prec pv, dim3 grid, const KBlas &k, hipStream_t st) {
-  switch (pv) {
-    case WD_F64: hipLaunchKernelGGL((k_cg_update<PX, WD_F64>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_F32: hipLaunchKernelGGL((k_cg_update<PX, WD_F32>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_F16: hipLaunchKernelGGL((k_cg_update<PX, WD_F16>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_BF16: hipLaunchKernelGGL((k_cg_update<PX, WD_BF16>), grid, dim3(BLAS_BS), 0, st, k); break;
-  }
+// Blocks per system of a CG recurrence over npk packets (FP16: sites): up to
+// CG_UNROLL items per thread, and no more blocks than are resident at once
+// with the one that ends the iteration (every block adds up the partials
+// first).
+static unsigned cg_blocks(const Geom &g, wd_prec pv, int nhalf, int nsys, size_t &npk) {
+  const int np = pv == WD_F64 ? 12 : pv == WD_F32 ? 6 : 3;
+  npk = (size_t)g.vpad * np * nhalf;
+  const unsigned b = blocks_for((long)(pv == WD_F16 ? (size_t)g.vh * nhalf : npk));
+  return std::max(1u, std::min(b, BLAS_MAX_BLOCKS / (unsigned)nsys - 1));
 }
 
 wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv, const VecRef &p, const VecRef &s,
-                         const VecRef &q, CgScalars *sc, int j, int nsys, RedBuf red, hipStream_t st) {
+                         const VecRef &q, CgScalars *sc, int j, int nsys, CgParts &cp, hipStream_t st) {
   if (!((px == WD_F64 && pv == WD_F64) || (px == WD_F32 && pv != WD_F64)))
     return set_error(WD_ERR_PREC, "cg_update: unsupported precision pair");
   KBlas k{};
   k.v = vgeom(g, p.nhalf, pv);
-  k.nblk = blocks_for((long)g.vh * p.nhalf);
+  k.nblk = cg_blocks(g, pv, p.nhalf, nsys, k.npk);
   k.x = (const char *)x.p; k.sx = x.sys_stride; k.hx = half_bytes(g, px);
   k.y = (const char *)p.p; k.sy = p.sys_stride; k.hy = half_bytes(g, pv);
   k.out = (char *)s.p; k.so = s.sys_stride; k.ho = half_bytes(g, pv);
   k.out2 = (char *)q.p; k.so2 = q.sys_stride; k.ho2 = half_bytes(g, pv);
   k.sc = sc; k.j = j;
-  k.partials = red.partials;
+  k.parts = cp.norm;
+  k.nparts = cp.nnorm;
+  k.partials = cp.ss;
+  cp.nss = k.nblk;
   dim3 grid(k.nblk, (unsigned)nsys);
-  if (px == WD_F64) launch_cgu<WD_F64>(pv, grid, k, st);
-  else launch_cgu<WD_F32>(pv, grid, k, st);
-  WD_TRY(hip_check(hipGetLastError(), "cg_update launch"));
-  hipLaunchKernelGGL(k_cg_update_finish, dim3((unsigned)nsys), dim3(FIN_BS), 0, st, (const double *)k.partials, k.nblk,
-                     sc);
-  return hip_check(hipGetLastError(), "cg_update finish launch");
+  switch (pv) {
+    case WD_F64: hipLaunchKernelGGL((k_cg_update<WD_F64, WD_F64>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_F32: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F32>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_F16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F16>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_BF16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_BF16>), grid, dim3(BLAS_BS), 0, st, k); break;
+  }
+  return hip_check(hipGetLastError(), "cg_update launch");
 }
 
 wd_status blas_cg_pupdate(const Geom &g, wd_prec pv, const VecRef &r, const VecRef &p, CgScalars *sc, int j,
-                          int nsys, hipStream_t st) {
+                          int nsys, const CgParts &cp, hipStream_t st) {
   KBlas k{};
   k.v = vgeom(g, p.nhalf, pv);
-  k.nblk = blocks_for((long)g.vh * p.nhalf);
+  k.nblk = cg_blocks(g, pv, p.nhalf, nsys, k.npk);
   k.x = (const char *)r.p; k.sx = r.sys_stride; k.hx = half_bytes(g, pv);
   k.out = (char *)p.p; k.so = p.sys_stride; k.ho = half_bytes(g, pv);
   k.sc = sc; k.j = j;
-  dim3 grid(k.nblk, (unsigned)nsys);
+  k.parts = cp.norm;
+  k.nparts = cp.nnorm;
+  k.ss_parts = cp.ss;
+  k.nss = cp.nss;
+  dim3 grid(k.nblk + 1, (unsigned)nsys);
   WD_DISPATCH_P(pv, k_cg_pupdate, grid, k, st);
   return hip_check(hipGetLastError(), "cg_pupdate launch");
 }

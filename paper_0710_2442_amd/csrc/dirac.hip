@@ -855,7 +855,7 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
     }
 #undef WD_DP
     WD_TRY(hip_check(hipGetLastError(), "dirac launch"));
-    if (norm)
+    if (norm && !leave_partials(a.red, 2u * (unsigned)k.nt))
       return launch_finish_sums(k.partials, 2u * (unsigned)k.nt, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
     return WD_OK;
   }
@@ -894,7 +894,8 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
   }
 #undef WD_DP
   WD_TRY(hip_check(hipGetLastError(), "dirac launch"));
-  if (norm) return launch_finish_sums(k.partials, nblk, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
+  if (norm && !leave_partials(a.red, nblk))
+    return launch_finish_sums(k.partials, nblk, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
   return WD_OK;
 }
 

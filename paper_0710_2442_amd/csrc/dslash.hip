@@ -283,7 +283,8 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
     default: return set_error(WD_ERR_PREC, "dslash: unknown precision %d", (int)prec);
   }
   WD_TRY(hip_check(hipGetLastError(), "dslash launch"));
-  if (norm) return launch_finish_sums(k.partials, nblk, 1, k.norm_out, 1, 0, k.skip, 1, st);
+  if (norm && !leave_partials(a.red, nblk))
+    return launch_finish_sums(k.partials, nblk, 1, k.norm_out, 1, 0, k.skip, 1, st);
   return WD_OK;
 }
 

@@ -356,8 +356,9 @@ wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs 
     default: return set_error(WD_ERR_PREC, "dslash_mrhs: unknown precision %d", (int)prec);
   }
   WD_TRY(hip_check(hipGetLastError(), "dslash_mrhs launch"));
-  if (norm)
-    return launch_finish_sums(m.k.partials, m.ntiles > 0 ? (unsigned)m.ntiles : grid.x, a.nrhs, m.k.norm_out,
+  const unsigned nparts = m.ntiles > 0 ? (unsigned)m.ntiles : grid.x;
+  if (norm && !leave_partials(a.red, nparts))
+    return launch_finish_sums(m.k.partials, nparts, a.nrhs, m.k.norm_out,
                               m.norm_stride, m.k.norm_accumulate, m.k.skip, m.skip_stride, st);
   return WD_OK;
 }

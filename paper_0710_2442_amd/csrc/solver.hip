@@ -30,9 +30,10 @@
 namespace wd {
 
 // ------------------------------------------------------------ workspace
-// largest grid.x of any reducing launch: single-RHS hop, level-1, multi-RHS hop
+// two lists of partials: the largest grid.x of any reducing launch
+// (single-RHS hop, one-launch D_W, level-1, multi-RHS hop)
 static size_t ws_partials(const wd_gauge *g, int nsys) {
-  const size_t nblk = std::max<size_t>(std::max<unsigned>(dslash_grid_blocks(g), BLAS_MAX_BLOCKS),
+  const size_t nblk = std::max<size_t>(std::max<unsigned>(2 * dslash_grid_blocks(g), BLAS_MAX_BLOCKS),
                                        mrhs_grid_blocks(g));
   return nblk * 2 * (size_t)nsys;
 }
@@ -85,7 +86,7 @@ void workspace_free(wd_gauge *g) {
   g->ws = nullptr;
 }
 
-static RedBuf red_of(const Workspace *w) { return RedBuf{w->partials}; }
+static RedBuf red_of(const Workspace *w) { return RedBuf{w->partials, nullptr}; }
 
 // ------------------------------------------------------------ operators
 // One hop application for nsys systems: single-RHS kernel when nsys == 1.
@@ -150,17 +151,23 @@ static wd_status apply_op(const wd_gauge *g, const CglsVecs &v, double kappa, co
   return launch_dirac(g, v.pv, a, st);
 }
 
-// q = A p -> qq;  cg_update;  r = A^dag s -> rr[1-j];  p = r + beta p
+// q = A p -> qq;  cg_update;  r = A^dag s -> rr[1-j];  p = r + beta p and the
+// iteration's end: six launches.  The blocks of the two recurrences add up the
+// norm partials of the application before them where these are at most
+// CONSUMER_PARTS per system; beyond, a finishing launch adds them first.
 static wd_status cgls_iteration(const wd_gauge *g, const CglsVecs &v, double kappa, CgScalars *sc, int j,
                                 RedBuf red, hipStream_t st) {
   const int *skip = &sc->done;
   const int nh = v.full ? 2 : 1;
+  CgParts cp;
+  cp.norm = red.partials;
+  cp.ss = red.partials + ws_partials(g, v.nsys) / 2;
+  red.nparts = &cp.nnorm;
   WD_TRY(apply_op(g, v, kappa, v.p, v.q, 0, &sc->qq, skip, red, st));
   WD_TRY(blas_cg_update(g->geom, v.px, vref(v.x, nh, v.sx), v.pv, vref(v.p, nh, v.sv), vref(v.s, nh, v.sv),
-                        vref(v.q, nh, v.sv), sc, j, v.nsys, red, st));
+                        vref(v.q, nh, v.sv), sc, j, v.nsys, cp, st));
   WD_TRY(apply_op(g, v, kappa, v.s, v.r, 1, &sc->rr[1 - j], skip, red, st));
-  WD_TRY(blas_cg_pupdate(g->geom, v.pv, vref(v.r, nh, v.sv), vref(v.p, nh, v.sv), sc, j, v.nsys, st));
-  return WD_OK;
+  return blas_cg_pupdate(g->geom, v.pv, vref(v.r, nh, v.sv), vref(v.p, nh, v.sv), sc, j, v.nsys, cp, st);
 }
 
 // Runs CGLS on M x = s (s holds the right-hand side on entry; x is zeroed).

@@ -43,9 +43,19 @@ wd_status blas_convert(const Geom &g, wd_prec pi, const VecRef &x, wd_prec po, c
 // x64 += scale * sqrt(sc[sys].rnorm2) * e(pe)
 wd_status blas_accum(const Geom &g, wd_prec pe, const VecRef &e, const VecRef &x64, double scale, CgScalars *sc,
                      int nsys, hipStream_t st);
+// The partial sums that the two CG recurrences of an iteration work on: the
+// norm partials of the operator application before them (nnorm per system; 0
+// when a finishing launch has put the sum into the scalars) and the |s|^2
+// partials that the update leaves (nss per system) for the p update.
+struct CgParts {
+  const double *norm = nullptr;
+  unsigned nnorm = 0;
+  double *ss = nullptr;
+  unsigned nss = 0;
+};
 wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv, const VecRef &p, const VecRef &s,
-                         const VecRef &q, CgScalars *sc, int j, int nsys, RedBuf red, hipStream_t st);
+                         const VecRef &q, CgScalars *sc, int j, int nsys, CgParts &cp, hipStream_t st);
 wd_status blas_cg_pupdate(const Geom &g, wd_prec pv, const VecRef &r, const VecRef &p, CgScalars *sc, int j,
-                          int nsys, hipStream_t st);
+                          int nsys, const CgParts &cp, hipStream_t st);
 
 }  // namespace wd

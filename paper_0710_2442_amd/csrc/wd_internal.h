@@ -143,8 +143,20 @@ wd_status hip_check(hipError_t e, const char *what);
 // NULL and *skip != 0 the launch does nothing.
 // reduction workspace needed by a grid of `nblocks` blocks summing N values
 struct RedBuf {
-  double *partials;   // N * nblocks block partials, summed by a finishing kernel
+  double *partials = nullptr;  // N * nblocks block partials, summed by a finishing kernel
+  // if set: receives the partials per system; when these are at most
+  // CONSUMER_PARTS no finishing kernel is launched, the consumer adds them up
+  unsigned *nparts = nullptr;
 };
+// A consumer that adds up n partials in every block instead of waiting for a
+// finishing launch: see cgls_iteration for where the line lies.
+constexpr unsigned CONSUMER_PARTS = 2048;
+// true: leave the n partials to the consumer (the count is set); false: finish them
+inline bool leave_partials(const RedBuf &red, unsigned n) {
+  if (!red.nparts) return false;
+  *red.nparts = n <= CONSUMER_PARTS ? n : 0;
+  return n <= CONSUMER_PARTS;
+}
 
 struct DslashArgs {
   const void *in = nullptr;
@@ -155,7 +167,7 @@ struct DslashArgs {
   int dagger = 0;
   double *norm_out = nullptr;  // device
   const int *skip = nullptr;   // device flag
-  RedBuf red{nullptr};
+  RedBuf red{};
 };
 // Full-lattice D_W in one launch (dirac.hip): full fields in, out, X, Y;
 // out = a H in (+ X (- Y)), optional FP64 |out|^2 over both parities.
@@ -174,7 +186,7 @@ struct DiracArgs {
   double *norm_out = nullptr;
   int norm_accumulate = 0;
   const int *skip = nullptr;  // device flag: when set, the launch does nothing
-  RedBuf red{nullptr};
+  RedBuf red{};
 };
 wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &args, hipStream_t st);
 // one-launch D_W: occupancy of its kernels, queried once per handle (dirac.hip)
@@ -225,7 +237,7 @@ struct MrhsArgs {
   int norm_accumulate = 0;
   const int *skip = nullptr;
   int skip_stride = 1;
-  RedBuf red{nullptr};
+  RedBuf red{};
 };
 wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs &a, hipStream_t st);
 
