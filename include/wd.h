@@ -409,15 +409,19 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path,
  * tuned: block size (64, 128, 256 sites), rpl (1..16) and block -> tile
  * order (groups as above).  FP64: fixed 16-site x RHS tiles; tuned: tile
  * order.  Candidates are checked byte for byte against the linear variant,
- * then timed; the fastest is kept in the handle.  cache_path and force as
- * for wd_tune_dslash (the key adds nrhs; the cache line's third field is
+ * then timed; the fastest is kept in the handle.  In every precision also
+ * block 512: one wave per hop direction, 64 sites per block, rpl right-hand
+ * sides one after the other, orders as above or WD_ORDER_RANGES.  cache_path
+ * and force as for wd_tune_dslash (the key adds nrhs; the cache line's third field is
  * "rpl").  Outputs may be NULL.  Synchronous. */
 wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs,
                               const char *cache_path, int force, int *block,
                               int *groups, int *rpl, double *us);
 
-/* Set / read the multi-RHS hop variant used for precision prec: block (FP64:
- * 16; others 64, 128 or 256 sites), groups (block -> tile order, as for
+/* Set / read the multi-RHS hop variant used for precision prec: block (512,
+ * the default, with rpl 1..16, see above: until a variant is set or tuned, rpl
+ * counts as the most and small lattices take fewer; FP64: 16; others 64, 128
+ * or 256 sites), groups (block -> tile order, as for
  * wd_set_dslash_variant) and rpl (FP64: 4; others 1..16 right-hand sides per
  * lane).  WD_ERR_ARG for a value
  * outside these or a variant that does not fit the lattice.  The variants

@@ -133,9 +133,7 @@ wd_status wd_gauge_create(const double *U_host, const int dims[4], int t_bc, wd_
   g->stream = (hipStream_t)hip_stream;
   for (int p = 0; p < 4; ++p) {
     dslash_default_variant(g, p);
-    g->mrhs_block[p] = (p == WD_F64) ? 16 : 128;
-    g->mrhs_rpl[p] = 4;
-    g->mrhs_groups[p] = dslash_variant_ok(g->geom, g->mrhs_block[p], 4) ? 4 : 0;
+    mrhs_default_variant(g, p);
   }
   wd_status rc = WD_OK;
   void *canon = nullptr;

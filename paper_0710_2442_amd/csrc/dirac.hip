@@ -614,9 +614,9 @@ __device__ __forceinline__ void dirac_split_wave(const KDirac &k, int i, int p, 
 #pragma unroll
   for (int j = 0; j < CW; ++j) o[j] = y[j] = {(T)0, (T)0};
   if (i < k.g.vh) {
-    split_load<P, W>(k.X + off, i, o);
+    split_load<P>(k.X + off, i, W, o);
     if constexpr (EPI == 2) {
-      split_load<P, W>(k.Y + off, i, y);
+      split_load<P>(k.Y + off, i, W, y);
       if constexpr (!LATE) {
 #pragma unroll
         for (int j = 0; j < CW; ++j) o[j] = o[j] - y[j];

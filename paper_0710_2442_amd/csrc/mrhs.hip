@@ -205,6 +205,339 @@ __global__ __launch_bounds__(256) void k_dslash_mrhs_reg(KMrhs m) {
 }
 
 
+// ---------------------------------------------- one wave per hop direction
+// The packets of one neighbour spinor (or of the half that a time hop keeps),
+// loaded one right-hand side ahead and unpacked when used: in 16-bit storage
+// they take half the registers of the numbers.
+template <int P>
+struct NbRaw;
+template <>
+struct NbRaw<WD_F64> {
+  cplx<double> s[12];
+  // time: the half of the spinor (lower: spins 2, 3) that the hop keeps
+  __device__ __forceinline__ void load(const char *in, int nb, bool time, bool lower) {
+    const v2d *p = (const v2d *)in + chunk_base<Spinor<WD_F64>::CHUNK>((size_t)nb) + (lower ? 6 * 64 : 0);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const v2d v = p[64 * c];
+      s[c] = {v.x, v.y};
+    }
+    if (time) return;
+#pragma unroll
+    for (int c = 6; c < 12; ++c) {
+      const v2d v = p[64 * c];
+      s[c] = {v.x, v.y};
+    }
+  }
+  // the spinor, or the half (components 0 .. 5 of what was loaded) of a time hop
+  __device__ __forceinline__ void whole(cplx<double> (&psi)[12]) const {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) psi[c] = s[c];
+  }
+  template <bool LOWER>
+  __device__ __forceinline__ void half(cplx<double> (&h)[6]) const {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) h[c] = s[c];
+  }
+};
+template <>
+struct NbRaw<WD_F32> {
+  v4f a, b, c, d, e, f;
+  __device__ __forceinline__ void load(const char *in, int nb, bool time, bool lower) {
+    const v4f *p = (const v4f *)in + chunk_base<Spinor<WD_F32>::CHUNK>((size_t)nb) + (lower ? 192 : 0);
+    a = p[0]; b = p[64]; c = p[128];
+    if (!time) { d = p[192]; e = p[256]; f = p[320]; }
+  }
+  template <bool LOWER>
+  __device__ __forceinline__ void half(cplx<float> (&h)[6]) const {
+    h[0] = {a.x, a.y}; h[1] = {a.z, a.w}; h[2] = {b.x, b.y}; h[3] = {b.z, b.w}; h[4] = {c.x, c.y}; h[5] = {c.z, c.w};
+  }
+  __device__ __forceinline__ void whole(cplx<float> (&s)[12]) const {
+    s[0] = {a.x, a.y}; s[1] = {a.z, a.w}; s[2] = {b.x, b.y}; s[3] = {b.z, b.w};
+    s[4] = {c.x, c.y}; s[5] = {c.z, c.w}; s[6] = {d.x, d.y}; s[7] = {d.z, d.w};
+    s[8] = {e.x, e.y}; s[9] = {e.z, e.w}; s[10] = {f.x, f.y}; s[11] = {f.z, f.w};
+  }
+};
+template <int P>
+struct NbRaw16 {
+  v4u a, b, c;
+  float n;  // FP16: the site's scale
+  // components 6h .. 6h+5 live in packets (0, 1) or (1, 2)
+  __device__ __forceinline__ void load(const char *in, int nb, bool time, bool lower) {
+    const v4u *p = (const v4u *)in + chunk_base<Spinor<P>::CHUNK>((size_t)nb) + (lower ? 64 : 0);
+    a = p[0]; b = p[64];
+    if (!time) c = p[128];
+    if constexpr (P == WD_F16) n = Spinor<P>::scale(in, (size_t)nb);
+  }
+  __device__ __forceinline__ cplx<float> num(uint32_t w) const {
+    if constexpr (P == WD_F16) return {n * f16_to_f32((uint16_t)(w & 0xffffu)), n * f16_to_f32((uint16_t)(w >> 16))};
+    else return {bf16_to_f32((uint16_t)(w & 0xffffu)), bf16_to_f32((uint16_t)(w >> 16))};
+  }
+  __device__ __forceinline__ void whole(cplx<float> (&s)[12]) const {
+    s[0] = num(a.x); s[1] = num(a.y); s[2] = num(a.z); s[3] = num(a.w);
+    s[4] = num(b.x); s[5] = num(b.y); s[6] = num(b.z); s[7] = num(b.w);
+    s[8] = num(c.x); s[9] = num(c.y); s[10] = num(c.z); s[11] = num(c.w);
+  }
+  template <bool LOWER>
+  __device__ __forceinline__ void half(cplx<float> (&h)[6]) const {
+    if constexpr (LOWER) {
+      h[0] = num(a.z); h[1] = num(a.w); h[2] = num(b.x); h[3] = num(b.y); h[4] = num(b.z); h[5] = num(b.w);
+    } else {
+      h[0] = num(a.x); h[1] = num(a.y); h[2] = num(a.z); h[3] = num(a.w); h[4] = num(b.x); h[5] = num(b.y);
+    }
+  }
+  // the spinor, or in its first 6 components the half that was loaded
+  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool, bool lower) const {
+    s[0] = num(lower ? a.z : a.x); s[1] = num(lower ? a.w : a.y);
+    s[2] = num(lower ? b.x : a.z); s[3] = num(lower ? b.y : a.w);
+    s[4] = num(lower ? b.z : b.x); s[5] = num(lower ? b.w : b.y);
+    s[6] = num(b.z); s[7] = num(b.w);
+    s[8] = num(c.x); s[9] = num(c.y); s[10] = num(c.z); s[11] = num(c.w);
+  }
+};
+template <>
+struct NbRaw<WD_F16> : NbRaw16<WD_F16> {};
+template <>
+struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {};
+
+// h = the half spinor that hop D projects from the loaded neighbour.
+template <int P, bool DAG, int D>
+__device__ __forceinline__ void mrhs_split_project(const NbRaw<P> &raw, RealOf<P> f, cplx<RealOf<P>> (&h)[6]) {
+  constexpr int S = ((D < 4) != DAG) ? 1 : -1;
+  if constexpr ((D & 3) == 3) {
+    raw.template half<(S < 0)>(h);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) h[c] = f * h[c];
+  } else {
+    cplx<RealOf<P>> psi[12];
+    raw.whole(psi);
+    project<D & 3, S>(psi, h);
+  }
+}
+
+// The wave's hop of one right-hand side into LDS (q: the lane's first
+// element): the products of split_hop.
+template <int P>
+__device__ __forceinline__ void mrhs_split_mul(const cplx<RealOf<P>> (&u)[6], const cplx<RealOf<P>> (&r2)[3],
+                                               const cplx<RealOf<P>> (&h)[6], cplx<RealOf<P>> *q) {
+  using T = RealOf<P>;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const cplx<T> v[3] = {h[3 * s], h[3 * s + 1], h[3 * s + 2]};
+    cplx<T> y[3];
+    su3_mul(u, r2, v, y);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) q[(3 * s + a) * SPLIT_SITES] = y[a];
+  }
+}
+
+// FP16: project and multiply per direction (24^3x48, 12 right-hand sides: 222
+// us against 260 when the directions are joined in between, which copies every
+// operand); the others join them and load the next neighbour once this one's
+// registers are free (BF16 161 against 166, FP32 and FP64 would spill).
+template <bool DAG, int D>
+__device__ __forceinline__ void mrhs_split_hop16(const cplx<float> (&psi)[12], float f, const cplx<float> (&u)[6],
+                                                 const cplx<float> (&r2)[3], cplx<float> *q) {
+  constexpr int S = ((D < 4) != DAG) ? 1 : -1;
+  cplx<float> h[6];
+  if constexpr ((D & 3) == 3) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) h[c] = f * psi[c];
+  } else {
+    project<D & 3, S>(psi, h);
+  }
+  mrhs_split_mul<WD_F16>(u, r2, h, q);
+}
+
+// The sums and the epilogue of wave slot W for one right-hand side (out at
+// byte offset off, epilogue operands x, y); returns the lane's |components|^2
+// when NORM.
+template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
+__device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off, int i, int lane,
+                                                    const SplitLds<P> &lds,
+                                                    cplx<RealOf<P>> (&x)[SplitOut<P>::CW],
+                                                    cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
+                                                    std::integer_sequence<int, J...>) {
+  using T = RealOf<P>;
+  constexpr int CW = SplitOut<P>::CW;
+  cplx<T> o[CW];
+  if (i < k.g.vh) {
+    const T a = (T)k.a;
+    // one component's LDS reads at a time: the links and the next neighbour
+    // stay in registers meanwhile
+    ((o[J] = split_sum<P, DAG, W * CW + J>(lds, lane), __builtin_amdgcn_sched_barrier(0)), ...);
+    if constexpr (P == WD_F64) {
+      if constexpr (EPI >= 1) split_load<P>(k.X + off, i, W, x);
+      if constexpr (EPI == 2) split_load<P>(k.Y + off, i, W, y);
+    }
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+      o[j] = a * o[j];
+      if constexpr (EPI >= 1) o[j] = o[j] + x[j];
+      if constexpr (EPI == 2) o[j] = o[j] - y[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
+  }
+  split_store<P, W, true, NORM>(k.out + off, i, o);
+  double n = 0.0;
+  if constexpr (NORM) {
+    if (i < k.g.vh) {
+#pragma unroll
+      for (int j = 0; j < CW; ++j) n += (double)o[j].re * o[j].re + (double)o[j].im * o[j].im;
+    }
+  }
+  return n;
+}
+
+// Multi-RHS hop with one wave per direction (see wd_hop.h): a block of eight
+// waves keeps the links of 64 sites, one direction per wave, in registers and
+// walks the rpl right-hand sides of its chunk.  Per right-hand side each wave
+// transports one neighbour into LDS (the next neighbour is already on its
+// way), and after a barrier NW of the waves, another set for each right-hand
+// side, add up and store.  Two LDS buffers, so one barrier a right-hand side
+// (FP64: one buffer and two barriers, two blocks a CU instead of one).  80
+// registers a lane and 24 waves a CU (FP64, FP16 128 and 16); all eight links
+// in one lane took 232 registers, 8 waves a CU.  Bound by VALU issue in BF16
+// (about 1400 instructions per 64 sites and right-hand side, 158 us of the 161
+// at 24^3x48 with 12) and by fetches in FP64 (1.8 times the algorithmic bytes
+// at 6 TB/s).
+template <int P, bool DAG, int EPI, bool NORM>
+__global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) void k_dslash_mrhs_split(KMrhs m) {
+  using T = RealOf<P>;
+  constexpr int NB = P == WD_F64 ? 1 : 2, NW = SplitOut<P>::NW, CW = SplitOut<P>::CW;
+  __shared__ SplitLds<P> lds[NB];
+  __shared__ double sred[NORM ? MR_CHUNK : 1][NW];
+  const KDslash &k = m.k;
+  int tile, chunk;
+  if (m.nx3 > 0) {
+    mrhs_box(m, (int)blockIdx.x, tile, chunk);
+  } else if (k.groups == SPLIT_RANGES) {
+    // a contiguous range of tiles per XCD, a tile's chunks side by side
+    const int q = (int)blockIdx.x >> 3;
+    chunk = q % m.nchunks;
+    tile = ((int)blockIdx.x & 7) * k.tiles_per_slice + q / m.nchunks;
+    if (tile >= m.ntiles) return;
+  } else {
+    tile = tile_of(k);
+    chunk = (int)blockIdx.y;
+  }
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int i = tile * SPLIT_SITES + lane;
+  const bool site = i < k.g.vh;
+  const int r0 = chunk * m.rpl, r1 = min(m.nrhs, r0 + m.rpl);
+  auto live = [&](int r) { return r < r1 && !(k.skip && k.skip[(size_t)r * m.skip_stride]); };
+  int nb = 0;
+  bool edge = false;
+  cplx<T> u[6], r2[3];
+  if (site) {
+    switch (w) {
+      case 0: nb = neighbour_of<0, true>(k.g, i, k.parity, edge); break;
+      case 1: nb = neighbour_of<1, true>(k.g, i, k.parity, edge); break;
+      case 2: nb = neighbour_of<2, true>(k.g, i, k.parity, edge); break;
+      case 3: nb = neighbour_of<3, true>(k.g, i, k.parity, edge); break;
+      case 4: nb = neighbour_of<0, false>(k.g, i, k.parity, edge); break;
+      case 5: nb = neighbour_of<1, false>(k.g, i, k.parity, edge); break;
+      case 6: nb = neighbour_of<2, false>(k.g, i, k.parity, edge); break;
+      default: nb = neighbour_of<3, false>(k.g, i, k.parity, edge); break;
+    }
+  }
+  Link<T>::load(k.links, w, i, u);  // (padding slots hold zero links)
+  rebuild_row2(u, r2);
+  const T f = (T)2 * (edge ? (T)k.g.tbc : (T)1);
+  NbRaw<P> nx;  // (padding lanes read site 0)
+  const bool time = (w & 3) == 3, lower = time && (w == 3) == DAG;
+  nx.load(k.in + (size_t)r0 * m.rhs_stride, nb, time, lower);
+#pragma unroll 1
+  for (int r = r0; r < r1; ++r) {
+    // opaque copies: the addresses of the six sums are formed where they are
+    // used, not kept in registers across the loop
+    int li = lane, ii = i;
+    asm volatile("" : "+v"(li), "+v"(ii));
+    const int slot = w * 6 * SPLIT_SITES + li;
+    const bool on = live(r);
+    SplitLds<P> &L = lds[NB == 2 ? (r - r0) & 1 : 0];
+    // the next right-hand side's neighbour is loaded, by one load for all
+    // directions, before this one's products
+    const char *next = k.in + (size_t)(r + 1) * m.rhs_stride;
+    cplx<T> *q = L.g + slot;
+    if constexpr (P == WD_F16) {
+      cplx<T> psi[12];
+      nx.unpack(psi, time, lower);
+      if (r + 1 < r1) nx.load(next, nb, time, lower);
+      if (on) {
+#define WD_HOP(D) mrhs_split_hop16<DAG, D>(psi, f, u, r2, q)
+        switch (w) {
+          case 0: WD_HOP(0); break;
+          case 1: WD_HOP(1); break;
+          case 2: WD_HOP(2); break;
+          case 3: WD_HOP(3); break;
+          case 4: WD_HOP(4); break;
+          case 5: WD_HOP(5); break;
+          case 6: WD_HOP(6); break;
+          default: WD_HOP(7); break;
+        }
+#undef WD_HOP
+      }
+    } else {
+      cplx<T> h[6];
+#define WD_HOP(D) mrhs_split_project<P, DAG, D>(nx, f, h)
+      switch (w) {
+        case 0: WD_HOP(0); break;
+        case 1: WD_HOP(1); break;
+        case 2: WD_HOP(2); break;
+        case 3: WD_HOP(3); break;
+        case 4: WD_HOP(4); break;
+        case 5: WD_HOP(5); break;
+        case 6: WD_HOP(6); break;
+        default: WD_HOP(7); break;
+      }
+#undef WD_HOP
+      if (r + 1 < r1) nx.load(next, nb, time, lower);
+      if (on) mrhs_split_mul<P>(u, r2, h, q);
+    }
+    const int ws = NB == 2 ? (w + NW * (r - r0)) & 7 : w;  // the waves take turns
+    const size_t off = (size_t)r * m.rhs_stride;
+    cplx<T> x[CW], y[CW];  // loaded before the barrier (FP64, short of registers: after the sums)
+    if (P != WD_F64 && on && ws < NW && ii < k.g.vh) {
+      if constexpr (EPI >= 1) split_load<P>(k.X + off, ii, ws, x);
+      if constexpr (EPI == 2) split_load<P>(k.Y + off, ii, ws, y);
+    }
+    __syncthreads();
+    double n = 0.0;
+    if (on) {
+      constexpr auto J = std::make_integer_sequence<int, CW>{};
+      if (ws == 0) n = mrhs_split_finish<P, DAG, EPI, NORM, 0>(k, off, ii, li, L, x, y, J);
+      if constexpr (NW > 1) {
+        if (ws == 1) n = mrhs_split_finish<P, DAG, EPI, NORM, 1>(k, off, ii, li, L, x, y, J);
+        if (ws == 2) n = mrhs_split_finish<P, DAG, EPI, NORM, 2>(k, off, ii, li, L, x, y, J);
+      }
+      if constexpr (NW > 3) {
+        if (ws == 3) n = mrhs_split_finish<P, DAG, EPI, NORM, 3>(k, off, ii, li, L, x, y, J);
+        if (ws == 4) n = mrhs_split_finish<P, DAG, EPI, NORM, 4>(k, off, ii, li, L, x, y, J);
+        if (ws == 5) n = mrhs_split_finish<P, DAG, EPI, NORM, 5>(k, off, ii, li, L, x, y, J);
+      }
+    }
+    if constexpr (NORM) {
+      if (ws < NW) {
+        n = wave_sum(n);
+        if (lane == 0) sred[r - r0][ws] = n;
+      }
+    }
+    if constexpr (NB == 1) __syncthreads();  // before the next right-hand side overwrites the buffer
+  }
+  if constexpr (NORM) {
+    __syncthreads();
+    for (int r = r0 + (int)threadIdx.x; r < r1; r += SPLIT_BS) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) s += sred[r - r0][q];
+      k.partials[(size_t)r * m.ntiles + tile] = s;
+    }
+  }
+}
+
 // ------------------------------------------------------------ launchers
 static KDslash make_k_mrhs(const wd_gauge *g, wd_prec prec, int parity) {
   KDslash k{};
@@ -250,6 +583,10 @@ __global__ __launch_bounds__(256) void k_dslash_mrhs_l2(KMrhs m) {
 
 template <int P, bool DAG, int EPI, bool NORM>
 static void launch_mrhs_t(const KMrhs &m, dim3 grid, dim3 block, hipStream_t st) {
+  if (m.k.split) {
+    hipLaunchKernelGGL((k_dslash_mrhs_split<P, DAG, EPI, NORM>), grid, block, 0, st, m);
+    return;
+  }
   if constexpr (P == WD_F64) {
     if (m.nx3 > 0) hipLaunchKernelGGL((k_dslash_mrhs_l2<P, DAG, EPI, NORM>), grid, block, 0, st, m);
     else hipLaunchKernelGGL((k_dslash_mrhs<P, DAG, EPI, NORM>), grid, block, 0, st, m);
@@ -280,12 +617,22 @@ bool mrhs_box_ok(const Geom &G, int bs, int groups) {
   return (slice / bs) % nx3 == 0 && G.L[3] % (8 / nx3) == 0;
 }
 
+// Orders of the one-wave-per-direction form (block SPLIT_BS, 64-site tiles).
+bool mrhs_split_order_ok(const Geom &G, int groups) {
+  if (groups == SPLIT_RANGES) return true;
+  return groups <= -100 ? mrhs_box_ok(G, SPLIT_SITES, groups) : dslash_variant_ok(G, SPLIT_SITES, groups, 1);
+}
+
 // Block size of the multi-RHS hop: FP64 keeps 16 sites x RHS lanes, the
 // others one lane per site (tunable, 64..256).
 static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
   const int pi = (int)prec;
   int bs = g->mrhs_block[pi];
   groups = g->mrhs_groups[pi];
+  if (bs == SPLIT_BS) {
+    if (!mrhs_split_order_ok(g->geom, groups)) groups = SPLIT_RANGES;
+    return bs;
+  }
   const bool box = mrhs_box_ok(g->geom, bs, groups);
   if (prec == WD_F64) {
     // FP64: 16-site x RHS tiles, or one RHS per block in box order
@@ -297,6 +644,47 @@ static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
   if (bs != 64 && bs != 128 && bs != 256) bs = 128;
   if (!box && !dslash_variant_ok(g->geom, bs, groups, 1)) groups = 0;
   return bs;
+}
+
+// The variant of a new handle: one wave per direction, up to 12 right-hand
+// sides per block (fewer on small lattices, see mrhs_split_rpl).  us per
+// launch against the defaults of the other forms (128 sites, 4 right-hand
+// sides per lane; FP64 16-site tiles), 12 right-hand sides: BF16 8^4 6.7 / 16,
+// 20^3x40 85 / 108, 24^3x48 161 / 208; FP32 20^3x40 120 / 153, 24^3x48 246 /
+// 309; FP64 16^4 52 / 69, 24^3x48 540 / 714, 32^3x64 1610 / 2290.  FP16 keeps
+// the other form where its tiles fill the device (one wave adds up all 12
+// components of a site to find its scale): 24^3x48 222 / 235, but 32^3x32
+// with 3 118 / 102, 16^4 with 24 55 / 49.
+// Order as for the single-RHS hop: contiguous ranges per XCD (BF16 24^3x48 161
+// against 166 with regions); from 2^18 sites in FP64 and FP32 regions of each
+// slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 540 / 573, 32^3x64
+// 1610 / 1777).
+void mrhs_default_variant(wd_gauge *g, int p) {
+  const Geom &G = g->geom;
+  g->mrhs_auto[p] = 1;
+  g->mrhs_rpl[p] = 12;
+  g->mrhs_block[p] = SPLIT_BS;
+  g->mrhs_groups[p] = SPLIT_RANGES;
+  if (p == WD_F16 && G.vpad / SPLIT_SITES >= 512) {
+    g->mrhs_auto[p] = 0;
+    g->mrhs_rpl[p] = 4;
+    g->mrhs_block[p] = 128;
+    g->mrhs_groups[p] = dslash_variant_ok(G, 128, 4) ? 4 : 0;
+  } else if (G.vh >= (1 << 18)) {
+    if (dslash_variant_ok(G, SPLIT_SITES, 8)) g->mrhs_groups[p] = 8;
+    else if (p <= WD_F32 && dslash_variant_ok(G, SPLIT_SITES, 4)) g->mrhs_groups[p] = 4;
+  }
+}
+
+// Right-hand sides per block of a default variant: chunks are added until the
+// blocks are two a CU, for fewer would leave the chain of right-hand sides as
+// the run time: 8^4 (32 tiles), 12 right-hand sides BF16: 3 per block 6.7 us,
+// 12 per block 15.2; 16^4 (512 tiles) FP64: 12 per block 52, 4 per block 62.
+static int mrhs_split_rpl(const wd_gauge *g, int prec, int nrhs, int ntiles) {
+  const int most = g->mrhs_rpl[prec];
+  if (!g->mrhs_auto[prec]) return most;
+  const int chunks = std::max((nrhs + most - 1) / most, std::min(nrhs, (512 + ntiles - 1) / ntiles));
+  return (nrhs + chunks - 1) / chunks;
 }
 
 wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs &a, hipStream_t st) {
@@ -321,11 +709,28 @@ wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs 
   if (norm && !m.k.partials) return set_error(WD_ERR_ARG, "dslash_mrhs norm: no reduction buffer");
   const int epi = a.Y ? 2 : (a.X ? 1 : 0);
   int groups;
-  const int bs = mrhs_block_of(g, prec, groups);
+  int bs = mrhs_block_of(g, prec, groups);
+  m.k.split = bs == SPLIT_BS;
+  if (m.k.split) bs = SPLIT_SITES;
   m.k.groups = groups;
   m.k.tiles_per_slice = groups ? (int)((long)g->geom.vh / g->geom.L[3] / bs) : 0;
   dim3 grid, block;
-  if (prec == WD_F64 && groups <= -100) {
+  if (m.k.split) {
+    m.ntiles = g->geom.vpad / SPLIT_SITES;
+    m.rpl = std::max(1, std::min(MR_CHUNK, mrhs_split_rpl(g, (int)prec, a.nrhs, m.ntiles)));
+    m.nchunks = (a.nrhs + m.rpl - 1) / m.rpl;
+    m.rpl = (a.nrhs + m.nchunks - 1) / m.nchunks;  // even chunks
+    block = dim3(SPLIT_BS);
+    if (groups == SPLIT_RANGES) {
+      m.k.tiles_per_slice = (m.ntiles + 7) / 8;  // tiles per range
+      grid = dim3((unsigned)(8 * m.k.tiles_per_slice * m.nchunks));
+    } else if (groups <= -100) {
+      m.nx3 = -groups - 100;
+      grid = dim3((unsigned)(m.ntiles * m.nchunks));
+    } else {
+      grid = dim3((unsigned)m.ntiles, (unsigned)m.nchunks);
+    }
+  } else if (prec == WD_F64 && groups <= -100) {
     m.rpl = 1;
     m.nchunks = a.nrhs;
     m.ntiles = (int)((g->geom.vpad + bs - 1) / bs);

@@ -178,7 +178,11 @@ wd_status wd_set_dslash_variant(wd_gauge *g, wd_prec prec, int block, int groups
 wd_status wd_set_dslash_mrhs_variant(wd_gauge *g, wd_prec prec, int block, int groups, int rpl) {
   if (!g) return set_error(WD_ERR_ARG, "gauge handle is NULL");
   if ((int)prec < 0 || (int)prec > 3) return set_error(WD_ERR_PREC, "prec = %d", (int)prec);
-  if (prec == WD_F64) {
+  if (block == 512) {
+    if (rpl < 1 || rpl > 16) return set_error(WD_ERR_ARG, "multi-RHS rpl %d (1..16)", rpl);
+    if (!mrhs_split_order_ok(g->geom, groups))
+      return set_error(WD_ERR_ARG, "variant (block %d, groups %d) does not fit this lattice", block, groups);
+  } else if (prec == WD_F64) {
     const bool tiles16 = block == 16 && rpl == 4 && groups > -100 && dslash_variant_ok(g->geom, 16, groups);
     const bool box = (block == 64 || block == 128 || block == 256) && rpl == 1 && mrhs_box_ok(g->geom, block, groups);
     if (!tiles16 && !box)
@@ -195,6 +199,7 @@ wd_status wd_set_dslash_mrhs_variant(wd_gauge *g, wd_prec prec, int block, int g
   g->mrhs_block[prec] = block;
   g->mrhs_groups[prec] = groups;
   g->mrhs_rpl[prec] = rpl;
+  g->mrhs_auto[prec] = 0;
   return WD_OK;
 }
 
@@ -410,6 +415,7 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
   wd_status rc = WD_OK;
   int *flag = nullptr;
   const int save = g->mrhs_groups[prec], save_b = g->mrhs_block[prec], save_r = g->mrhs_rpl[prec];
+  const int save_a = g->mrhs_auto[prec];
   const int ref_b = (prec == WD_F64) ? 16 : 128;
   int best_g = 0, best_b = ref_b, best_r = 4;
   double best_us = 1e30;
@@ -432,6 +438,7 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
     }
     if ((rc = hip_check(hipEventCreate(&e0), "event")) != WD_OK) break;
     if ((rc = hip_check(hipEventCreate(&e1), "event")) != WD_OK) break;
+    g->mrhs_auto[prec] = 0;
     g->mrhs_groups[prec] = 0;
     g->mrhs_block[prec] = ref_b;
     g->mrhs_rpl[prec] = 4;
@@ -447,6 +454,9 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
     }
     // candidates listed first: one loop runs them, and a failure ends the search
     std::vector<std::array<int, 3>> cands;
+    for (int rp : {3, 4, 6, 8, 12, 16})  // one wave per direction
+      for (int gr : {(int)WD_ORDER_RANGES, 0, 4, 8, -101, -102, -104, -108})
+        if ((rp <= nrhs || rp == 3) && mrhs_split_order_ok(G, gr)) cands.push_back({rp, 512, gr});
     for (int rp : rpls)
       for (int bs : blocks)
         for (int gr : {0, 2, 4, 8, -8, -16, -101, -102, -104, -108}) {
@@ -487,6 +497,7 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
   g->mrhs_groups[prec] = (rc == WD_OK) ? best_g : save;
   g->mrhs_block[prec] = (rc == WD_OK) ? best_b : save_b;
   g->mrhs_rpl[prec] = (rc == WD_OK) ? best_r : save_r;
+  g->mrhs_auto[prec] = (rc == WD_OK) ? 0 : save_a;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (in) (void)hipFree(in);

@@ -606,23 +606,20 @@ struct SplitOut {
   static constexpr int NW = 12 / CW;
 };
 
-// Components W CW .. of a stored spinor.
-template <int P, int W>
-__device__ __forceinline__ void split_load(const char *base, int i, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
+// Components W CW .. of a stored spinor (w = W may be a run-time value).
+template <int P>
+__device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
   if constexpr (P == WD_F64) {
-    const v2d *p = (const v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * W;
+    const v2d *p = (const v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * w;
     const v2d a = p[0], b = p[64];
     x[0] = {a.x, a.y};
     x[1] = {b.x, b.y};
   } else if constexpr (P == WD_F32) {
-    const v4f v = *((const v4f *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
+    const v4f v = *((const v4f *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w);
     x[0] = {v.x, v.y};
     x[1] = {v.z, v.w};
   } else if constexpr (P == WD_BF16) {
-    const v4u v = *((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x[j] = {bf16_to_f32((uint16_t)(w[j] & 0xffffu)), bf16_to_f32((uint16_t)(w[j] >> 16))};
+    Packet<WD_BF16>::unpack(*((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w), x);
   } else {
     Spinor<P>::load(base, i, x);
   }
@@ -641,7 +638,7 @@ __device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (
   } else if constexpr (P == WD_BF16) {
     uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)f32_to_bf16(x[j].re) | ((uint32_t)f32_to_bf16(x[j].im) << 16);
+    for (int j = 0; j < 4; ++j) w[j] = pack_bf16(x[j].re, x[j].im);
     st_policy<NT>(v4u{w[0], w[1], w[2], w[3]}, (v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * W);
     if constexpr (NORM) {
 #pragma unroll
@@ -689,9 +686,9 @@ __device__ __forceinline__ void split_wave(const KDslash &k, int i, int lane, Sp
   // the epilogue operands are loaded before the barrier
   cplx<T> x[CW], y[CW];
   if constexpr (EPI >= 1)
-    if (i < k.g.vh) split_load<P, W>(k.X, i, x);
+    if (i < k.g.vh) split_load<P>(k.X, i, W, x);
   if constexpr (EPI == 2)
-    if (i < k.g.vh) split_load<P, W>(k.Y, i, y);
+    if (i < k.g.vh) split_load<P>(k.Y, i, W, y);
   __syncthreads();
   split_finish_w<P, DAG, EPI, NORM, W>(k, i, lane, lds, x, y, std::make_integer_sequence<int, CW>{});
 }

@@ -102,6 +102,7 @@ struct wd_gauge {
   int mrhs_groups[4];      // per precision: block -> tile order of the multi-RHS hop
   int mrhs_block[4];       // per precision: sites per block of the FP32/16-bit multi-RHS hop
   int mrhs_rpl[4];         // per precision: right-hand sides per lane of that kernel
+  int mrhs_auto[4];        // per precision: 1 = variant neither set nor tuned (rpl by the lattice's size)
   int hop_lds[4];          // per precision: dynamic LDS bytes per block (caps blocks per CU)
   int hop_pre[4];          // per precision: 1 = links loaded before the first hop (not FP64)
   int hop_spl[4];          // per precision: output sites per lane along x4 (1, 2, 4)
@@ -215,6 +216,10 @@ bool dslash_stage_ok(const Geom &G, int bs);
 size_t dslash_stage_lds_bytes(const Geom &G, int bs, wd_prec prec);
 // box order (groups -(100 + n)) of the FP32-arithmetic multi-RHS hop fits the lattice
 bool mrhs_box_ok(const Geom &G, int bs, int groups);
+// the multi-RHS hop variant of precision index p that a new handle uses
+void mrhs_default_variant(wd_gauge *g, int p);
+// (order) fits the one-wave-per-direction multi-RHS hop (block 512)
+bool mrhs_split_order_ok(const Geom &G, int groups);
 // grid.x of the multi-RHS hop (16 sites per block)
 inline size_t mrhs_grid_blocks(const wd_gauge *g) { return ((size_t)g->geom.vpad + 15) / 16; }
 wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &args, hipStream_t st);

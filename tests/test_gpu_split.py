@@ -9,6 +9,7 @@ import torch
 
 import paper_0710_2442_amd as wd
 import synthetic as syn
+from oracle import solvers
 from gpu_util import BARS_L2, SITE_BARS, assert_close, from_field, to_field
 
 pytestmark = pytest.mark.gpu
@@ -110,4 +111,66 @@ def test_split_dirac_is_bitwise_the_march(dims, prec):
         # same value, each within the precision's bars of it
         assert_close(from_field(g, hops, prec), from_field(g, outs[0], prec), prec, l2=2 * BARS_L2[prec],
                      site=2 * SITE_BARS[prec], what=f"D_W {dims} {prec}")
+    g.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 6, 10), (8, 8, 8, 16)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("nrhs", [1, 5, 17])
+def test_split_mrhs_hop_is_bitwise_the_single_hop(dims, prec, nrhs):
+    """Block 512 with 1, 2, 4 and 16 right-hand sides per block (even and
+    ragged chunks, a buffer of one and of many), every order that fits, and
+    the default's own choice."""
+    g = wd.Gauge(syn.gauge_field(dims, 0.3, 67), dims, -1, prec)
+    psis = syn.gaussian_spinor(dims, 68, nrhs=nrhs)
+    assert wd.wd_get_dslash_mrhs_variant(g, prec)[0] == 512
+    for parity in (wd.WD_EVEN, wd.WD_ODD):
+        src = torch.cat([to_field(g, p, prec, 1 - parity) for p in psis])
+        hb = src.numel() // nrhs
+        ref = torch.empty_like(src)
+        for r in range(nrhs):
+            wd.wd_dslash_ex(g, src[r * hb:(r + 1) * hb], ref[r * hb:(r + 1) * hb], 0.7, parity, prec)
+        n = 0
+        for variant in [None] + [(512, o, rpl) for o in ORDERS for rpl in (1, 2, 4, 16)]:
+            if variant:
+                try:
+                    wd.wd_set_dslash_mrhs_variant(g, prec, *variant)
+                except wd.WdError:
+                    assert variant[1] not in (0, wd.WD_ORDER_RANGES)
+                    continue
+            out = torch.full_like(src, 0xAB)
+            wd.wd_dslash_mrhs(g, src, out, 0.7, parity, prec, nrhs)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref), (variant, parity)
+            n += 1
+        assert n >= 9
+    for bad in ((512, 0, 0), (512, 0, 17), (512, 5, 4)):
+        with pytest.raises(wd.WdError):
+            wd.wd_set_dslash_mrhs_variant(g, prec, *bad)
+    g.close()
+
+
+@pytest.mark.parametrize("inner", ["f32", "f16", "bf16"])
+def test_split_mrhs_solve_matches_the_single_solves(inner):
+    """Epilogues, per-RHS norms and skip flags of the multi-RHS hop in a solve
+    whose systems stop at different iterations (a point source, a zero source
+    and Gaussian ones) on a lattice with padding slots: each system's solution
+    solves its own equation."""
+    dims, kappa = (6, 4, 6, 10), 0.12
+    U = syn.gauge_field(dims, 0.3, 69)
+    g = wd.Gauge(U, dims, -1, "f64")
+    b = [syn.point_source(dims, 1, 2), 0 * syn.point_source(dims, 0, 0)]
+    b += [syn.gaussian_spinor(dims, 70 + r) for r in range(5)]
+    fb = torch.cat([to_field(g, x) for x in b])
+    fx = torch.empty_like(fb)
+    p = wd.wd_solve_params_default(solver=wd.WD_SOLVER_DEFECT_CG, inner_prec=inner, inner_tol=1e-2)
+    rc, infos = wd.wd_solve_mrhs(g, fb, fx, len(b), kappa, 1e-10, p)
+    assert rc == 0 and all(i["status"] == 0 for i in infos)
+    n = fb.numel() // len(b)
+    for r, src in enumerate(b):
+        x = from_field(g, fx[r * n:(r + 1) * n])
+        if r == 1:
+            assert not x.any()
+        else:
+            assert solvers.true_residual(U, src, x, kappa) <= 1.01e-10
     g.close()
