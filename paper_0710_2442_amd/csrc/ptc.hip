@@ -22,8 +22,10 @@
 // adjoint weights W'^{(hbar)}_{c c'} = (W^{(h)}_{c'c})^dag, hbar the adjoint hop
 // (T_{+mu}^dag = T_{-mu}), so it is a gather with no atomics.  The weight
 // gradient G^{(h)}_{c'c}[s',s] = sum_x sum_a g_{c'}(x)[s',a] conj((T_h psi_c)(x)[s,a])
-// is summed over a wave's sites in FP64 (through LDS), then over the block's
-// waves and the blocks in FP64, each in a fixed order.
+// is a contraction over sites and colours and runs on the FP64 matrix cores
+// (exact products of the FP32 operands, FP64 sums), then over the block's
+// waves and the blocks in FP64, each in a fixed order.  The samples of a batch
+// go through each kernel together.
 #include <math.h>
 #include <string.h>
 
@@ -52,56 +54,57 @@ struct KPtc {
   size_t in_chan;       // bytes per input channel (full field)
   size_t out_chan;
   size_t in_half, out_half;  // bytes per half field
+  size_t in_samp, out_samp;  // bytes per sample (blockIdx.z)
   const float *W;       // this layer's weights [9][cout][cin][4][4] (re, im)
-  // weight gradient
-  const char *gy;       // C_out full fields, FP32 gradients
-  size_t gy_chan, gy_half;
-  double *partials;     // [nblocks][nparam floats]
-  int accumulate;       // add to existing partials
+  // layer 2 of the loss: out = scale (N(r) - e), and each block's sum of |N(r) - e|^2
+  const char *e;
+  size_t e_samp;
+  float scale;
+  double *loss;         // [block of the launch]
+  int accumulate;       // add to the sums that are there
 };
 
 // Coordinates and neighbours of checkerboard site i on parity p (same
 // arithmetic as the hop kernel).
 struct PtcSite {
-  int nb[8];
-  float sf, sb;
+  int x1, x2, x3, x4, rest;
 };
 
 __device__ __forceinline__ PtcSite ptc_site(const Geom &g, int i, int p) {
   PtcSite s;
-  const int x1h = i % g.L1h;
-  const int rest = i / g.L1h;
-  const int x2 = rest % g.L[1];
-  const int r2 = rest / g.L[1];
-  const int x3 = r2 % g.L[2];
-  const int x4 = r2 / g.L[2];
-  const int x1 = 2 * x1h + ((p + x2 + x3 + x4) & 1);
-  const int xp1 = (x1 + 1 == g.L[0]) ? 0 : x1 + 1;
-  const int xm1 = (x1 == 0) ? g.L[0] - 1 : x1 - 1;
-  s.nb[0] = (xp1 >> 1) + g.L1h * rest;
-  s.nb[4] = (xm1 >> 1) + g.L1h * rest;
-  s.nb[1] = i + ((x2 == g.L[1] - 1) ? -(g.L[1] - 1) * g.s2 : g.s2);
-  s.nb[5] = i + ((x2 == 0) ? (g.L[1] - 1) * g.s2 : -g.s2);
-  s.nb[2] = i + ((x3 == g.L[2] - 1) ? -(g.L[2] - 1) * g.s3 : g.s3);
-  s.nb[6] = i + ((x3 == 0) ? (g.L[2] - 1) * g.s3 : -g.s3);
-  s.nb[3] = i + ((x4 == g.L[3] - 1) ? -(g.L[3] - 1) * g.s4 : g.s4);
-  s.nb[7] = i + ((x4 == 0) ? (g.L[3] - 1) * g.s4 : -g.s4);
-  s.sf = (x4 == g.L[3] - 1) ? g.tbc : 1.0f;
-  s.sb = (x4 == 0) ? g.tbc : 1.0f;
+  s.rest = fdiv(i, g.dl1h);
+  const int x1h = i - s.rest * g.L1h;
+  const int r2 = fdiv(s.rest, g.dl2);
+  s.x2 = s.rest - r2 * g.L[1];
+  s.x4 = fdiv(r2, g.dl3);
+  s.x3 = r2 - s.x4 * g.L[2];
+  s.x1 = 2 * x1h + ((p + s.x2 + s.x3 + s.x4) & 1);
   return s;
 }
 
-// a[d] without dynamic register indexing (a rolled loop would spill it)
-__device__ __forceinline__ int pick8(const int (&a)[8], int d) {
-  int r = a[0];
-#pragma unroll
-  for (int j = 1; j < 8; ++j) r = (d == j) ? a[j] : r;
-  return r;
+// Index (other parity) of the neighbour in direction d (0-3 forward, 4-7
+// backward) and the hop's time-boundary factor.  d is the same in every lane,
+// so the selects cost less than the registers of all eight indices.  (All
+// members are read first: reads behind a choice become one read at a chosen
+// address, which indexes the structs in scratch.)
+__device__ __forceinline__ int ptc_nb(const Geom &g, const PtcSite &s, int i, int d) {
+  const int mu = d & 3;
+  const bool back = d >= 4;
+  const int x1 = s.x1, x2 = s.x2, x3 = s.x3, x4 = s.x4;
+  const int L0 = g.L[0], L1 = g.L[1], L2 = g.L[2], L3 = g.L[3], s2 = g.s2, s3 = g.s3, s4 = g.s4;
+  const int x = (mu == 0) ? x1 : ((mu == 1) ? x2 : ((mu == 2) ? x3 : x4));
+  const int L = (mu == 0) ? L0 : ((mu == 1) ? L1 : ((mu == 2) ? L2 : L3));
+  const int st = (mu == 1) ? s2 : ((mu == 2) ? s3 : s4);
+  const int y = back ? (x == 0 ? L - 1 : x - 1) : (x == L - 1 ? 0 : x + 1);
+  return (mu == 0) ? (y >> 1) + g.L1h * s.rest : i + (y - x) * st;
+}
+__device__ __forceinline__ float ptc_sign(const Geom &g, const PtcSite &s, int d) {
+  return (d == 3 && s.x4 == g.L[3] - 1) || (d == 7 && s.x4 == 0) ? g.tbc : 1.0f;
 }
 
 // v = T_h psi_c at site (p, i); psi channel base `chan` (full field).
-template <int PIN>
-__device__ __forceinline__ void transport(const KPtc &k, const PtcSite &s, int p, int i, int h, const char *chan,
+template <int PIN, class K>
+__device__ __forceinline__ void transport(const K &k, const PtcSite &s, int p, int i, int h, const char *chan,
                                           cplx<float> (&v)[12]) {
   if (h == 0) {
     cplx<RealOf<PIN>> t[12];
@@ -112,11 +115,11 @@ __device__ __forceinline__ void transport(const KPtc &k, const PtcSite &s, int p
   }
   const int d = h - 1;
   cplx<RealOf<PIN>> t[12];
-  Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, pick8(s.nb, d), t);
+  Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, ptc_nb(k.g, s, i, d), t);
   cplx<float> u[6], r2[3];
   Link<float>::load(k.links32 + (size_t)p * k.link_par, d, i, u);
   rebuild_row2(u, r2);
-  const float sg = (d == 3) ? s.sf : ((d == 7) ? s.sb : 1.0f);
+  const float sg = ptc_sign(k.g, s, d);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp) {
     cplx<float> a[3] = {{(float)t[3 * sp].re, (float)t[3 * sp].im},
@@ -137,7 +140,7 @@ __device__ __forceinline__ void load_source(const KPtc &k, const PtcSite &s, int
                                             cplx<float> (&v)[12]) {
   cplx<RealOf<PIN>> t[12];
   if (h == 0) Spinor<PIN>::load(chan + (size_t)p * k.in_half, i, t);
-  else Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, pick8(s.nb, h - 1), t);
+  else Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, ptc_nb(k.g, s, i, h - 1), t);
 #pragma unroll
   for (int c = 0; c < 12; ++c) v[c] = {(float)t[c].re, (float)t[c].im};
 }
@@ -148,7 +151,7 @@ __device__ __forceinline__ void transport_add(const KPtc &k, const PtcSite &s, i
   cplx<float> u[6], r2[3];
   Link<float>::load(k.links32 + (size_t)p * k.link_par, d, i, u);
   rebuild_row2(u, r2);
-  const float sg = (d == 3) ? s.sf : ((d == 7) ? s.sb : 1.0f);
+  const float sg = ptc_sign(k.g, s, d);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp) {
     cplx<float> a[3] = {m[3 * sp], m[3 * sp + 1], m[3 * sp + 2]};
@@ -178,21 +181,9 @@ __device__ __forceinline__ void spin_mat_acc(const float *W, const cplx<float> (
 // INPAR = -1: the input lives on both parities.  INPAR = q: the input is zero
 // off parity q, so a site of parity q takes only the h = 0 term and a site of
 // the other parity only the hops (h >= 1); the zero terms are not read.
-template <int PIN, int POUT, int CIN, int COUT, int INPAR = -1>
-__global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
-  const int p = blockIdx.y;
-  const int i = blockIdx.x * PTC_BS + threadIdx.x;
-  if (i >= k.g.vpad) return;
-  cplx<RealOf<POUT>> o[12];
-  if (i >= k.g.vh) {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = {0, 0};
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) Spinor<POUT>::store(k.out + co * k.out_chan + (size_t)p * k.out_half, i, o);
-    return;
-  }
+template <int PIN, int CIN, int COUT, int INPAR>
+__device__ __forceinline__ void ptc_layer_site(const KPtc &k, int i, int p, cplx<float> (&acc)[COUT][12]) {
   const PtcSite s = ptc_site(k.g, i, p);
-  cplx<float> acc[COUT][12];
 #pragma unroll
   for (int co = 0; co < COUT; ++co)
 #pragma unroll
@@ -230,6 +221,53 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
       }
     }
   }
+}
+
+// LOSS: the layer's output y becomes scale (y - e) and the block's sum of
+// |y - e|^2 is stored (or added to k.loss), so y itself is never written.
+template <int PIN, int POUT, int CIN, int COUT, int INPAR = -1, bool LOSS = false>
+__global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
+  const int p = blockIdx.y;
+  const int i = blockIdx.x * PTC_BS + threadIdx.x;  // < vpad: a multiple of PTC_BS
+  k.in += blockIdx.z * k.in_samp;
+  k.out += blockIdx.z * k.out_samp;
+  cplx<RealOf<POUT>> o[12];
+  if constexpr (LOSS) {
+    double sum = 0.0;
+    if (i < k.g.vh) {
+      cplx<float> y[COUT][12], e[12];
+      ptc_layer_site<PIN, CIN, COUT, INPAR>(k, i, p, y);
+      Spinor<WD_F32>::load(k.e + blockIdx.z * k.e_samp + (size_t)p * k.out_half, i, e);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        const cplx<float> d = y[0][c] - e[c];
+        sum += (double)d.re * d.re + (double)d.im * d.im;
+        o[c] = {k.scale * d.re, k.scale * d.im};
+      }
+      Spinor<POUT>::template store<false>(k.out + (size_t)p * k.out_half, i, o);
+    }
+    __shared__ double ws[PTC_BS / 64];
+    const double t = wave_sum(sum);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double b = 0.0;
+#pragma unroll
+      for (int j = 0; j < PTC_BS / 64; ++j) b += ws[j];
+      double *dst = k.loss + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+      *dst = k.accumulate ? *dst + b : b;
+    }
+    return;
+  }
+  if (i >= k.g.vh) {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) o[c] = {0, 0};
+#pragma unroll
+    for (int co = 0; co < COUT; ++co) Spinor<POUT>::store(k.out + co * k.out_chan + (size_t)p * k.out_half, i, o);
+    return;
+  }
+  cplx<float> acc[COUT][12];
+  ptc_layer_site<PIN, CIN, COUT, INPAR>(k, i, p, acc);
 #pragma unroll
   for (int co = 0; co < COUT; ++co) {
 #pragma unroll
@@ -238,92 +276,209 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
   }
 }
 
-// Weight gradient of one layer: partials[block][f] (+)= block sum of the
-// per-site products; f indexes the layer's floats [h][c'][c][s'][s](re,im).
-// The products of one (h, c', c) chunk (32 floats per site) go through LDS:
-// each wave writes its 64 sites' rows, then lane f < 32 adds column f over
-// the 64 sites in FP64 (site order), and the block adds its 4 waves in FP64.
-template <int PIN, int CIN, int COUT>
-__global__ __launch_bounds__(PTC_BS) void k_ptc_wgrad(KPtc k) {
-  constexpr int NF = 9 * COUT * CIN * 32;
+// Weight gradient of one layer over the samples of a batch, as a matrix product
+// over sites and colours.
+//
+// D[m][n] = sum over sites, colours of F_m T_n on v_mfma_f64_16x16x4_f64: row m
+// = 8c + 2s + (re, im) of the two-channel field F at the site itself, column n
+// = 8 slot + 2s + (re, im) of the one-channel field T transported by a pair of
+// hops.  For layer 1 -> 2 (TG = false) F is the output gradient and T_h the
+// transported input.  For layer 2 -> 1 (TG) the sum is taken at the input's
+// site instead,
+//   sum_x g(x) conj((T_h psi_c)(x)) = sum_y (T_hbar g)(y) conj(psi_c(y)),
+// so that one field is transported instead of two.  A wave takes 64 sites: a lane
+// transports its own site's spinor and leaves it in LDS component by
+// component, and reads the four sites of its K slot back as one 16-byte row
+// piece (rows of 68 floats: no bank conflicts).  No barrier: a wave's LDS
+// accesses complete in order.  The sums stay in the matrix cores' FP64
+// registers over all of a wave's sites; 5 pairs of hops (h = 0 alone), 48
+// products each per 64 sites.
+// Bound by the FP64 products (240 of 64 cycles per 64 sites: 51 us of the 124
+// below at the full rate) next to the transports' vector work.  Each
+// lane summing its site's products and a wave adding 64 rows per float in FP64
+// took 55 us a sample of 16^4 on 256 blocks; 8 samples together now take 124
+// (layer 1, BF16 input) and 120 us (layer 2).
+typedef double d4v __attribute__((ext_vector_type(4)));
+constexpr int WG_BLOCKS = 512;  // two blocks per CU of 256
+constexpr int WG_ROW = 68;
+
+struct KWg {
+  Geom g;
+  const char *links32;
+  size_t link_par;
+  const char *t;            // transported field (one channel)
+  size_t in_half, t_samp;
+  const char *f;            // field at the site (two channels)
+  size_t f_half;
+  double *partials;         // [block][576]
+  int accumulate;           // add to the partials that are there
+  int nch;                  // groups of 64 sites per parity
+  long units;               // samples * 2 * nch
+};
+
+template <int PT, int PF, bool TG>
+__global__ __launch_bounds__(PTC_BS, 2) void k_ptc_wgrad(KWg k) {
   constexpr int NW = PTC_BS / 64;
-  __shared__ float tile[NW][64][33];  // one chunk's products per wave (row padded: no bank conflicts)
-  __shared__ double wsum[NW][NF];     // the waves' site sums
-  const int p = blockIdx.y;
-  const int i = blockIdx.x * PTC_BS + threadIdx.x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const bool live = i < k.g.vh;
-  PtcSite s;
-  cplx<float> gy[COUT][12];
-  if (live) {
-    s = ptc_site(k.g, i, p);
+  __shared__ __align__(16) float tile[NW][48 * WG_ROW];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  float *T = tile[w];
+  d4v acc[5];
 #pragma unroll
-    for (int co = 0; co < COUT; ++co)
-      Spinor<WD_F32>::load(k.gy + co * k.gy_chan + (size_t)p * k.gy_half, i, gy[co]);
-  }
+  for (int j = 0; j < 5; ++j) acc[j] = d4v{0, 0, 0, 0};
+  for (long u = (long)blockIdx.x * NW + w; u < k.units; u += (long)gridDim.x * NW) {
+    const int smp = (int)(u / (2 * k.nch)), r = (int)(u - (long)smp * (2 * k.nch));
+    const int p = r >= k.nch ? 1 : 0;
+    const int i0 = (r - p * k.nch) * 64 + lane;
+    const int i = min(i0, k.g.vh - 1);
+    const uint32_t live = i0 < k.g.vh ? 0xffffffffu : 0u;  // lanes past the last site add products with zero
+    const PtcSite s = ptc_site(k.g, i, p);
+    const char *tb = k.t + smp * k.t_samp;
+    // the field at the site, as the A operand: F[a][j] = row n, colour a, site 16q + j
+    float F[3][16];
 #pragma unroll
-  for (int h = 0; h < 9; ++h) {
+    for (int c = 0; c < 2; ++c) {
+      cplx<RealOf<PF>> x[12];
+      Spinor<PF>::load(k.f + (smp * 2 + c) * (2 * k.f_half) + (size_t)p * k.f_half, i, x);
 #pragma unroll
-    for (int ci = 0; ci < CIN; ++ci) {
-      cplx<float> v[12];
-      if (live) {
-        transport<PIN>(k, s, p, i, h, k.in + ci * k.in_chan, v);
-      } else {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) v[c] = {0.f, 0.f};
-      }
-#pragma unroll
-      for (int co = 0; co < COUT; ++co) {
-        float row[32];
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp) {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            cplx<float> acc = {0.f, 0.f};
-            if (live) {
-#pragma unroll
-              for (int a = 0; a < 3; ++a) {
-                // gy[s',a] * conj(v[s,a])
-                const cplx<float> g = gy[co][3 * sp + a], x = v[3 * t + a];
-                acc.re += g.re * x.re + g.im * x.im;
-                acc.im += g.im * x.re - g.re * x.im;
-              }
-            }
-            row[2 * (4 * sp + t)] = acc.re;
-            row[2 * (4 * sp + t) + 1] = acc.im;
-          }
-        }
-#pragma unroll
-        for (int f = 0; f < 32; ++f) tile[w][lane][f] = row[f];
-        __builtin_amdgcn_wave_barrier();  // a wave's LDS accesses complete in order
-        if (lane < 32) {
-          double t = 0.0;
-#pragma unroll 4
-          for (int q = 0; q < 64; ++q) t += (double)tile[w][q][lane];
-          wsum[w][((h * COUT + co) * CIN + ci) * 32 + lane] = t;
-        }
-        __builtin_amdgcn_wave_barrier();
+      for (int j = 0; j < 12; ++j) {
+        const int row = (j % 3) * 16 + 8 * c + 2 * (j / 3);
+        T[row * WG_ROW + lane] = __uint_as_float(__float_as_uint((float)x[j].re) & live);
+        T[(row + 1) * WG_ROW + lane] = __uint_as_float(__float_as_uint((float)x[j].im) & live);
       }
     }
-  }
-  __syncthreads();
-  const size_t blk = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-  for (int f = threadIdx.x; f < NF; f += PTC_BS) {
-    double t = 0.0;
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int q = 0; q < NW; ++q) t += wsum[q][f];
-    double *dst = k.partials + blk * NF + f;
-    *dst = k.accumulate ? (*dst + t) : t;
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const v4f x = *(const v4f *)(T + (a * 16 + n) * WG_ROW + 16 * q + 4 * j);
+        F[a][4 * j] = x.x, F[a][4 * j + 1] = x.y, F[a][4 * j + 2] = x.z, F[a][4 * j + 3] = x.w;
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+    for (int h = 0; h < 9; ++h) {
+      cplx<float> v[12];
+      transport<PT>(k, s, p, i, h, tb, v);
+      float *Th = T + ((h > 0 && !(h & 1)) ? 8 * WG_ROW : 0) + lane;
+#pragma unroll
+      for (int j = 0; j < 12; ++j) {
+        const int row = (j % 3) * 16 + 2 * (j / 3);
+        Th[row * WG_ROW] = v[j].re;
+        Th[(row + 1) * WG_ROW] = v[j].im;
+      }
+      if (h & 1) continue;
+      // h = 0, or the second hop of a pair (the columns of slot 1 are not used for h = 0)
+      __builtin_amdgcn_wave_barrier();
+      auto products = [&](d4v D) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const v4f x = *(const v4f *)(T + (a * 16 + n) * WG_ROW + 16 * q + 4 * j);
+            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j], x.x, D, 0, 0, 0);
+            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 1], x.y, D, 0, 0, 0);
+            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 2], x.z, D, 0, 0, 0);
+            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 3], x.w, D, 0, 0, 0);
+          }
+        return D;
+      };
+      // the products go straight into the pair's sums: a sum of D and acc after
+      // this branch is read too early (the compiler counts the wait states of
+      // FP64 products short across branches)
+      switch (h >> 1) {
+        case 0: acc[0] = products(acc[0]); break;
+        case 1: acc[1] = products(acc[1]); break;
+        case 2: acc[2] = products(acc[2]); break;
+        case 3: acc[3] = products(acc[3]); break;
+        default: acc[4] = products(acc[4]); break;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  asm volatile("s_nop 15\n\ts_nop 7");  // the last products (18 wait states)
+  // the block's sum over its waves; the products of real components combine
+  // into the complex gradient
+  __syncthreads();
+  double *R = (double *)tile[w];
+#pragma unroll
+  for (int j = 0; j < 5; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) R[j * 256 + (4 * e + q) * 16 + n] = acc[j][e];  // row 4e + lane / 16, column lane % 16
+  __syncthreads();
+  for (int f = threadIdx.x; f < 288; f += PTC_BS) {
+    const int h = f >> 5, c = (f >> 4) & 1, sr = (f >> 2) & 3, sc = f & 3;
+    const int ht = (TG && h > 0) ? (h <= 4 ? h + 4 : h - 4) : h;  // the hop whose transport holds the term
+    const int m = 8 * c + 2 * (TG ? sc : sr);
+    const int col = ((ht > 0 && !(ht & 1)) ? 8 : 0) + 2 * (TG ? sr : sc);
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      const double *P = (const double *)tile[j] + ((ht + 1) >> 1) * 256 + m * 16 + col;
+      re += P[0] + P[17];
+      im += TG ? P[1] - P[16] : P[16] - P[1];
+    }
+    double *dst = k.partials + (size_t)blockIdx.x * 576 + 2 * f;
+    dst[0] = k.accumulate ? dst[0] + re : re;
+    dst[1] = k.accumulate ? dst[1] + im : im;
   }
 }
 
-// grad[f] = sum over blocks of partials[b][f], in block order.
-__global__ __launch_bounds__(256) void k_ptc_reduce(const double *partials, int nblk, int nf, float *grad) {
-  const int f = blockIdx.x * 256 + threadIdx.x;
-  if (f >= nf) return;
-  double t = 0.0;
-  for (int b = 0; b < nblk; ++b) t += partials[(size_t)b * nf + f];
-  grad[f] = (float)t;
+// Gradient of both layers and the loss from the blocks' partial sums: one
+// block per spin matrix adds its 32 floats over the blocks (32 threads each,
+// in a fixed order) and rotates the matrix into the chiral basis (W = S Wc S, S
+// orthogonal and symmetric, see k_ptc_rotate); the last block adds up the loss.
+constexpr int GRAD_BS = 1024;
+__global__ __launch_bounds__(GRAD_BS) void k_ptc_grad(const double *partials, int nblk, const double *loss, int nloss,
+                                                      float *gradc, double *loss_out) {
+  __shared__ double part[32][33];
+  __shared__ float M[32], MS[32];
+  const int f = threadIdx.x & 31, t = threadIdx.x >> 5;
+  const int mat = blockIdx.x;
+  double sum = 0.0;
+  if (mat < PTC_NW / 32) {
+    const double *src = partials + (size_t)(mat / 18) * WG_BLOCKS * 576 + (mat % 18) * 32 + f;
+#pragma unroll 4
+    for (int b = t; b < nblk; b += 32) sum += src[(size_t)b * 576];
+  } else {
+    for (int b = threadIdx.x; b < nloss; b += GRAD_BS) sum += loss[b];
+  }
+  part[t][f] = sum;
+  __syncthreads();
+  if (t != 0) return;
+  double tot = 0.0;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) tot += part[j][f];
+  if (mat == PTC_NW / 32) {
+    part[0][f] = tot;
+    __builtin_amdgcn_wave_barrier();
+    if (f == 0) {
+      double l = 0.0;
+      for (int j = 0; j < 32; ++j) l += part[0][j];
+      *loss_out = l;
+    }
+    return;
+  }
+  // S = (1/sqrt 2) [[1, 1], [1, -1]]: column b of M S = r (M_b' +- M_b''), as k_ptc_rotate
+  const float r = 0.70710678118654752440f;
+  M[f] = (float)tot;
+  __builtin_amdgcn_wave_barrier();
+  const int ri = f & 1, b = (f >> 1) & 3, a = f >> 3;
+  float x = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float S = ((j & 1) == (b & 1)) ? ((j >= 2 && b >= 2) ? -r : r) : 0.f;
+    x += M[2 * (4 * a + j) + ri] * S;
+  }
+  MS[f] = x;
+  __builtin_amdgcn_wave_barrier();
+  float y = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float S = ((a & 1) == (j & 1)) ? ((a >= 2 && j >= 2) ? -r : r) : 0.f;
+    y += S * MS[2 * (4 * j + b) + ri];
+  }
+  gradc[mat * 32 + f] = y;
 }
 
 // Adjoint weights for the input gradient of a layer (cout x cin):
@@ -375,36 +530,6 @@ __global__ void k_ptc_rotate(const float *M, float *out, int n) {
       dst[2 * (4 * a + b)] = re;
       dst[2 * (4 * a + b) + 1] = im;
     }
-}
-
-// Loss pieces: d = y - e (FP32 full fields); gy = scale * d; each block
-// stores its FP64 partial sum of |d|^2, which the finishing kernel adds up in
-// block order.
-__global__ __launch_bounds__(256) void k_ptc_loss(const char *y, const char *e, char *gy, Geom g, float scale,
-                                                  double *partials) {
-  const int p = blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const size_t hb = (size_t)96 * g.vpad;  // one FP32 half field
-  double acc = 0.0;
-  if (i < g.vpad) {
-    cplx<float> a[12], b[12];
-    if (i < g.vh) {
-      Spinor<WD_F32>::load(y + p * hb, i, a);
-      Spinor<WD_F32>::load(e + p * hb, i, b);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        a[c] = a[c] - b[c];
-        acc += (double)a[c].re * a[c].re + (double)a[c].im * a[c].im;
-        a[c] = scale * a[c];
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 12; ++c) a[c] = {0.f, 0.f};
-    }
-    Spinor<WD_F32>::store(gy + p * hb, i, a);
-  }
-  double v[1] = {acc};
-  block_sum_store<1>(v, partials, gridDim.x * gridDim.y, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // Adam on the 1152 real parameters (real and imaginary parts separately).
@@ -562,16 +687,16 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_h_l1(KPtcH k) {
     } else {
       const PtcSite s = ptc_site(k.g, i, 1);
       RawH nx;
-      raw_h(k, k.in, s.nb[0], 1, 0, i, nx);
+      raw_h(k, k.in, ptc_nb(k.g, s, i, 0), 1, 0, i, nx);
 #pragma unroll
       for (int d = 0; d < 8; ++d) {
         const RawH cur = nx;
-        if (d < 7) raw_h(k, k.in, s.nb[d + 1], 1, d + 1, i, nx);
+        if (d < 7) raw_h(k, k.in, ptc_nb(k.g, s, i, d + 1), 1, d + 1, i, nx);
         HPk v[12];
         unpack_spinor_h(cur.q, sc, v);
         hv2 u[9];
         unpack_link_h(cur.l, u);
-        const float sg = (d == 3) ? s.sf : ((d == 7) ? s.sb : 1.0f);
+        const float sg = ptc_sign(k.g, s, d);
         cplx<float> y[12];
         transport_h(u, v, sg, y);
         HPk yv[12];
@@ -598,9 +723,9 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_h_l2(KPtcH k) {
   if (i < k.g.vh) {
     const PtcSite s = ptc_site(k.g, i, 0);
     RawH n0, n1;  // the two channels at the next neighbour (links in n0)
-    raw_h(k, k.in + k.in_half, s.nb[0], 0, 0, i, n0);
+    raw_h(k, k.in + k.in_half, ptc_nb(k.g, s, i, 0), 0, 0, i, n0);
     {
-      const v4u *b = (const v4u *)(k.in + k.in_chan + k.in_half) + chunk_base<Spinor<WD_BF16>::CHUNK>(s.nb[0]);
+      const v4u *b = (const v4u *)(k.in + k.in_chan + k.in_half) + chunk_base<Spinor<WD_BF16>::CHUNK>(ptc_nb(k.g, s, i, 0));
 #pragma unroll
       for (int q = 0; q < 3; ++q) n1.q[q] = b[64 * q];
     }
@@ -615,7 +740,7 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_h_l2(KPtcH k) {
       const RawH c0 = n0;
       const v4u c1[3] = {n1.q[0], n1.q[1], n1.q[2]};
       if (d < 7) {
-        const int nb = pick8(s.nb, d + 1);
+        const int nb = ptc_nb(k.g, s, i, d + 1);
         raw_h(k, k.in + k.in_half, nb, 0, d + 1, i, n0);
         const v4u *b = (const v4u *)(k.in + k.in_chan + k.in_half) + chunk_base<Spinor<WD_BF16>::CHUNK>(nb);
 #pragma unroll
@@ -636,7 +761,7 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_h_l2(KPtcH k) {
       for (int c = 0; c < 12; ++c) mv[c] = hpk(m[c].re, m[c].im);
       hv2 u[9];
       unpack_link_h(c0.l, u);
-      const float sg = (d == 3) ? s.sf : ((d == 7) ? s.sb : 1.0f);
+      const float sg = ptc_sign(k.g, s, d);
       cplx<float> y[12];
       transport_h(u, mv, sg, y);
 #pragma unroll
@@ -1126,15 +1251,18 @@ struct wd_ptc {
   float *Wc;       // device, the parameters: chiral-basis weights, 1152 floats
   float *gradc;    // device, gradient with respect to Wc
   float *W;        // device, the same weights in the storage spin basis (used by the kernels)
-  float *Wadj;     // device, adjoint weights of both layers
-  float *grad;     // device, 1152
+  float *Wadj;     // device, adjoint weights of layer 2
   float *m, *v;    // Adam state
   int t;           // Adam steps taken
   wd_prec act;     // activation storage (WD_BF16 or WD_F32)
-  void *x0, *y1, *y2, *gy2, *gy1;  // activations / gradients of one sample
-  double *partials;                // wgrad partials: layer 1 then layer 2, nblk x 576 each
-  double *scal;                    // [0] loss; [64..] reduction partials
-  int nblk;                        // blocks of a full-lattice launch (both parities)
+  void *x0, *y1;   // input and hidden layer of one application
+  // training: the input, hidden layer and both gradients of tcap samples (one
+  // allocation, made for the first batch and for a larger one), and the
+  // partial sums of the weight gradients (both layers) and of the loss
+  char *tbuf;
+  int tcap;
+  double *partials;                // [layer][WG_BLOCKS][576]
+  double *scal;                    // [0] loss; [64..] its partials, one per block of the layer launch
   // FP16-product inference (made on first use): FP16 hop links of both
   // parities, FP16 weights, and the input norm with its reduction partials
   uint2 *links16;
@@ -1156,25 +1284,28 @@ static KPtc ptc_k(const wd_ptc *n) {
   return k;
 }
 
-static dim3 ptc_grid(const Geom &G) { return dim3((unsigned)((G.vpad + PTC_BS - 1) / PTC_BS), 2); }
+static dim3 ptc_grid(const Geom &G, int nsamp = 1) {
+  return dim3((unsigned)((G.vpad + PTC_BS - 1) / PTC_BS), 2, (unsigned)nsamp);
+}
 
 template <int PIN, int POUT>
-static void launch_layer(const KPtc &k, int cin, int cout, hipStream_t st) {
-  const dim3 grid = ptc_grid(k.g);
+static void launch_layer(const KPtc &k, int cin, int cout, int nsamp, hipStream_t st) {
+  const dim3 grid = ptc_grid(k.g, nsamp);
   if (cin == 1 && cout == 2) hipLaunchKernelGGL((k_ptc_layer<PIN, POUT, 1, 2>), grid, dim3(PTC_BS), 0, st, k);
   else hipLaunchKernelGGL((k_ptc_layer<PIN, POUT, 2, 1>), grid, dim3(PTC_BS), 0, st, k);
 }
 
-static void dispatch_layer(const KPtc &k, wd_prec pin, wd_prec pout, int cin, int cout, hipStream_t st) {
-  if (pin == WD_BF16 && pout == WD_BF16) launch_layer<WD_BF16, WD_BF16>(k, cin, cout, st);
-  else if (pin == WD_BF16 && pout == WD_F32) launch_layer<WD_BF16, WD_F32>(k, cin, cout, st);
-  else if (pin == WD_F32 && pout == WD_BF16) launch_layer<WD_F32, WD_BF16>(k, cin, cout, st);
-  else launch_layer<WD_F32, WD_F32>(k, cin, cout, st);
+static void dispatch_layer(const KPtc &k, wd_prec pin, wd_prec pout, int cin, int cout, int nsamp, hipStream_t st) {
+  if (pin == WD_BF16 && pout == WD_BF16) launch_layer<WD_BF16, WD_BF16>(k, cin, cout, nsamp, st);
+  else if (pin == WD_BF16 && pout == WD_F32) launch_layer<WD_BF16, WD_F32>(k, cin, cout, nsamp, st);
+  else if (pin == WD_F32 && pout == WD_BF16) launch_layer<WD_F32, WD_BF16>(k, cin, cout, nsamp, st);
+  else launch_layer<WD_F32, WD_F32>(k, cin, cout, nsamp, st);
 }
 
-// out (pout, cout channels) = layer(in (pin, cin channels)) with weights W.
+// out (pout, cout channels) = layer(in (pin, cin channels)) with weights W, on
+// nsamp consecutive samples.
 static wd_status ptc_layer(const wd_ptc *n, const float *W, const void *in, wd_prec pin, int cin, void *out,
-                           wd_prec pout, int cout, hipStream_t st) {
+                           wd_prec pout, int cout, hipStream_t st, int nsamp = 1) {
   KPtc k = ptc_k(n);
   k.in = (const char *)in;
   k.out = (char *)out;
@@ -1182,29 +1313,62 @@ static wd_status ptc_layer(const wd_ptc *n, const float *W, const void *in, wd_p
   k.out_half = half_bytes(k.g, pout);
   k.in_chan = 2 * k.in_half;
   k.out_chan = 2 * k.out_half;
+  k.in_samp = cin * k.in_chan;
+  k.out_samp = cout * k.out_chan;
   k.W = W;
-  dispatch_layer(k, pin, pout, cin, cout, st);
+  dispatch_layer(k, pin, pout, cin, cout, nsamp, st);
   return hip_check(hipGetLastError(), "ptc layer");
 }
 
-// Weight-gradient partials of one layer (layer 0: 1 -> 2, layer 1: 2 -> 1).
-static wd_status ptc_wgrad(const wd_ptc *n, int layer, const void *in, wd_prec pin, const void *gy, int accumulate,
-                           hipStream_t st) {
+// Layer 2 of nsamp samples with the loss in its epilogue (k_ptc_layer, LOSS).
+static wd_status ptc_loss_layer(const wd_ptc *n, const void *y1, const void *e, void *gy2, float scale, int nsamp,
+                                bool accumulate, hipStream_t st) {
   KPtc k = ptc_k(n);
-  k.in = (const char *)in;
-  k.in_half = half_bytes(k.g, pin);
+  k.in = (const char *)y1;
+  k.out = (char *)gy2;
+  k.in_half = half_bytes(k.g, n->act);
   k.in_chan = 2 * k.in_half;
-  k.gy = (const char *)gy;
-  k.gy_half = half_bytes(k.g, WD_F32);
-  k.gy_chan = 2 * k.gy_half;
-  k.partials = n->partials + (size_t)layer * n->nblk * 576;
+  k.in_samp = 2 * k.in_chan;
+  k.out_half = half_bytes(k.g, WD_F32);
+  k.out_chan = 2 * k.out_half;
+  k.out_samp = k.out_chan;
+  k.W = n->W + 576;
+  k.e = (const char *)e;
+  k.e_samp = k.out_chan;
+  k.scale = scale;
+  k.loss = n->scal + 64;
   k.accumulate = accumulate;
-  const dim3 grid = ptc_grid(k.g);
-#define WD_WG(PIN)                                                                                 \
-  if (layer == 0) hipLaunchKernelGGL((k_ptc_wgrad<PIN, 1, 2>), grid, dim3(PTC_BS), 0, st, k); \
-  else hipLaunchKernelGGL((k_ptc_wgrad<PIN, 2, 1>), grid, dim3(PTC_BS), 0, st, k);
-  if (pin == WD_BF16) { WD_WG(WD_BF16) } else { WD_WG(WD_F32) }
-#undef WD_WG
+  const dim3 grid = ptc_grid(k.g, nsamp);
+  if (n->act == WD_BF16) hipLaunchKernelGGL((k_ptc_layer<WD_BF16, WD_F32, 2, 1, -1, true>), grid, dim3(PTC_BS), 0, st, k);
+  else hipLaunchKernelGGL((k_ptc_layer<WD_F32, WD_F32, 2, 1, -1, true>), grid, dim3(PTC_BS), 0, st, k);
+  return hip_check(hipGetLastError(), "ptc loss layer");
+}
+
+// Weight gradient of one layer over nsamp samples (k_ptc_wgrad): layer 1
+// transports its output gradient t, layer 0 its input t.
+static wd_status ptc_wgrad(const wd_ptc *n, int layer, const void *t, wd_prec pt, const void *f, wd_prec pf, int nsamp,
+                           unsigned nblk, bool accumulate, hipStream_t st) {
+  KWg k{};
+  k.g = n->g->geom;
+  k.links32 = (const char *)n->g->links32;
+  k.link_par = link_parity_bytes(k.g, false);
+  k.t = (const char *)t;
+  k.in_half = half_bytes(k.g, pt);
+  k.t_samp = 2 * k.in_half;
+  k.f = (const char *)f;
+  k.f_half = half_bytes(k.g, pf);
+  k.partials = n->partials + (size_t)layer * WG_BLOCKS * 576;
+  k.accumulate = accumulate;
+  k.nch = (k.g.vh + 63) / 64;
+  k.units = (long)nsamp * 2 * k.nch;
+  const dim3 grid(nblk), bs(PTC_BS);
+  if (layer == 1) {
+    if (pf == WD_BF16) hipLaunchKernelGGL((k_ptc_wgrad<WD_F32, WD_BF16, true>), grid, bs, 0, st, k);
+    else hipLaunchKernelGGL((k_ptc_wgrad<WD_F32, WD_F32, true>), grid, bs, 0, st, k);
+  } else {
+    if (pt == WD_BF16) hipLaunchKernelGGL((k_ptc_wgrad<WD_BF16, WD_F32, false>), grid, bs, 0, st, k);
+    else hipLaunchKernelGGL((k_ptc_wgrad<WD_F32, WD_F32, false>), grid, bs, 0, st, k);
+  }
   return hip_check(hipGetLastError(), "ptc wgrad");
 }
 
@@ -1372,69 +1536,94 @@ wd_status ptc_apply(const wd_ptc *n, const void *in, void *out, hipStream_t st) 
   return WD_OK;
 }
 
+// Samples per launch of the training kernels: 2^19 sites fill the device
+// (8192 waves of 64 sites), and the workspace is bounded by them.  One sample
+// of 16^4 at a time left one block on a CU: loss and gradient of 8 pairs took
+// 2.00 ms, together 0.58 ms.
+static int train_samples(const Geom &G) { return (int)std::max<long>(1, (1L << 19) / (2L * G.vpad)); }
+static size_t loss_parts(const Geom &G, int nsamp) { return (size_t)(G.vpad / PTC_BS) * 2 * (size_t)nsamp; }
+
 static wd_status ptc_alloc(wd_ptc *n) {
   const Geom &G = n->g->geom;
-  const size_t fa = 2 * half_bytes(G, n->act), f32 = 2 * half_bytes(G, WD_F32);
-  n->nblk = (int)((G.vpad + PTC_BS - 1) / PTC_BS) * 2;
+  const size_t fa = 2 * half_bytes(G, n->act);
   WD_HIP(hipMalloc(&n->W, PTC_NW * sizeof(float)));
   WD_HIP(hipMalloc(&n->Wc, PTC_NW * sizeof(float)));
   WD_HIP(hipMalloc(&n->gradc, PTC_NW * sizeof(float)));
-  WD_HIP(hipMalloc(&n->Wadj, PTC_NW * sizeof(float)));
-  WD_HIP(hipMalloc(&n->grad, PTC_NW * sizeof(float)));
+  WD_HIP(hipMalloc(&n->Wadj, PTC_NW / 2 * sizeof(float)));
   WD_HIP(hipMalloc(&n->m, PTC_NW * sizeof(float)));
   WD_HIP(hipMalloc(&n->v, PTC_NW * sizeof(float)));
   WD_HIP(hipMemset(n->m, 0, PTC_NW * sizeof(float)));
   WD_HIP(hipMemset(n->v, 0, PTC_NW * sizeof(float)));
   WD_HIP(hipMalloc(&n->x0, fa));
   WD_HIP(hipMalloc(&n->y1, 2 * fa));
-  WD_HIP(hipMalloc(&n->y2, f32));
-  WD_HIP(hipMalloc(&n->gy2, f32));
-  WD_HIP(hipMalloc(&n->gy1, 2 * f32));
-  WD_HIP(hipMalloc(&n->partials, (size_t)2 * n->nblk * 576 * sizeof(double)));
-  WD_HIP(hipMalloc(&n->scal, (size_t)(n->nblk + 64) * sizeof(double)));
+  WD_HIP(hipMalloc(&n->partials, (size_t)2 * WG_BLOCKS * 576 * sizeof(double)));
+  WD_HIP(hipMalloc(&n->scal, (size_t)(64 + loss_parts(G, train_samples(G))) * sizeof(double)));
   WD_HIP(hipMalloc(&n->tabs, PTC_B_TABS * sizeof(v4u)));
   return WD_OK;
 }
 
+// Training buffers for up to `want` samples at once: bytes of one sample's
+// input, hidden layer, output gradient and hidden gradient.
+static size_t train_sample_bytes(const wd_ptc *n) {
+  const size_t fa = 2 * half_bytes(n->g->geom, n->act), f32 = 2 * half_bytes(n->g->geom, WD_F32);
+  return (n->act == WD_F32 ? 0 : fa) + 2 * fa + 3 * f32;
+}
+// The samples that go through the kernels together: all of a batch that the
+// workspace holds.  Where memory is short it is halved down to one sample.
+static wd_status train_reserve(wd_ptc *n, int want) {
+  want = std::min(want, train_samples(n->g->geom));
+  if (n->tcap >= want) return WD_OK;
+  for (; want > n->tcap; want /= 2) {
+    char *p = nullptr;
+    if (hipMalloc(&p, want * train_sample_bytes(n)) == hipSuccess) {
+      if (n->tbuf) (void)hipFree(n->tbuf);
+      n->tbuf = p;
+      n->tcap = want;
+      return WD_OK;
+    }
+    (void)hipGetLastError();
+  }
+  return n->tcap > 0 ? WD_OK : set_error(WD_ERR_OOM, "ptc training buffers");
+}
+
 static void ptc_free(wd_ptc *n) {
-  void *ps[] = {n->Wc,  n->gradc, n->W,  n->Wadj,     n->grad, n->m,   n->v,       n->x0,  n->y1,    n->y2,
-                n->gy2, n->gy1,   n->partials, n->scal, n->links16, n->W16, n->hnorm, n->linksb, n->tabs};
+  void *ps[] = {n->Wc, n->gradc, n->W,    n->Wadj,    n->m,   n->v,     n->x0,     n->y1,
+                n->tbuf, n->partials, n->scal, n->links16, n->W16, n->hnorm, n->linksb, n->tabs};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   delete n;
 }
 
 // Loss and gradients of a batch of B normalised pairs (r_b, e_b), F32 full
-// fields, B of each, consecutive.  n->grad receives dL/dRe W + i dL/dIm W of
+// fields, B of each, consecutive.  n->gradc receives dL/dRe Wc + i dL/dIm Wc of
 // L = (1/B) sum_b |N(r_b) - e_b|^2; n->scal[0] receives L * B.
 static wd_status ptc_loss_grad(wd_ptc *n, const void *r, const void *e, int B, hipStream_t st) {
   const Geom &G = n->g->geom;
-  const size_t f32 = 2 * half_bytes(G, WD_F32);
-  WD_HIP(hipMemsetAsync(n->scal, 0, sizeof(double), st));
-  hipLaunchKernelGGL(k_ptc_adjoint, dim3(1), dim3(64), 0, st, (const float *)n->W, n->Wadj, 2, 1);
-  hipLaunchKernelGGL(k_ptc_adjoint, dim3(1), dim3(64), 0, st, (const float *)(n->W + 576), n->Wadj + 576, 1, 2);
+  const size_t fa = 2 * half_bytes(G, n->act), f32 = 2 * half_bytes(G, WD_F32);
+  WD_TRY(train_reserve(n, B));
+  const int S = std::min(B, n->tcap);  // samples per launch
+  char *gy2 = n->tbuf, *gy1 = gy2 + S * f32, *y1 = gy1 + 2 * S * f32, *x0 = y1 + 2 * S * fa;
+  const long units = (long)S * 2 * ((G.vh + 63) / 64);
+  const unsigned nblk = (unsigned)std::min<long>((units + PTC_BS / 64 - 1) / (PTC_BS / 64), WG_BLOCKS);
+  hipLaunchKernelGGL(k_ptc_adjoint, dim3(1), dim3(64), 0, st, (const float *)(n->W + 576), n->Wadj, 1, 2);
   WD_HIP(hipGetLastError());
-  for (int b = 0; b < B; ++b) {
-    const char *rb = (const char *)r + (size_t)b * f32;
-    const char *eb = (const char *)e + (size_t)b * f32;
-    WD_TRY(blas_convert(G, WD_F32, vref(rb, 2), n->act, vref(n->x0, 2), 1.0, nullptr, 1, st));
-    WD_TRY(ptc_layer(n, n->W, n->x0, n->act, 1, n->y1, n->act, 2, st));
-    WD_TRY(ptc_layer(n, n->W + 576, n->y1, n->act, 2, n->y2, WD_F32, 1, st));
-    hipLaunchKernelGGL(k_ptc_loss, ptc_grid(G), dim3(256), 0, st, (const char *)n->y2, eb, (char *)n->gy2, G,
-                       2.0f / (float)B, n->scal + 64);
-    WD_HIP(hipGetLastError());
-    WD_TRY(launch_finish_sums(n->scal + 64, (unsigned)n->nblk, 1, n->scal, 1, 1, nullptr, 1, st));
-    WD_TRY(ptc_wgrad(n, 1, n->y1, n->act, n->gy2, b > 0, st));
+  for (int b = 0; b < B; b += S) {
+    const int ns = std::min(S, B - b);
+    const void *rb = (const char *)r + (size_t)b * f32;
+    const void *eb = (const char *)e + (size_t)b * f32;
+    if (n->act != WD_F32) {
+      WD_TRY(blas_convert(G, WD_F32, vref(rb, 2, f32), n->act, vref(x0, 2, fa), 1.0, nullptr, ns, st));
+      rb = x0;
+    }
+    WD_TRY(ptc_layer(n, n->W, rb, n->act, 1, y1, n->act, 2, st, ns));
+    WD_TRY(ptc_loss_layer(n, y1, eb, gy2, 2.0f / (float)B, ns, b > 0, st));
+    WD_TRY(ptc_wgrad(n, 1, gy2, WD_F32, y1, n->act, ns, nblk, b > 0, st));
     // input gradient of layer 2 (adjoint weights: 1 -> 2 channels)
-    WD_TRY(ptc_layer(n, n->Wadj + 576, n->gy2, WD_F32, 1, n->gy1, WD_F32, 2, st));
-    WD_TRY(ptc_wgrad(n, 0, n->x0, n->act, n->gy1, b > 0, st));
+    WD_TRY(ptc_layer(n, n->Wadj, gy2, WD_F32, 1, gy1, WD_F32, 2, st, ns));
+    WD_TRY(ptc_wgrad(n, 0, rb, n->act, gy1, WD_F32, ns, nblk, b > 0, st));
   }
-  hipLaunchKernelGGL(k_ptc_reduce, dim3((576 + 255) / 256), dim3(256), 0, st, (const double *)n->partials, n->nblk,
-                     576, n->grad);
-  hipLaunchKernelGGL(k_ptc_reduce, dim3((576 + 255) / 256), dim3(256), 0, st,
-                     (const double *)(n->partials + (size_t)n->nblk * 576), n->nblk, 576, n->grad + 576);
-  // gradient with respect to the chiral-basis parameters (W = S Wc S, S orthogonal and symmetric)
-  hipLaunchKernelGGL(k_ptc_rotate, dim3(1), dim3(128), 0, st, (const float *)n->grad, n->gradc, PTC_NW / 32);
+  hipLaunchKernelGGL(k_ptc_grad, dim3(PTC_NW / 32 + 1), dim3(GRAD_BS), 0, st, (const double *)n->partials, (int)nblk,
+                     (const double *)(n->scal + 64), (int)loss_parts(G, S), n->gradc, n->scal);
   return hip_check(hipGetLastError(), "ptc loss/grad");
 }
 
