@@ -266,7 +266,7 @@ typedef struct {
   int batch_tile;        /* wd_solve_batch: slots per tile and workgroup,    */
                          /* 64, 128 or 256 (0 = 256)                         */
   int batch_blocks_per_cu; /* wd_solve_batch: persistent workgroups per CU   */
-                         /* (0 = as many as fit, -1 = one per tile)          */
+                         /* (0 and -1 = one workgroup per tile)              */
 } wd_solve_params;
 
 typedef struct {
@@ -517,7 +517,7 @@ wd_status wd_solve_batch(const wd_gauge *const *gs, int n, const void *const *b,
 
 /* Tune wd_solve_batch for these lattices: the slots per tile and workgroup
  * (params->batch_tile: 256, 128, 64) and the persistent workgroups per CU
- * (params->batch_blocks_per_cu: as many as fit, 1, 2, 4, 8, or one per tile).
+ * (params->batch_blocks_per_cu: one per tile, 1, 2, 4 or 8).
  * Each candidate solves the batch (gs, b, x, kappa, tol and params as for
  * wd_solve_batch; x is overwritten) once to warm up and twice timed; only
  * candidates whose every lattice reaches tol count, and the fastest wall time

@@ -1,19 +1,27 @@
 // Persistent multi-lattice solver: one launch covers every lattice of a batch.
 //
-// The lattices' half fields are cut into tiles of 64, 128 or 256 slots
-// (one tile per workgroup); a work list maps each tile to its lattice.  A
-// grid of (#CU x resident blocks, or a tuned number of blocks per CU)
-// workgroups walks the list; each tile reads its lattice's descriptor
+// The lattices' half fields are cut into groups of 256 slots, and for the hop
+// into tiles of 64, 128 or 256 slots (one tile per workgroup); a work list
+// maps each group to its lattice.  Each tile reads its lattice's descriptor
 // (geometry, links, vector pointers, kappa, CG scalars), so lattices of any
 // size share every launch.  Reductions are segmented by lattice: each tile
-// stores its block partial, and a finishing kernel (one workgroup per
-// lattice) sums that lattice's partials in tile order, so results do not
-// depend on scheduling and no block waits on a shared counter.  A lattice
-// whose CG has converged is masked: its tiles are skipped.  One pair of CG iterations over the whole batch is
-// captured in a hipGraph and replayed; the host polls the per-lattice flags
-// every few replays.  Outer loop: FP64 defect correction per lattice (true
-// residual, solution accumulation and norms in FP64; inner CG in FP32
-// arithmetic with the chosen storage precision).
+// stores its block partial, and the kernel that needs the sum adds up that
+// lattice's partials in a fixed order (or, where a lattice has more than
+// BATCH_PARTS of them, a finishing kernel does, one workgroup per lattice), so
+// results do not depend on scheduling and no block waits on a shared counter.
+// A lattice whose CG has converged is masked: its tiles are skipped.  One pair
+// of CG iterations over the whole batch (six launches each) is captured in a
+// hipGraph and replayed; the host polls the per-lattice flags every few
+// replays.  Outer loop: FP64 defect correction per lattice (true residual,
+// solution accumulation and norms in FP64; inner CG in FP32 arithmetic with
+// the chosen storage precision).
+//
+// Hop: one thread per site.  (One wave per hop direction on 64 slots a block,
+// the faster form for one lattice, loses here: each block starts with a chain
+// of reads, list, descriptor, mask, that 64 sites do not hide.  The eight
+// lattices of 8^4 to 20^3x40 in BF16 took 26.7 ms with it, 23.0 without.)
+// Bound by the FP32 links: 528 bytes a site in BF16, 21 us a hop over all eight
+// lattices, 8.6 TB/s from the memory-side cache.
 #include <math.h>
 #include <string.h>
 
@@ -27,7 +35,11 @@
 
 namespace wd {
 
-constexpr int BT = 256;  // threads of the finishing kernels; largest tile
+constexpr int BT = 256;  // slots of a group; threads of the elementwise and finishing kernels
+// Most partial sums of one lattice that the consumers add up themselves (the
+// line of one lattice's solver).  Four finishing launches an iteration less for
+// 1.5 us in each of two consumers (625 partials at most): 23.7 -> 23.0 ms.
+constexpr int BATCH_PARTS = (int)CONSUMER_PARTS;
 
 // vector slots of a lattice
 enum Slot { S_B = 0, S_X, S_R64, S_RH, S_E, S_P, S_S, S_R, S_Q, S_T, NSLOT };
@@ -36,7 +48,7 @@ struct LatDesc {
   Geom g;
   const char *links64, *links32;
   size_t lpar64, lpar32;  // link bytes per parity
-  int tile0, ntiles;      // tiles per half field, first tile in the work list
+  int grp0, ngrp;         // first group in the work list, groups per half field
   double kappa;
   char *vec[NSLOT];
   CgScalars *sc;
@@ -53,8 +65,10 @@ struct Opnd {
 
 struct KBatch {
   const LatDesc *desc;
-  const int *tile_lat;
-  int ntiles;           // total tiles (per half field) over the batch
+  const int *grp_lat;   // lattice of each group
+  int ngrp;             // total groups (per half field) over the batch
+  int tpg;              // hop tiles per group
+  int fused;            // the consumers add up the partials
   // hop
   Opnd in, out, X, Y;
   int a_mode;           // 0: a = 1; 1: a = kappa; 2: a = -kappa^2; 3: a = -kappa
@@ -65,7 +79,8 @@ struct KBatch {
   int nhalf;            // elementwise ops: halves per vector
   double scale;
   int use_mask;         // skip lattices whose CG is done
-  double *partials;     // per work item
+  double *partials;     // per hop tile, or elementwise work item
+  double *ss_parts;     // per group: |s|^2 of the CG update
 };
 
 __device__ __forceinline__ char *vec_ptr(const LatDesc &d, Opnd o, int P) {
@@ -80,23 +95,28 @@ __device__ __forceinline__ void seg_store(double v, int w, double *partials) {
 }
 
 // ------------------------------------------------------------------ hop
+template <int P, int EPI>
+__device__ __forceinline__ KDslash batch_dslash(const KBatch &a, const LatDesc &d) {
+  KDslash k{};
+  k.g = d.g;
+  k.links = (P == WD_F64) ? d.links64 + (size_t)a.parity * d.lpar64 : d.links32 + (size_t)a.parity * d.lpar32;
+  k.parity = a.parity;
+  k.in = vec_ptr(d, a.in, P);
+  k.out = vec_ptr(d, a.out, P);
+  if constexpr (EPI >= 1) k.X = vec_ptr(d, a.X, P);
+  if constexpr (EPI == 2) k.Y = vec_ptr(d, a.Y, P);
+  k.a = a.a_mode == 0 ? 1.0 : a.a_mode == 1 ? d.kappa : a.a_mode == 2 ? -d.kappa * d.kappa : -d.kappa;
+  k.nt_store = 1;
+  return k;
+}
+
 template <int P, bool DAG, int EPI, bool NORM, int TB>
 __global__ __launch_bounds__(TB) void k_batch_hop(KBatch a) {
-  for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int l = a.tile_lat[t];
-    const LatDesc &d = a.desc[l];
+  for (int t = blockIdx.x; t < a.ngrp * a.tpg; t += gridDim.x) {
+    const LatDesc &d = a.desc[a.grp_lat[t / (BT / TB)]];
     if (a.use_mask && d.sc->done) continue;
-    KDslash k{};
-    k.g = d.g;
-    k.links = (P == WD_F64) ? d.links64 + (size_t)a.parity * d.lpar64 : d.links32 + (size_t)a.parity * d.lpar32;
-    k.parity = a.parity;
-    k.in = vec_ptr(d, a.in, P);
-    k.out = vec_ptr(d, a.out, P);
-    if constexpr (EPI >= 1) k.X = vec_ptr(d, a.X, P);
-    if constexpr (EPI == 2) k.Y = vec_ptr(d, a.Y, P);
-    k.a = a.a_mode == 0 ? 1.0 : a.a_mode == 1 ? d.kappa : a.a_mode == 2 ? -d.kappa * d.kappa : -d.kappa;
-    k.nt_store = 1;
-    const int i = (t - d.tile0) * TB + (int)threadIdx.x;
+    const KDslash k = batch_dslash<P, EPI>(a, d);
+    const int i = (t - d.grp0 * (BT / TB)) * TB + (int)threadIdx.x;
     const double nrm = dslash_site<P, DAG, EPI, NORM>(k, i);
     if constexpr (NORM) seg_store(nrm, t, a.partials);
   }
@@ -105,24 +125,33 @@ __global__ __launch_bounds__(TB) void k_batch_hop(KBatch a) {
 // ------------------------------------------------------------ elementwise
 enum BOp { OP_CGU = 0, OP_PUP, OP_CONV, OP_ACC, OP_NORM };
 
-// Work item w = h * ntiles + t covers the TS slots of tile t in half h.
-template <int OP, int PA, int PB, int TS>
-__global__ __launch_bounds__(TS) void k_batch_elem(KBatch a) {
+// Work item w = h * ngrp + t covers the slots of group t in half h.
+template <int OP, int PA, int PB>
+__global__ __launch_bounds__(BT) void k_batch_elem(KBatch a) {
   using TA = typename Spinor<PA>::real;
   using TB = typename Spinor<PB>::real;
-  const int nitems_total = a.ntiles * a.nhalf;
+  const int nitems_total = a.ngrp * a.nhalf;
   for (int w = blockIdx.x; w < nitems_total; w += gridDim.x) {
-    const int t = w % a.ntiles, h = w / a.ntiles;
-    const int l = a.tile_lat[t];
-    const LatDesc &d = a.desc[l];
+    const int t = w % a.ngrp, h = w / a.ngrp;
+    const LatDesc &d = a.desc[a.grp_lat[t]];
     CgScalars *sc = d.sc;
-    if (a.use_mask && sc->done) continue;
-    const int i = (t - d.tile0) * TS + (int)threadIdx.x;
+    // The CG update notes the mask for the p update, whose own launch changes
+    // `done`: a block that sees it change between its waves would lose count
+    // of the barriers below.
+    if constexpr (OP == OP_PUP) {
+      if (!sc->live) continue;
+    } else {
+      if (OP == OP_CGU && t == d.grp0 && threadIdx.x == 0) sc->live = sc->done == 0;
+      if (a.use_mask && sc->done) continue;
+    }
+    const int i = (t - d.grp0) * BT + (int)threadIdx.x;
     double acc = 0.0;
     if constexpr (OP == OP_CGU) {
       // X(PA) += alpha P(PB); S(PB) -= alpha Q(PB); |S|^2
-      const double qq = sc->qq, rr = sc->rr[a.j];
+      const double qq = a.fused ? sum_partials(a.partials + d.grp0 * a.tpg, d.ngrp * a.tpg) : sc->qq;
+      const double rr = sc->rr[a.j];
       const bool ok = (qq > 0.0) && (qq < 1e300) && (rr < 1e300);
+      if (a.fused && t == d.grp0 && threadIdx.x == 0) sc->qq = qq;
       if (ok && i < d.g.vh) {
         const double alpha = rr / qq;
         cplx<TA> x[12];
@@ -148,12 +177,30 @@ __global__ __launch_bounds__(TS) void k_batch_elem(KBatch a) {
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc += (double)s[c].re * s[c].re + (double)s[c].im * s[c].im;
       }
-      // every tile of the lattice stores a partial; the sum and then the
-      // flags (k_batch_flags) follow in their own launches
-      seg_store(acc, t, a.partials);
+      // every group of the lattice stores a partial
+      seg_store(acc, t, a.ss_parts);
     } else if constexpr (OP == OP_PUP) {
+      const double rrn = a.fused ? sum_partials(a.partials + d.grp0 * a.tpg, d.ngrp * a.tpg) : sc->rr[1 - a.j];
+      if (t == d.grp0) {
+        // The lattice's first group also ends its iteration: |s|^2, iteration
+        // count, convergence.  Breakdown (|M p|^2 not positive, or a
+        // non-finite scalar) ends that lattice's CG.
+        const double ss = sum_partials(a.ss_parts + d.grp0, d.ngrp);
+        if (threadIdx.x == 0) {
+          const double qq = sc->qq, rr = sc->rr[a.j];
+          sc->rr[1 - a.j] = rrn;
+          sc->ss = ss;
+          if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
+            sc->done = 2;
+          } else {
+            sc->iters += 1;
+            if (ss <= sc->stop2) sc->done = 1;
+            else if (sc->iters >= sc->max_iters) sc->done = 3;
+          }
+        }
+      }
       if (i < d.g.vh) {
-        const TB beta = (TB)(sc->rr[1 - a.j] / sc->rr[a.j]);
+        const TB beta = (TB)(rrn / sc->rr[a.j]);
         cplx<TB> r[12], p[12];
         char *Pp = vec_ptr(d, Opnd{S_P, 0}, PB);
         Spinor<PB>::load(vec_ptr(d, Opnd{S_R, 0}, PB), i, r);
@@ -210,49 +257,35 @@ __global__ __launch_bounds__(TS) void k_batch_elem(KBatch a) {
 
 // Per-lattice sums of the block partials, in work-item order (one workgroup
 // per lattice).  mode 0: hop norm (items = the lattice's tiles) into
-// sc[norm_field] (+= with norm_accumulate); 1: CG update, |s|^2 into ss;
-// 2: norm over nhalf halves (items h * ntiles + tile) into sc[norm_field].
-// Masked lattices (done) stored no partials and are left alone.
+// sc[norm_field] (+= with norm_accumulate); 2: norm over nhalf halves (items
+// h * ngrp + group) into sc[norm_field].  Masked lattices (done) stored no
+// partials and are left alone.
 __global__ __launch_bounds__(BT) void k_batch_finish(KBatch a, int mode) {
   const int l = blockIdx.x;
   const LatDesc &d = a.desc[l];
   CgScalars *sc = d.sc;
   if (a.use_mask && sc->done) return;
-  const int t0 = d.tile0, nt = d.ntiles, NT = a.ntiles;
+  const int tpg = (mode == 2) ? 1 : a.tpg;
+  const int t0 = d.grp0 * tpg, nt = d.ngrp * tpg, NT = a.ngrp * tpg;
   const int nitems = (mode == 2) ? nt * a.nhalf : nt;
   double v[1] = {0.0};
   for (int q = threadIdx.x; q < nitems; q += BT) v[0] += a.partials[(q / nt) * NT + t0 + (q % nt)];
   block_sum_n<1>(v);
   if (threadIdx.x != 0) return;
-  double *dst = (mode == 1) ? &sc->ss : (double *)sc + a.norm_field;
+  double *dst = (double *)sc + a.norm_field;
   *dst = (mode == 0 && a.norm_accumulate) ? (*dst + v[0]) : v[0];
-}
-
-// Convergence flags after a CG update: one thread per lattice.  Breakdown
-// (|M p|^2 not positive, or a non-finite scalar) ends that lattice's CG.
-__global__ void k_batch_flags(const LatDesc *desc, int n, int j) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= n) return;
-  CgScalars *sc = desc[l].sc;
-  if (sc->done) return;
-  const double qq = sc->qq, rr = sc->rr[j];
-  if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
-    sc->done = 2;
-    return;
-  }
-  sc->iters += 1;
-  if (sc->ss <= sc->stop2) sc->done = 1;
-  else if (sc->iters >= sc->max_iters) sc->done = 3;
 }
 
 // ============================================================ host side
 struct BatchRun {
   int n = 0;
-  int ntiles = 0;
-  int grid = 0;
-  int tb = 256;  // slots per tile = threads per workgroup
+  int ngrp = 0;
+  int grid = 0;   // blocks of the hop
+  int egrid = 0;  // blocks of the elementwise kernels over one half (0: one per group)
+  int tb = 256;   // slots per hop tile
+  bool fused = true;
   LatDesc *d_desc = nullptr;
-  int *d_tile_lat = nullptr;
+  int *d_grp_lat = nullptr;  // lattice of each group
   CgScalars *d_sc = nullptr;
   CgScalars *h_sc = nullptr;  // pinned
   double *partials = nullptr;
@@ -262,7 +295,7 @@ struct BatchRun {
   wd_prec S;
   ~BatchRun() {
     if (d_desc) (void)hipFree(d_desc);
-    if (d_tile_lat) (void)hipFree(d_tile_lat);
+    if (d_grp_lat) (void)hipFree(d_grp_lat);
     if (d_sc) (void)hipFree(d_sc);
     if (h_sc) (void)hipHostFree(h_sc);
     if (partials) (void)hipFree(partials);
@@ -273,11 +306,14 @@ struct BatchRun {
 static KBatch kb(const BatchRun &R) {
   KBatch a{};
   a.desc = R.d_desc;
-  a.tile_lat = R.d_tile_lat;
-  a.ntiles = R.ntiles;
+  a.grp_lat = R.d_grp_lat;
+  a.ngrp = R.ngrp;
+  a.tpg = BT / R.tb;
+  a.fused = R.fused;
   a.in = a.out = a.X = a.Y = Opnd{-1, 0};
   a.norm_field = -1;
-  a.partials = R.partials;
+  a.ss_parts = R.partials;
+  a.partials = R.partials + R.ngrp;
   a.nhalf = 1;
   a.use_mask = 1;
   return a;
@@ -285,49 +321,42 @@ static KBatch kb(const BatchRun &R) {
 
 #define SC_FIELD(f) ((int)(offsetof(CgScalars, f) / sizeof(double)))
 
-template <int P, int TB>
-static void hop_launch_tb(const BatchRun &R, const KBatch &a, bool dag, int epi, bool norm) {
-  dim3 g(R.grid), b(TB);
-#define WD_BH(D, E, N) \
-  if (dag == D && epi == E && norm == N) hipLaunchKernelGGL((k_batch_hop<P, D, E, N, TB>), g, b, 0, R.st, a);
+template <int P>
+static void hop_launch(const BatchRun &R, const KBatch &a, bool dag, int epi, bool norm) {
+  const dim3 g((unsigned)R.grid);
+#define WD_BH(D, E, N)                                                                                   \
+  if (dag == D && epi == E && norm == N) {                                                               \
+    if (R.tb == 64) hipLaunchKernelGGL((k_batch_hop<P, D, E, N, 64>), g, dim3(64), 0, R.st, a);          \
+    else if (R.tb == 128) hipLaunchKernelGGL((k_batch_hop<P, D, E, N, 128>), g, dim3(128), 0, R.st, a);  \
+    else hipLaunchKernelGGL((k_batch_hop<P, D, E, N, 256>), g, dim3(256), 0, R.st, a);                   \
+  }
   WD_BH(false, 0, false) WD_BH(false, 1, false) WD_BH(false, 1, true) WD_BH(false, 2, true)
   WD_BH(true, 0, false) WD_BH(true, 1, true)
 #undef WD_BH
 }
 
-template <int P>
-static void hop_launch(const BatchRun &R, const KBatch &a, bool dag, int epi, bool norm) {
-  if (R.tb == 64) hop_launch_tb<P, 64>(R, a, dag, epi, norm);
-  else if (R.tb == 128) hop_launch_tb<P, 128>(R, a, dag, epi, norm);
-  else hop_launch_tb<P, 256>(R, a, dag, epi, norm);
-}
-
-static void hop_any(const BatchRun &R, wd_prec P, const KBatch &a, bool dag, int epi, bool norm) {
+// consumed: the kernel after it adds up the norm's partials
+static void hop_any(const BatchRun &R, wd_prec P, const KBatch &a, bool dag, int epi, bool norm,
+                    bool consumed = false) {
   switch (P) {
     case WD_F64: hop_launch<WD_F64>(R, a, dag, epi, norm); break;
     case WD_F32: hop_launch<WD_F32>(R, a, dag, epi, norm); break;
     case WD_F16: hop_launch<WD_F16>(R, a, dag, epi, norm); break;
     case WD_BF16: hop_launch<WD_BF16>(R, a, dag, epi, norm); break;
   }
-  if (norm) hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)R.n), dim3(BT), 0, R.st, a, 0);
-}
-
-template <int OP, int PA, int TB>
-static void elem_pb_tb(const BatchRun &R, const KBatch &a, wd_prec pb) {
-  dim3 g(R.grid), b(TB);
-  switch (pb) {
-    case WD_F64: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F64, TB>), g, b, 0, R.st, a); break;
-    case WD_F32: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F32, TB>), g, b, 0, R.st, a); break;
-    case WD_F16: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F16, TB>), g, b, 0, R.st, a); break;
-    case WD_BF16: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_BF16, TB>), g, b, 0, R.st, a); break;
-  }
+  if (norm && !(consumed && R.fused))
+    hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)R.n), dim3(BT), 0, R.st, a, 0);
 }
 
 template <int OP, int PA>
 static void elem_pb(const BatchRun &R, const KBatch &a, wd_prec pb) {
-  if (R.tb == 64) elem_pb_tb<OP, PA, 64>(R, a, pb);
-  else if (R.tb == 128) elem_pb_tb<OP, PA, 128>(R, a, pb);
-  else elem_pb_tb<OP, PA, 256>(R, a, pb);
+  const dim3 g((unsigned)(R.egrid > 0 ? R.egrid : R.ngrp * a.nhalf)), b(BT);
+  switch (pb) {
+    case WD_F64: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F64>), g, b, 0, R.st, a); break;
+    case WD_F32: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F32>), g, b, 0, R.st, a); break;
+    case WD_F16: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_F16>), g, b, 0, R.st, a); break;
+    case WD_BF16: hipLaunchKernelGGL((k_batch_elem<OP, PA, WD_BF16>), g, b, 0, R.st, a); break;
+  }
 }
 
 template <int OP>
@@ -338,8 +367,7 @@ static void elem(const BatchRun &R, const KBatch &a, wd_prec pa, wd_prec pb) {
     case WD_F16: elem_pb<OP, WD_F16>(R, a, pb); break;
     case WD_BF16: elem_pb<OP, WD_BF16>(R, a, pb); break;
   }
-  if (OP == OP_CGU || OP == OP_NORM)
-    hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)R.n), dim3(BT), 0, R.st, a, OP == OP_CGU ? 1 : 2);
+  if (OP == OP_NORM) hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)R.n), dim3(BT), 0, R.st, a, 2);
 }
 
 // one CG iteration of every unconverged lattice (CGLS on the Schur operator)
@@ -351,12 +379,11 @@ static void batch_cg_iteration(const BatchRun &R, int j) {
   hop_any(R, S, a, false, 0, false);
   a = kb(R);
   a.in = {S_T, 0}; a.out = {S_Q, 0}; a.X = {S_P, 0}; a.parity = 0; a.a_mode = 2; a.norm_field = SC_FIELD(qq);
-  hop_any(R, S, a, false, 1, true);
-  // x += alpha p ; s -= alpha q  (-> ss), then flags
+  hop_any(R, S, a, false, 1, true, true);
+  // x += alpha p ; s -= alpha q  (-> ss)
   a = kb(R);
   a.j = j;
   elem<OP_CGU>(R, a, WD_F32, S);
-  hipLaunchKernelGGL(k_batch_flags, dim3((R.n + 63) / 64), dim3(64), 0, R.st, (const LatDesc *)R.d_desc, R.n, j);
   // t = H^dag_oe s ; r = s - k^2 H^dag_eo t  (-> rr[1-j])
   a = kb(R);
   a.in = {S_S, 0}; a.out = {S_T, 0}; a.parity = 1; a.a_mode = 0;
@@ -364,8 +391,8 @@ static void batch_cg_iteration(const BatchRun &R, int j) {
   a = kb(R);
   a.in = {S_T, 0}; a.out = {S_R, 0}; a.X = {S_S, 0}; a.parity = 0; a.a_mode = 2;
   a.norm_field = SC_FIELD(rr) + (1 - j);
-  hop_any(R, S, a, true, 1, true);
-  // p = r + beta p
+  hop_any(R, S, a, true, 1, true, true);
+  // p = r + beta p, and the end of the iteration
   a = kb(R);
   a.j = j;
   elem<OP_PUP>(R, a, WD_F32, S);
@@ -377,7 +404,7 @@ wd_status solve_batch(const wd_gauge *const *gs, int n, const void *const *b, vo
   BatchRun R;
   R.n = n;
   R.S = prm.inner_prec;
-  R.tb = prm.batch_tile ? prm.batch_tile : 256;
+  R.tb = prm.batch_tile ? prm.batch_tile : BT;
   const wd_prec S = R.S;
   R.st = gs[0]->own_stream;
   // events: wait for every caller stream
@@ -390,7 +417,7 @@ wd_status solve_batch(const wd_gauge *const *gs, int n, const void *const *b, vo
   }
   // descriptors and vector storage
   R.desc.resize(n);
-  std::vector<int> tile_lat;
+  std::vector<int> grp_lat;
   size_t vec_bytes = 0;
   std::vector<size_t> off(n);
   for (int l = 0; l < n; ++l) {
@@ -405,18 +432,19 @@ wd_status solve_batch(const wd_gauge *const *gs, int n, const void *const *b, vo
     d.links32 = (const char *)gs[l]->links32;
     d.lpar64 = link_parity_bytes(G, true);
     d.lpar32 = link_parity_bytes(G, false);
-    d.ntiles = G.vpad / R.tb;
-    d.tile0 = (int)tile_lat.size();
+    d.ngrp = G.vpad / BT;
+    d.grp0 = (int)grp_lat.size();
     d.kappa = kappa[l];
-    for (int q = 0; q < d.ntiles; ++q) tile_lat.push_back(l);
+    grp_lat.insert(grp_lat.end(), (size_t)d.ngrp, l);
+    if (d.ngrp * (BT / R.tb) > BATCH_PARTS) R.fused = false;
   }
-  R.ntiles = (int)tile_lat.size();
+  R.ngrp = (int)grp_lat.size();
   WD_HIP(hipMalloc(&R.vecmem, vec_bytes));
   WD_HIP(hipMalloc(&R.d_desc, sizeof(LatDesc) * n));
-  WD_HIP(hipMalloc(&R.d_tile_lat, sizeof(int) * R.ntiles));
+  WD_HIP(hipMalloc(&R.d_grp_lat, sizeof(int) * grp_lat.size()));
   WD_HIP(hipMalloc(&R.d_sc, sizeof(CgScalars) * n));
   WD_HIP(hipHostMalloc((void **)&R.h_sc, sizeof(CgScalars) * n, hipHostMallocDefault));
-  WD_HIP(hipMalloc(&R.partials, sizeof(double) * 2 * R.ntiles));
+  WD_HIP(hipMalloc(&R.partials, sizeof(double) * (size_t)R.ngrp * (1 + std::max(2, BT / R.tb))));
   for (int l = 0; l < n; ++l) {
     LatDesc &d = R.desc[l];
     const Geom &G = d.g;
@@ -434,19 +462,19 @@ wd_status solve_batch(const wd_gauge *const *gs, int n, const void *const *b, vo
     d.sc = R.d_sc + l;
   }
   WD_HIP(hipMemcpyAsync(R.d_desc, R.desc.data(), sizeof(LatDesc) * n, hipMemcpyHostToDevice, R.st));
-  WD_HIP(hipMemcpyAsync(R.d_tile_lat, tile_lat.data(), sizeof(int) * R.ntiles, hipMemcpyHostToDevice, R.st));
-  // persistent grid: the resident blocks of the hop kernel on every CU, or
-  // batch_blocks_per_cu blocks per CU, or (-1) one block per tile
+  WD_HIP(hipMemcpyAsync(R.d_grp_lat, grp_lat.data(), sizeof(int) * grp_lat.size(), hipMemcpyHostToDevice, R.st));
+  // grid: one block per tile (the default, and -1), or batch_blocks_per_cu
+  // blocks per CU that walk the list.  As many as are resident, which every
+  // tuned number comes close to from below, took 19.0 ms for the eight lattices
+  // of 8^4 to 20^3x40 (BF16, inner 1e-2) against 18.5: the device refills a CU
+  // sooner than a block reaches its next descriptor.
   {
-    int dev, ncu = 0, per_cu = 0;
+    int dev, ncu = 0;
     WD_HIP(hipGetDevice(&dev));
     WD_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    const void *kern = R.tb == 64    ? (const void *)k_batch_hop<WD_F32, false, 1, true, 64>
-                       : R.tb == 128 ? (const void *)k_batch_hop<WD_F32, false, 1, true, 128>
-                                     : (const void *)k_batch_hop<WD_F32, false, 1, true, 256>;
-    WD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, R.tb, 0));
-    if (prm.batch_blocks_per_cu > 0) per_cu = prm.batch_blocks_per_cu;
-    R.grid = prm.batch_blocks_per_cu < 0 ? R.ntiles : std::max(1, std::min(R.ntiles, ncu * std::max(1, per_cu)));
+    const int bpc = prm.batch_blocks_per_cu, ntiles = R.ngrp * (BT / R.tb);
+    R.grid = bpc > 0 ? std::min(ntiles, ncu * bpc) : ntiles;
+    R.egrid = bpc > 0 ? std::min(R.ngrp, ncu * bpc) : 0;
   }
   auto sync_sc = [&]() -> wd_status {
     WD_HIP(hipMemcpyAsync(R.h_sc, R.d_sc, sizeof(CgScalars) * n, hipMemcpyDeviceToHost, R.st));

@@ -241,10 +241,7 @@ __device__ __forceinline__ bool cg_alpha(const KBlas &k, int sys, double &alpha)
     qq = sc->qq;
   }
   const double rr = sc->rr[k.j];
-  if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->done = 2;  // breakdown / non-finite
-    return false;
-  }
+  if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) return false;  // breakdown: the p update ends the CG
   alpha = rr / qq;
   return true;
 }
@@ -257,6 +254,7 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
   using TV = RealOf<PV>;
   using TX = RealOf<PX>;
   const int sys = blockIdx.y;
+  if (blockIdx.x == 0 && threadIdx.x == 0) k.sc[sys].live = k.sc[sys].done == 0;
   if (k.sc[sys].done) return;
   double alpha;
   if (!cg_alpha(k, sys, alpha)) return;
@@ -356,18 +354,25 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   using TV = RealOf<PV>;
   const int sys = blockIdx.y;
   CgScalars *sc = k.sc + sys;
-  if (sc->done) return;
+  // (not `done`, which block 0 changes: waves of one block that saw different
+  // values would add up different lists below)
+  if (!sc->live) return;
   double rrn;
   if (k.nparts) rrn = sum_partials(k.parts + (size_t)sys * k.nparts, k.nparts);
   else rrn = sc->rr[1 - k.j];
   if (blockIdx.x == 0) {
     const double ss = sum_partials(k.ss_parts + (size_t)sys * k.nss, k.nss);
     if (threadIdx.x == 0) {
+      const double qq = sc->qq, rr = sc->rr[k.j];
       if (k.nparts) sc->rr[1 - k.j] = rrn;
       sc->ss = ss;
-      sc->iters += 1;
-      if (ss <= sc->stop2) sc->done = 1;
-      else if (sc->iters >= sc->max_iters) sc->done = 3;
+      if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
+        sc->done = 2;  // breakdown / non-finite
+      } else {
+        sc->iters += 1;
+        if (ss <= sc->stop2) sc->done = 1;
+        else if (sc->iters >= sc->max_iters) sc->done = 3;
+      }
     }
     return;
   }

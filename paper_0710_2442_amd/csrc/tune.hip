@@ -668,13 +668,13 @@ extern "C" wd_status wd_tune_batch(const wd_gauge *const *gs, int n, const void 
     if (out_seconds) *out_seconds = us * 1e-6;
     return WD_OK;
   }
-  // candidates: tile size x persistent blocks per CU (0: as many as fit; -1: one block per tile);
+  // candidates: tile size x persistent blocks per CU (0: one block per tile);
   // each is run once to warm up and twice timed, and only solves that reach tol count
   std::vector<wd_solve_info> infos((size_t)n);
   double best = 1e30;
   int best_tile = 256, best_bpc = 0;
   for (int t : {256, 128, 64})
-    for (int c : {0, 1, 2, 4, 8, -1}) {
+    for (int c : {0, 1, 2, 4, 8}) {
       prm.batch_tile = t;
       prm.batch_blocks_per_cu = c;
       double sec = 1e30;

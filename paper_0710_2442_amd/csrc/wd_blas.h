@@ -19,7 +19,7 @@ struct CgScalars {
   int done;       // 0 running, 1 converged, 2 breakdown, 3 iteration cap
   int iters;
   int max_iters;
-  int pad;
+  int live;       // running when the CG update started (the p update's mask: its launch changes done)
 };
 
 // A vector operand: nhalf half fields starting at p; system y at p + y*sys_stride.

@@ -150,7 +150,9 @@ struct RedBuf {
   unsigned *nparts = nullptr;
 };
 // A consumer that adds up n partials in every block instead of waiting for a
-// finishing launch: see cgls_iteration for where the line lies.
+// finishing launch (3.5 us and a gap): 64 partials (FP64 CG on 8^3x16) 2.63 ->
+// 2.16 ms a solve, 5184 (BF16 defect correction on 24^3x48) 16.7 -> 17.6 ms, so
+// the line lies between.
 constexpr unsigned CONSUMER_PARTS = 2048;
 // true: leave the n partials to the consumer (the count is set); false: finish them
 inline bool leave_partials(const RedBuf &red, unsigned n) {
