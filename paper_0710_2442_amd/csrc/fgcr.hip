@@ -245,12 +245,17 @@ wd_status solve_fgcr(wd_gauge *g, const void *b, void *x, double kappa, double t
 //   rho = <w_k, r>       (one fused pass)
 //   alpha = rho / sigma_k,  e += alpha z_k,  r -= alpha w_k,  |r|^2 (one pass)
 // The basis is dropped after m directions (restart).  All coefficients stay
-// in device memory; the host reads |r|^2 once per iteration.
+// in device memory; a pass adds up the block partials of the pass before it
+// where they are few (FG_PARTS), and the host adds up those of |r|^2, which the
+// step writes to pinned memory.  The host queues the next direction before it
+// waits for |r|^2 unless convergence is near: a direction whose predecessor
+// turns out to have converged never enters the solution.
 
 namespace {
 
 constexpr int FG_MMAX = 16;
 constexpr int FG_BS = 256;
+constexpr int FG_BS_WAVES = FG_BS / 64;
 constexpr unsigned FG_MAX_BLOCKS = 2048;
 
 struct KFg {
@@ -264,11 +269,35 @@ struct KFg {
   double *dots;    // [2 FG_MMAX]: <w_j, w_k>
   double *sig;     // [FG_MMAX]: |w_j|^2
   double *rho;     // [2]: <w_k, r>
-  double *rr;      // |r|^2
+  double *rr_host; // [nblk]: block partials of |r|^2 (pinned host memory)
   float *alpha;    // [2 FG_MMAX]: the step lengths of the current cycle (re, im)
   int k;
   double *partials;
+  int sum_dots, sum_sig;  // the consumer adds up the partials of the dots / of sig and rho
 };
+
+// Most partials (over all lists) that each block of a consumer adds up; with
+// more, a finishing launch (2.5 us and a gap) does.  At 1536 (16^3x32, three
+// directions) the orthogonalisation takes 13.3 us instead of 12.2.
+constexpr unsigned FG_PARTS = 2048;
+
+// out[j] = sum of list j's n partials, in every block the same: wave w takes
+// lists w, w + 4, ...
+template <int NL>
+__device__ __forceinline__ void sum_lists(const double *p, unsigned n, double (&out)[NL]) {
+  __shared__ double red[NL];
+  const int lane = (int)threadIdx.x & 63;
+  for (int j = (int)threadIdx.x >> 6; j < NL; j += FG_BS_WAVES) {
+    double v = 0.0;
+#pragma unroll 4
+    for (unsigned b = lane; b < n; b += 64) v += p[(size_t)j * n + b];
+    v = wave_sum(v);
+    if (lane == 0) red[j] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NL; ++j) out[j] = red[j];
+}
 
 using F4 = Spinor<WD_F32>;
 
@@ -305,11 +334,20 @@ template <int S, int K>
 __global__ __launch_bounds__(FG_BS) void k_fg_orth(KFg a) {
   using V = Spinor<S>;
   cplx<float> c[K > 0 ? K : 1];
+  if constexpr (K > 0) {
+    double d[2 * K];
+    if (a.sum_dots) {
+      sum_lists<2 * K>(a.partials, a.nblk, d);
+    } else {
 #pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const double s = a.sig[j];
-    const double f = (s > 0.0) ? 1.0 / s : 0.0;
-    c[j] = {(float)(a.dots[2 * j] * f), (float)(a.dots[2 * j + 1] * f)};
+      for (int j = 0; j < 2 * K; ++j) d[j] = a.dots[j];
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const double s = a.sig[j];
+      const double f = (s > 0.0) ? 1.0 / s : 0.0;
+      c[j] = {(float)(d[2 * j] * f), (float)(d[2 * j + 1] * f)};
+    }
   }
   double acc[3] = {0.0, 0.0, 0.0};
   for (long i = (long)blockIdx.x * FG_BS + threadIdx.x; i < a.vh; i += (long)a.nblk * FG_BS) {
@@ -339,7 +377,7 @@ __global__ __launch_bounds__(FG_BS) void k_fg_orth(KFg a) {
     for (int q = 0; q < 12; ++q) acc[0] += (double)w[q].re * w[q].re + (double)w[q].im * w[q].im;
     site_dot(w, r, acc[1], acc[2]);
   }
-  block_sum_store<3>(acc, a.partials, a.nblk, blockIdx.x);
+  block_sum_store<3>(acc, a.partials + (size_t)2 * FG_MMAX * a.nblk, a.nblk, blockIdx.x);
 }
 
 // r -= alpha w_k, |r|^2; alpha_k is kept for the solution update, which is
@@ -347,9 +385,16 @@ __global__ __launch_bounds__(FG_BS) void k_fg_orth(KFg a) {
 template <int S>
 __global__ __launch_bounds__(FG_BS) void k_fg_step(KFg a) {
   using V = Spinor<S>;
-  const double s = a.sig[a.k];
+  double v[3];  // |w_k|^2, <w_k, r>
+  if (a.sum_sig) {
+    sum_lists<3>(a.partials + (size_t)2 * FG_MMAX * a.nblk, a.nblk, v);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sig[a.k] = v[0];
+  } else {
+    v[0] = a.sig[a.k], v[1] = a.rho[0], v[2] = a.rho[1];
+  }
+  const double s = v[0];
   const bool ok = s > 0.0 && s < 1e300;
-  const cplx<float> al = {ok ? (float)(a.rho[0] / s) : 0.f, ok ? (float)(a.rho[1] / s) : 0.f};
+  const cplx<float> al = {ok ? (float)(v[1] / s) : 0.f, ok ? (float)(v[2] / s) : 0.f};
   const cplx<float> ml = {-al.re, -al.im};
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.alpha[2 * a.k] = al.re;
@@ -367,7 +412,7 @@ __global__ __launch_bounds__(FG_BS) void k_fg_step(KFg a) {
 #pragma unroll
     for (int q = 0; q < 12; ++q) acc[0] += (double)r[q].re * r[q].re + (double)r[q].im * r[q].im;
   }
-  block_sum_store<1>(acc, a.partials, a.nblk, blockIdx.x);
+  block_sum_store<1>(acc, a.rr_host, a.nblk, blockIdx.x);
 }
 
 // e += sum_{j < K} alpha_j z_j for the K steps of a cycle, in step order
@@ -392,19 +437,19 @@ __global__ __launch_bounds__(FG_BS) void k_fg_accum(KFg a) {
   }
 }
 
-// Second stage of the three kernels above: value j = sum of the block
-// partials (block order) goes to dst[j] (dots, or rr), or for the
-// orthogonalisation to sig[k] (j = 0) and rho (j = 1, 2).
+// Second stage of the dots and the orthogonalisation where their partials are
+// many: value j = sum of the block partials (block order) goes to dots[j], or
+// to sig[k] (j = 0) and rho (j = 1, 2).
 constexpr int FG_FIN = 1024;
 __global__ __launch_bounds__(FG_FIN) void k_fg_finish(KFg a, int which) {
   const int j = blockIdx.x;
   double v[1] = {0.0};
-  for (unsigned b = threadIdx.x; b < a.nblk; b += FG_FIN) v[0] += a.partials[(size_t)j * a.nblk + b];
+  const double *p = a.partials + (size_t)(which == 0 ? j : 2 * FG_MMAX + j) * a.nblk;
+  for (unsigned b = threadIdx.x; b < a.nblk; b += FG_FIN) v[0] += p[b];
   block_sum_n<1>(v);
   if (threadIdx.x != 0) return;
   if (which == 0) a.dots[j] = v[0];
-  else if (which == 1) (j == 0 ? a.sig[a.k] : a.rho[j - 1]) = v[0];
-  else *a.rr = v[0];
+  else (j == 0 ? a.sig[a.k] : a.rho[j - 1]) = v[0];
 }
 
 template <int S, int K>
@@ -437,15 +482,16 @@ void launch_accum(const KFg &a, int K, hipStream_t st, std::integer_sequence<int
 // One FGCR direction after w_k = Mhat z_k: orthogonalise against the k
 // earlier directions, then the step; FP32 arithmetic on S-stored vectors.
 template <int S>
-void fg_direction(const KFg &a, int k, hipStream_t st) {
+void fg_direction(KFg &a, int k, hipStream_t st) {
+  a.sum_dots = 2 * k * a.nblk <= FG_PARTS;
+  a.sum_sig = 3 * a.nblk <= FG_PARTS;
   if (k > 0) {
     launch_dots<S>(a, k, st, std::make_integer_sequence<int, FG_MMAX - 1>{});
-    hipLaunchKernelGGL(k_fg_finish, dim3(2 * k), dim3(FG_FIN), 0, st, a, 0);
+    if (!a.sum_dots) hipLaunchKernelGGL(k_fg_finish, dim3(2 * k), dim3(FG_FIN), 0, st, a, 0);
   }
   launch_orth<S>(a, k, st, std::make_integer_sequence<int, FG_MMAX>{});
-  hipLaunchKernelGGL(k_fg_finish, dim3(3), dim3(FG_FIN), 0, st, a, 1);
+  if (!a.sum_sig) hipLaunchKernelGGL(k_fg_finish, dim3(3), dim3(FG_FIN), 0, st, a, 1);
   hipLaunchKernelGGL(k_fg_step<S>, dim3(a.nblk), dim3(FG_BS), 0, st, a);
-  hipLaunchKernelGGL(k_fg_finish, dim3(1), dim3(FG_FIN), 0, st, a, 2);
 }
 
 // out = Mhat in = in - kappa^2 H_eo H_oe in   (even half fields in precision
@@ -483,7 +529,7 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
   // step lengths) and the reduction partials.  Kept in the handle between solves (grown
   // when a solve needs more).
   const unsigned nblk = (unsigned)std::min<long>(std::max<long>(1, ((long)G.vh + FG_BS - 1) / FG_BS), FG_MAX_BLOCKS);
-  const size_t npart = std::max<size_t>((size_t)2 * FG_MMAX * nblk,
+  const size_t npart = std::max<size_t>((size_t)(2 * FG_MMAX + 3) * nblk,
                                         (size_t)2 * std::max<unsigned>(dslash_grid_blocks(g), BLAS_MAX_BLOCKS));
   const size_t vec_bytes = round_up(4 * h64 + 4 * h32 + (2 + 2 * (size_t)m) * hS, 256);
   const size_t scal_bytes = 1024;
@@ -502,8 +548,20 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
     }
     g->fg_bytes = need;
   }
-  if (!g->fg_host) WD_HIP(hipHostMalloc((void **)&g->fg_host, 64 * sizeof(double), hipHostMallocDefault));
+  // 64 doubles for copies, then two lists of block partials of |r|^2
+  if (!g->fg_host)
+    WD_HIP(hipHostMalloc((void **)&g->fg_host, (64 + 2 * FG_MAX_BLOCKS) * sizeof(double), hipHostMallocDefault));
   double *hres = g->fg_host;
+  double *rr_dev = nullptr;
+  WD_HIP(hipHostGetDevicePointer((void **)&rr_dev, hres + 64, 0));
+  struct Events {
+    hipEvent_t e[2] = {nullptr, nullptr};
+    ~Events() {
+      for (hipEvent_t v : e)
+        if (v) (void)hipEventDestroy(v);
+    }
+  } ev;
+  for (hipEvent_t &v : ev.e) WD_HIP(hipEventCreateWithFlags(&v, hipEventDisableTiming));
   char *red = (char *)g->fg_mem + vec_bytes;
   WD_HIP(hipMemsetAsync(red, 0, scal_bytes, st));
   char *c0 = (char *)g->fg_mem;
@@ -522,7 +580,7 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
   a.dots = ds;
   a.sig = ds + 2 * FG_MMAX;
   a.rho = a.sig + FG_MMAX;
-  a.rr = a.rho + 2;
+  double *const nrm = a.rho + 2;  // a norm that the host reads
   a.alpha = (float *)(red + 640);  // 2 FG_MMAX floats inside the scalar block
   static_assert(sizeof(CgScalars) <= 128, "CgScalars exceed their slot");
   static_assert(128 + (2 * FG_MMAX + FG_MMAX + 3) * sizeof(double) <= 640, "FGCR scalars overlap");
@@ -544,8 +602,8 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
 
   // |b|^2;  x = 0;  r = b
   double bb;
-  WD_TRY(blas_norm2(G, WD_F64, vref(b, 2), 1, rb, a.rr, st));
-  WD_TRY(read(a.rr, 1, &bb));
+  WD_TRY(blas_norm2(G, WD_F64, vref(b, 2), 1, rb, nrm, st));
+  WD_TRY(read(nrm, 1, &bb));
   if (!(bb < 1e300)) return set_error(WD_ERR_NONFINITE, "FGCR: |b|^2 is not finite");
   WD_TRY(blas_convert(G, WD_F64, vref(b, 2), WD_F64, vref(x, 2), 0.0, nullptr, 1, st));
   if (bb == 0.0) {
@@ -596,25 +654,46 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
     }
     WD_HIP(hipMemsetAsync(E, 0, h32, st));
     double s2;
-    WD_TRY(blas_norm2(G, S, vref(R, 1), 1, rb, a.rr, st));
-    WD_TRY(read(a.rr, 1, &s2));
+    WD_TRY(blas_norm2(G, S, vref(R, 1), 1, rb, nrm, st));
+    WD_TRY(read(nrm, 1, &s2));
     const double target = prm.inner_tol * prm.inner_tol * s2;
-    double rr = s2, best = s2;
-    int since = 0, k = 0;
-    while (rr > target && it < prm.max_iter) {
-      char *zk = (char *)a.Z[k], *wk = (char *)a.W[k];
+    double rr = s2, last = s2, best = s2;
+    int since = 0, k = 0;        // k: accepted directions of the cycle
+    int queued = 0, taken = 0;   // directions of this inner solve queued, and read back
+    // queue the next direction (slot queued % m)
+    auto direction = [&]() -> wd_status {
+      const int q = queued % m;
+      // the full basis enters the solution before its first slot is used again
+      if (q == 0 && queued > 0) accum(m);
+      char *zk = (char *)a.Z[q], *wk = (char *)a.W[q];
       if (N && ptc_act(N) == WD_BF16) WD_TRY(ptc_apply_even_b(N, R, S, zk, S, st));
       else if (N) WD_TRY(ptc_apply_even(N, R, S, zk, S, st));
       else WD_TRY(blas_convert(G, S, vref(R, 1), S, vref(zk, 1), 1.0, nullptr, 1, st));
       WD_TRY(apply_mhat(g, S, zk, wk, T, kappa, st));
-      calls += 2;
       a.wk = wk;
       a.zk = zk;
-      a.k = k;
-      if (S == WD_F32) fg_direction<WD_F32>(a, k, st);
-      else fg_direction<WD_BF16>(a, k, st);
+      a.k = q;
+      a.rr_host = rr_dev + (size_t)(queued & 1) * nblk;
+      if (S == WD_F32) fg_direction<WD_F32>(a, q, st);
+      else fg_direction<WD_BF16>(a, q, st);
       WD_TRY(hip_check(hipGetLastError(), "fgcr launch"));
-      WD_TRY(read(a.rr, 1, &rr));
+      WD_HIP(hipEventRecord(ev.e[queued & 1], st));
+      ++queued;
+      return WD_OK;
+    };
+    while (rr > target && it < prm.max_iter) {
+      if (queued == taken) WD_TRY(direction());
+      // One direction ahead, unless the one that is waited for may converge:
+      // at twice the last step's reduction in the exponent it would not.  The
+      // two lists of partials and events alternate.
+      const double f = taken > 0 ? std::min(1.0, rr / last) : 0.25;
+      if (rr * f * f > target && it + 1 < prm.max_iter) WD_TRY(direction());
+      WD_HIP(hipEventSynchronize(ev.e[taken & 1]));
+      last = rr;
+      rr = 0.0;
+      for (unsigned q = 0; q < nblk; ++q) rr += hres[64 + (size_t)(taken & 1) * nblk + q];
+      ++taken;
+      calls += 2;
       ++it;
       if (!(rr < 1e300)) {
         fallback = true;
@@ -627,13 +706,11 @@ wd_status solve_fgcr_mixed(wd_gauge *g, const void *b, void *x, double kappa, do
         fallback = true;
         break;
       }
-      // the cycle's steps enter the solution when the basis wraps (and after the loop)
-      k = k + 1;
-      if (k == m) {
-        accum(k);
-        k = 0;
-      }
+      k = (taken - 1) % m + 1;
     }
+    // a direction queued after the last accepted one may have started a cycle:
+    // then the accepted cycle has entered the solution already
+    if (queued > taken && k == m) k = 0;
     if (fallback) break;
     if (k > 0) accum(k);
     // e_o = rh_o + kappa H_oe E;  x += |r| e;  r = b - D x
