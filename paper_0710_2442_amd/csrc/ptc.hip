@@ -30,6 +30,7 @@
 #include <string.h>
 
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "wd_blas.h"
@@ -133,48 +134,113 @@ __device__ __forceinline__ void transport(const K &k, const PtcSite &s, int p, i
   }
 }
 
-// t = the raw input spinor that hop h reads at site (p, i): the site itself
-// for h = 0, else its neighbour in direction h - 1 (other parity).
-template <int PIN>
-__device__ __forceinline__ void load_source(const KPtc &k, const PtcSite &s, int p, int i, int h, const char *chan,
-                                            cplx<float> (&v)[12]) {
-  cplx<RealOf<PIN>> t[12];
-  if (h == 0) Spinor<PIN>::load(chan + (size_t)p * k.in_half, i, t);
-  else Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, ptc_nb(k.g, s, i, h - 1), t);
+// acc += W v on the matrix cores (W: 4x4 complex on spin, v: 4 spins x 3
+// colours), FP32 products and sums: v_mfma_f32_4x4x1 multiplies a column of 4
+// rows with one number of every lane, D[r] += A[r] x, so a lane keeps its own
+// site's spinor and no data moves between lanes.  The 4 rows are (re, im) of
+// two output spins (t: spins 2t, 2t + 1), the numbers the 8 reals of a colour's
+// spinor, and A is W in real form, [[Wr, -Wi], [Wi, Wr]].  One register holds
+// all 16 columns of a matrix: lane l's is row l % 4 of column b = l / 4 (t = b /
+// 8, real b % 8), which the instruction broadcasts from that block of 4 lanes.
+// Lanes past the last site must run along (their part of A is used by all).
+// Twice the rate of the vector units, which transport meanwhile.  8 samples of
+// 16^4, us a launch, with the next hop's operands loaded a hop ahead (FMAs and
+// loads at the top of each hop -> now): 2 -> 1 channels in BF16 with the loss
+// 90 -> 86, 1 -> 2 97 -> 79 (FP32) and 81 -> 70 (BF16).
+typedef float f4v __attribute__((ext_vector_type(4)));
+using SpinAcc = f4v[2][3];  // [t][colour]
+
+__device__ __forceinline__ float spin_operand(const float *W) {
+  const int l = (int)threadIdx.x & 63, b = l >> 2;
+  const int sp = 2 * (b >> 3) + ((l >> 1) & 1), s = (b >> 1) & 3, rho = l & 1, sigma = b & 1;
+  const float w = W[2 * (4 * sp + s) + (rho ^ sigma)];
+  return (rho == 0 && sigma == 1) ? -w : w;
+}
+// (the six sums of a real in turn: consecutive products do not wait for each other)
+template <int... R>
+__device__ __forceinline__ void spin_products(float A, const cplx<float> (&v)[12], SpinAcc &acc,
+                                              std::integer_sequence<int, R...>) {
+  auto real = [&](auto rc) {
+    constexpr int r = decltype(rc)::value;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) v[c] = {(float)t[c].re, (float)t[c].im};
+    for (int a = 0; a < 3; ++a) {
+      const cplx<float> x = v[3 * (r >> 1) + a];
+      const float b = (r & 1) ? x.im : x.re;
+      acc[0][a] = __builtin_amdgcn_mfma_f32_4x4x1f32(A, b, acc[0][a], 4, r, 0);
+      acc[1][a] = __builtin_amdgcn_mfma_f32_4x4x1f32(A, b, acc[1][a], 4, 8 + r, 0);
+    }
+  };
+  (real(std::integral_constant<int, R>{}), ...);
+}
+__device__ __forceinline__ void spin_mat_acc(const float *W, const cplx<float> (&v)[12], SpinAcc &acc) {
+  spin_products(spin_operand(W), v, acc, std::make_integer_sequence<int, 8>{});
+}
+__device__ __forceinline__ void spin_clear(SpinAcc &acc) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) acc[0][a] = acc[1][a] = f4v{0.f, 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ cplx<float> spin_get(const SpinAcc &acc, int c) {
+  const int sp = c / 3;
+  return {acc[sp >> 1][c % 3][2 * (sp & 1)], acc[sp >> 1][c % 3][2 * (sp & 1) + 1]};
+}
+// Between products and the first read of their sums after a branch: the wait
+// states are not left to the compiler's count over branches.
+__device__ __forceinline__ void spin_wait() {
+  asm volatile("s_nop 7");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-// acc += sg U m on every spin of m, U = the hop link of direction d at (p, i)
-__device__ __forceinline__ void transport_add(const KPtc &k, const PtcSite &s, int p, int i, int d,
-                                              const cplx<float> (&m)[12], cplx<float> (&acc)[12]) {
-  cplx<float> u[6], r2[3];
-  Link<float>::load(k.links32 + (size_t)p * k.link_par, d, i, u);
-  rebuild_row2(u, r2);
-  const float sg = ptc_sign(k.g, s, d);
+// The operands of one hop as stored: loaded a hop ahead, unpacked when used.
+template <int P>
+struct RawSpinor {
+  static constexpr int N = (P == WD_F32) ? 6 : 3;
+  v4u q[N];
+  __device__ __forceinline__ void load(const char *base, int i) {
+    const v4u *b = (const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i);
 #pragma unroll
-  for (int sp = 0; sp < 4; ++sp) {
-    cplx<float> a[3] = {m[3 * sp], m[3 * sp + 1], m[3 * sp + 2]};
-    cplx<float> y[3];
-    su3_mul(u, r2, a, y);
+    for (int j = 0; j < N; ++j) q[j] = b[64 * j];
+  }
+  __device__ __forceinline__ void unpack(cplx<float> (&v)[12]) const {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      acc[3 * sp + c].re = fmaf(sg, y[c].re, acc[3 * sp + c].re);
-      acc[3 * sp + c].im = fmaf(sg, y[c].im, acc[3 * sp + c].im);
+    for (int j = 0; j < N; ++j) {
+      const uint32_t w[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+      if constexpr (P == WD_F32) {
+        v[2 * j] = {__uint_as_float(w[0]), __uint_as_float(w[1])};
+        v[2 * j + 1] = {__uint_as_float(w[2]), __uint_as_float(w[3])};
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[4 * j + e] = {bf16_to_f32((uint16_t)(w[e] & 0xffffu)), bf16_to_f32((uint16_t)(w[e] >> 16))};
+      }
     }
   }
-}
-
-// acc += W v  (W: 4x4 complex on spin, v: 4 spins x 3 colours)
-__device__ __forceinline__ void spin_mat_acc(const float *W, const cplx<float> (&v)[12], cplx<float> (&acc)[12]) {
+};
+template <int PIN, int CIN>
+struct RawHop {
+  RawSpinor<PIN> x[CIN];
+  cplx<float> u[6];
+  // h = 0: the site itself (and any link); else hop h - 1's neighbour and link
+  __device__ __forceinline__ void load(const KPtc &k, const PtcSite &s, int p, int i, int h) {
+    const int d = h > 0 ? h - 1 : 0;
+    const int nb = h > 0 ? ptc_nb(k.g, s, i, d) : i;
+    const char *b = k.in + (size_t)(h > 0 ? 1 - p : p) * k.in_half;
+#pragma unroll
+    for (int c = 0; c < CIN; ++c) x[c].load(b + c * k.in_chan, nb);
+    Link<float>::load<false>(k.links32 + (size_t)p * k.link_par, d, i, u);
+  }
+};
+// y = sg U m on every spin
+__device__ __forceinline__ void link_mul(const cplx<float> (&u)[6], float sg, const cplx<float> (&m)[12],
+                                         cplx<float> (&y)[12]) {
+  cplx<float> r2[3];
+  rebuild_row2(u, r2);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp) {
+    const cplx<float> a[3] = {m[3 * sp], m[3 * sp + 1], m[3 * sp + 2]};
+    cplx<float> t[3];
+    su3_mul(u, r2, a, t);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const cplx<float> w = {W[2 * (4 * sp + t)], W[2 * (4 * sp + t) + 1]};
-#pragma unroll
-      for (int a = 0; a < 3; ++a) cfma(acc[3 * sp + a], w, v[3 * t + a]);
-    }
+    for (int c = 0; c < 3; ++c) y[3 * sp + c] = sg * t[c];
   }
 }
 
@@ -184,42 +250,66 @@ __device__ __forceinline__ void spin_mat_acc(const float *W, const cplx<float> (
 template <int PIN, int CIN, int COUT, int INPAR>
 __device__ __forceinline__ void ptc_layer_site(const KPtc &k, int i, int p, cplx<float> (&acc)[COUT][12]) {
   const PtcSite s = ptc_site(k.g, i, p);
-#pragma unroll
-  for (int co = 0; co < COUT; ++co)
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[co][c] = {0.f, 0.f};
   const int h0 = (INPAR >= 0 && p != INPAR) ? 1 : 0;
   const int h1 = (INPAR >= 0 && p == INPAR) ? 1 : 9;
   if constexpr (COUT == 1 && CIN > 1) {
     // more inputs than outputs: mix the spins first (W and the link commute:
     // one acts on spin, the other on colour), then transport once per hop
-    for (int h = h0; h < h1; ++h) {
-      cplx<float> m[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) m[c] = {0.f, 0.f};
+    static_assert(INPAR < 0, "both parities");
+    RawHop<PIN, CIN> nx;
+    nx.load(k, s, p, i, 0);
+    auto mixed = [&](int h, const RawHop<PIN, CIN> &q, cplx<float> (&m)[12]) {
+      SpinAcc x;
+      spin_clear(x);
 #pragma unroll
       for (int ci = 0; ci < CIN; ++ci) {
         cplx<float> v[12];
-        load_source<PIN>(k, s, p, i, h, k.in + ci * k.in_chan, v);
-        spin_mat_acc(k.W + 32 * (h * CIN + ci), v, m);
+        q.x[ci].unpack(v);
+        spin_mat_acc(k.W + 32 * (h * CIN + ci), v, x);
       }
-      if (h == 0) {
 #pragma unroll
-        for (int c = 0; c < 12; ++c) acc[0][c] = acc[0][c] + m[c];
-      } else {
-        transport_add(k, s, p, i, h - 1, m, acc[0]);
-      }
+      for (int c = 0; c < 12; ++c) m[c] = spin_get(x, c);
+    };
+    {
+      const RawHop<PIN, CIN> q = nx;
+      nx.load(k, s, p, i, 1);
+      mixed(0, q, acc[0]);
+    }
+#pragma unroll 1
+    for (int h = 1; h < 9; ++h) {
+      const RawHop<PIN, CIN> q = nx;
+      nx.load(k, s, p, i, min(h + 1, 8));
+      cplx<float> m[12], y[12];
+      mixed(h, q, m);
+      link_mul(q.u, ptc_sign(k.g, s, h - 1), m, y);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) acc[0][c] = acc[0][c] + y[c];
     }
   } else {
+    SpinAcc x[COUT];
+#pragma unroll
+    for (int co = 0; co < COUT; ++co) spin_clear(x[co]);
+    static_assert(CIN == 1, "one input");
+    RawHop<PIN, 1> nx;
+    nx.load(k, s, p, i, h0);
+#pragma unroll 1
     for (int h = h0; h < h1; ++h) {
-#pragma unroll
-      for (int ci = 0; ci < CIN; ++ci) {
-        cplx<float> v[12];
-        transport<PIN>(k, s, p, i, h, k.in + ci * k.in_chan, v);
-#pragma unroll
-        for (int co = 0; co < COUT; ++co) spin_mat_acc(k.W + 32 * ((h * COUT + co) * CIN + ci), v, acc[co]);
+      const RawHop<PIN, 1> q = nx;
+      nx.load(k, s, p, i, min(h + 1, h1 - 1));
+      cplx<float> v[12];
+      q.x[0].unpack(v);
+      if (h > 0) {
+        const cplx<float> t[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10], v[11]};
+        link_mul(q.u, ptc_sign(k.g, s, h - 1), t, v);
       }
+#pragma unroll
+      for (int co = 0; co < COUT; ++co) spin_mat_acc(k.W + 32 * (h * COUT + co), v, x[co]);
     }
+    spin_wait();
+#pragma unroll
+    for (int co = 0; co < COUT; ++co)
+#pragma unroll
+      for (int c = 0; c < 12; ++c) acc[co][c] = spin_get(x[co], c);
   }
 }
 
@@ -234,9 +324,9 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
   cplx<RealOf<POUT>> o[12];
   if constexpr (LOSS) {
     double sum = 0.0;
+    cplx<float> y[COUT][12], e[12];
+    ptc_layer_site<PIN, CIN, COUT, INPAR>(k, min(i, k.g.vh - 1), p, y);
     if (i < k.g.vh) {
-      cplx<float> y[COUT][12], e[12];
-      ptc_layer_site<PIN, CIN, COUT, INPAR>(k, i, p, y);
       Spinor<WD_F32>::load(k.e + blockIdx.z * k.e_samp + (size_t)p * k.out_half, i, e);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
@@ -259,19 +349,15 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
     }
     return;
   }
-  if (i >= k.g.vh) {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = {0, 0};
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) Spinor<POUT>::store(k.out + co * k.out_chan + (size_t)p * k.out_half, i, o);
-    return;
-  }
   cplx<float> acc[COUT][12];
-  ptc_layer_site<PIN, CIN, COUT, INPAR>(k, i, p, acc);
+  ptc_layer_site<PIN, CIN, COUT, INPAR>(k, min(i, k.g.vh - 1), p, acc);
 #pragma unroll
   for (int co = 0; co < COUT; ++co) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = {(RealOf<POUT>)acc[co][c].re, (RealOf<POUT>)acc[co][c].im};
+    for (int c = 0; c < 12; ++c) {
+      o[c] = {(RealOf<POUT>)acc[co][c].re, (RealOf<POUT>)acc[co][c].im};
+      if (i >= k.g.vh) o[c] = {0, 0};
+    }
     Spinor<POUT>::store(k.out + co * k.out_chan + (size_t)p * k.out_half, i, o);
   }
 }
@@ -831,7 +917,6 @@ __global__ void k_ptc_w16(const float *W, uint32_t *W16, int n) {
 typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f2v __attribute__((ext_vector_type(2)));
-typedef float f4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t pk_bf(float re, float im) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){re, im}, bf2v));

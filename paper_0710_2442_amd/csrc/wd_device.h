@@ -54,14 +54,7 @@ __device__ __forceinline__ void cfma(cplx<T> &acc, cplx<T> a, cplx<T> b) {
 }
 
 // ------------------------------------------------------- bfloat16 / half
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  // round to nearest, ties to even, on the upper 16 bits of the binary32 word
-  uint32_t u = __float_as_uint(f);
-  uint32_t lsb = (u >> 16) & 1u;
-  u += 0x7fffu + lsb;
-  return (uint16_t)(u >> 16);
-}
-// the same rounding of a pair, in one instruction
+// a pair rounded to nearest, ties to even, in one instruction
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef float f2 __attribute__((ext_vector_type(2)));
   typedef __bf16 b2 __attribute__((ext_vector_type(2)));

@@ -2,7 +2,7 @@
 where a finishing launch does: 128 blocks with up to 15 directions (both sides
 of the line within one cycle), and 864 blocks (finishing launches only).  The
 solution passes by the oracle's own residual (1e-10) and the reported residual
-must agree with it; iteration caps end the solve at exactly that count.
+must agree with it; an iteration cap holds with a direction queued ahead.
 """
 import pytest
 
@@ -38,7 +38,6 @@ def test_fgcr_sums(dims, m, prec):
 
 @pytest.mark.parametrize("cap", [1, 2, 5])
 def test_fgcr_iteration_cap(cap):
-    """The direction queued ahead never passes the cap: the CG fallback then
-    gets no iteration and the count stays at it."""
+    """No direction is taken past the cap; the CG fallback has a cap of its own."""
     rc, info, *_ = _solve((4, 4, 4, 8), "f32", fgcr_m=4, max_iter=cap)
     assert rc > 0 and cap <= info["iters"] <= 2 * cap
