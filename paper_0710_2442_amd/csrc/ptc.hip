@@ -103,37 +103,6 @@ __device__ __forceinline__ float ptc_sign(const Geom &g, const PtcSite &s, int d
   return (d == 3 && s.x4 == g.L[3] - 1) || (d == 7 && s.x4 == 0) ? g.tbc : 1.0f;
 }
 
-// v = T_h psi_c at site (p, i); psi channel base `chan` (full field).
-template <int PIN, class K>
-__device__ __forceinline__ void transport(const K &k, const PtcSite &s, int p, int i, int h, const char *chan,
-                                          cplx<float> (&v)[12]) {
-  if (h == 0) {
-    cplx<RealOf<PIN>> t[12];
-    Spinor<PIN>::load(chan + (size_t)p * k.in_half, i, t);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) v[c] = {(float)t[c].re, (float)t[c].im};
-    return;
-  }
-  const int d = h - 1;
-  cplx<RealOf<PIN>> t[12];
-  Spinor<PIN>::load(chan + (size_t)(1 - p) * k.in_half, ptc_nb(k.g, s, i, d), t);
-  cplx<float> u[6], r2[3];
-  Link<float>::load(k.links32 + (size_t)p * k.link_par, d, i, u);
-  rebuild_row2(u, r2);
-  const float sg = ptc_sign(k.g, s, d);
-#pragma unroll
-  for (int sp = 0; sp < 4; ++sp) {
-    cplx<float> a[3] = {{(float)t[3 * sp].re, (float)t[3 * sp].im},
-                        {(float)t[3 * sp + 1].re, (float)t[3 * sp + 1].im},
-                        {(float)t[3 * sp + 2].re, (float)t[3 * sp + 2].im}};
-    cplx<float> y[3];
-    su3_mul(u, r2, a, y);
-    v[3 * sp] = sg * y[0];
-    v[3 * sp + 1] = sg * y[1];
-    v[3 * sp + 2] = sg * y[2];
-  }
-}
-
 // acc += W v on the matrix cores (W: 4x4 complex on spin, v: 4 spins x 3
 // colours), FP32 products and sums: v_mfma_f32_4x4x1 multiplies a column of 4
 // rows with one number of every lane, D[r] += A[r] x, so a lane keeps its own
@@ -146,7 +115,7 @@ __device__ __forceinline__ void transport(const K &k, const PtcSite &s, int p, i
 // Twice the rate of the vector units, which transport meanwhile.  8 samples of
 // 16^4, us a launch, with the next hop's operands loaded a hop ahead (FMAs and
 // loads at the top of each hop -> now): 2 -> 1 channels in BF16 with the loss
-// 90 -> 86, 1 -> 2 97 -> 79 (FP32) and 81 -> 70 (BF16).
+// 90 -> 88, 1 -> 2 97 -> 81 (FP32) and 81 -> 69 (BF16).
 typedef float f4v __attribute__((ext_vector_type(4)));
 using SpinAcc = f4v[2][3];  // [t][colour]
 
@@ -183,11 +152,13 @@ __device__ __forceinline__ cplx<float> spin_get(const SpinAcc &acc, int c) {
   const int sp = c / 3;
   return {acc[sp >> 1][c % 3][2 * (sp & 1)], acc[sp >> 1][c % 3][2 * (sp & 1) + 1]};
 }
-// Between products and the first read of their sums after a branch: the wait
-// states are not left to the compiler's count over branches.
-__device__ __forceinline__ void spin_wait() {
-  asm volatile("s_nop 7");
-  __builtin_amdgcn_sched_barrier(0);
+// The wait for products whose sums are read past a branch: it stands in the
+// products' own block and takes the sums as operands, so that every read or copy
+// of them comes after it and nothing rests on the compiler's count of wait
+// states over branches.
+__device__ __forceinline__ void spin_wait(SpinAcc &x) {
+  asm volatile("s_nop 7"
+               : "+v"(x[0][0]), "+v"(x[0][1]), "+v"(x[0][2]), "+v"(x[1][0]), "+v"(x[1][1]), "+v"(x[1][2]));
 }
 
 // The operands of one hop as stored: loaded a hop ahead, unpacked when used.
@@ -267,6 +238,7 @@ __device__ __forceinline__ void ptc_layer_site(const KPtc &k, int i, int p, cplx
         q.x[ci].unpack(v);
         spin_mat_acc(k.W + 32 * (h * CIN + ci), v, x);
       }
+      spin_wait(x);  // (the sign of a hop is chosen by branches)
 #pragma unroll
       for (int c = 0; c < 12; ++c) m[c] = spin_get(x, c);
     };
@@ -304,8 +276,9 @@ __device__ __forceinline__ void ptc_layer_site(const KPtc &k, int i, int p, cplx
       }
 #pragma unroll
       for (int co = 0; co < COUT; ++co) spin_mat_acc(k.W + 32 * (h * COUT + co), v, x[co]);
+#pragma unroll
+      for (int co = 0; co < COUT; ++co) spin_wait(x[co]);
     }
-    spin_wait();
 #pragma unroll
     for (int co = 0; co < COUT; ++co)
 #pragma unroll
@@ -379,11 +352,12 @@ __global__ __launch_bounds__(PTC_BS) void k_ptc_layer(KPtc k) {
 // accesses complete in order.  The sums stay in the matrix cores' FP64
 // registers over all of a wave's sites; 5 pairs of hops (h = 0 alone), 48
 // products each per 64 sites.
-// Bound by the FP64 products (240 of 64 cycles per 64 sites: 51 us of the 124
+// Bound by the FP64 products (240 of 64 cycles per 64 sites: 51 us of the 116
 // below at the full rate) next to the transports' vector work.  Each
 // lane summing its site's products and a wave adding 64 rows per float in FP64
-// took 55 us a sample of 16^4 on 256 blocks; 8 samples together now take 124
-// (layer 1, BF16 input) and 120 us (layer 2).
+// took 55 us a sample of 16^4 on 256 blocks; 8 samples together now take 116
+// (layer 1, BF16 input) and 113 us (layer 2); 124 and 120 with the pairs in a
+// loop around a switch, where the sums moved between registers.
 typedef double d4v __attribute__((ext_vector_type(4)));
 constexpr int WG_BLOCKS = 512;  // two blocks per CU of 256
 constexpr int WG_ROW = 68;
@@ -442,10 +416,19 @@ __global__ __launch_bounds__(PTC_BS, 2) void k_ptc_wgrad(KWg k) {
         F[a][4 * j] = x.x, F[a][4 * j + 1] = x.y, F[a][4 * j + 2] = x.z, F[a][4 * j + 3] = x.w;
       }
     __builtin_amdgcn_wave_barrier();
-#pragma unroll 1
-    for (int h = 0; h < 9; ++h) {
-      cplx<float> v[12];
-      transport<PT>(k, s, p, i, h, tb, v);
+    auto transported = [&](int h) {
+      // every operand on its way before the first is unpacked (the compiler
+      // would wait for BF16 packets one by one: 143 us instead of 116)
+      RawSpinor<PT> x;
+      cplx<float> v[12], u[6];
+      x.load(tb + (size_t)(h > 0 ? 1 - p : p) * k.in_half, h > 0 ? ptc_nb(k.g, s, i, h - 1) : i);
+      if (h > 0) Link<float>::load(k.links32 + (size_t)p * k.link_par, h - 1, i, u);
+      __builtin_amdgcn_sched_barrier(0);
+      x.unpack(v);
+      if (h > 0) {
+        const cplx<float> t[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10], v[11]};
+        link_mul(u, ptc_sign(k.g, s, h - 1), t, v);
+      }
       float *Th = T + ((h > 0 && !(h & 1)) ? 8 * WG_ROW : 0) + lane;
 #pragma unroll
       for (int j = 0; j < 12; ++j) {
@@ -453,36 +436,40 @@ __global__ __launch_bounds__(PTC_BS, 2) void k_ptc_wgrad(KWg k) {
         Th[row * WG_ROW] = v[j].re;
         Th[(row + 1) * WG_ROW] = v[j].im;
       }
-      if (h & 1) continue;
-      // h = 0, or the second hop of a pair (the columns of slot 1 are not used for h = 0)
-      __builtin_amdgcn_wave_barrier();
-      auto products = [&](d4v D) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const v4f x = *(const v4f *)(T + (a * 16 + n) * WG_ROW + 16 * q + 4 * j);
-            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j], x.x, D, 0, 0, 0);
-            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 1], x.y, D, 0, 0, 0);
-            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 2], x.z, D, 0, 0, 0);
-            D = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 3], x.w, D, 0, 0, 0);
-          }
-        return D;
-      };
-      // the products go straight into the pair's sums: a sum of D and acc after
-      // this branch is read too early (the compiler counts the wait states of
-      // FP64 products short across branches)
-      switch (h >> 1) {
-        case 0: acc[0] = products(acc[0]); break;
-        case 1: acc[1] = products(acc[1]); break;
-        case 2: acc[2] = products(acc[2]); break;
-        case 3: acc[3] = products(acc[3]); break;
-        default: acc[4] = products(acc[4]); break;
+    };
+    // (one pair after the other: the sums and F leave no registers for two)
+    auto pair = [&](auto pc) {
+      constexpr int J = decltype(pc)::value;
+      if constexpr (J == 0) {
+        transported(0);  // (the columns of slot 1 are not used)
+      } else {
+        transported(2 * J - 1);
+        transported(2 * J);
       }
       __builtin_amdgcn_wave_barrier();
-    }
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const v4f x = *(const v4f *)(T + (a * 16 + n) * WG_ROW + 16 * q + 4 * j);
+          acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j], x.x, acc[J], 0, 0, 0);
+          acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 1], x.y, acc[J], 0, 0, 0);
+          acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 2], x.z, acc[J], 0, 0, 0);
+          acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(F[a][4 * j + 3], x.w, acc[J], 0, 0, 0);
+        }
+      __builtin_amdgcn_wave_barrier();
+    };
+    pair(std::integral_constant<int, 0>{});
+    pair(std::integral_constant<int, 1>{});
+    pair(std::integral_constant<int, 2>{});
+    pair(std::integral_constant<int, 3>{});
+    pair(std::integral_constant<int, 4>{});
+    // The wait for the last products (18 states) stands in their own block and
+    // takes the sums as operands, so that every read or copy of a sum comes
+    // after it: the compiler counts the wait states of FP64 products short
+    // across branches, and a sum read behind one is wrong.
+    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]));
   }
-  asm volatile("s_nop 15\n\ts_nop 7");  // the last products (18 wait states)
   // the block's sum over its waves; the products of real components combine
   // into the complex gradient
   __syncthreads();
