@@ -287,7 +287,7 @@ struct NbRaw16 {
     }
   }
   // the spinor, or in its first 6 components the half that was loaded
-  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool, bool lower) const {
+  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool lower) const {
     s[0] = num(lower ? a.z : a.x); s[1] = num(lower ? a.w : a.y);
     s[2] = num(lower ? b.x : a.z); s[3] = num(lower ? b.y : a.w);
     s[4] = num(lower ? b.z : b.x); s[5] = num(lower ? b.w : b.y);
@@ -427,7 +427,17 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
   const int i = tile * SPLIT_SITES + lane;
   const bool site = i < k.g.vh;
   const int r0 = chunk * m.rpl, r1 = min(m.nrhs, r0 + m.rpl);
-  auto live = [&](int r) { return r < r1 && !(k.skip && k.skip[(size_t)r * m.skip_stride]); };
+  // the chunk's systems that are not masked, one bit each: a finished system
+  // costs neither loads nor a barrier, a finished chunk not even its links
+  // (12 systems of 16^4 in BF16, none live: 13 us a launch -> 2)
+  bool mine = r0 + lane < r1;
+  if (k.skip && mine) mine = k.skip[(size_t)(r0 + lane) * m.skip_stride] == 0;
+  const unsigned chosen = (unsigned)__ballot(mine);  // (MR_CHUNK bits at most)
+  if (!chosen) {
+    if constexpr (NORM)
+      for (int r = r0 + (int)threadIdx.x; r < r1; r += SPLIT_BS) k.partials[(size_t)r * m.ntiles + tile] = 0.0;
+    return;
+  }
   int nb = 0;
   bool edge = false;
   cplx<T> u[6], r2[3];
@@ -448,38 +458,40 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
   const T f = (T)2 * (edge ? (T)k.g.tbc : (T)1);
   NbRaw<P> nx;  // (padding lanes read site 0)
   const bool time = (w & 3) == 3, lower = time && (w == 3) == DAG;
-  nx.load(k.in + (size_t)r0 * m.rhs_stride, nb, time, lower);
+  unsigned todo = chosen;
+  int r = r0 + __builtin_ctz(todo);
+  nx.load(k.in + (size_t)r * m.rhs_stride, nb, time, lower);
 #pragma unroll 1
-  for (int r = r0; r < r1; ++r) {
+  for (int n = 0;; ++n) {  // n-th live system of the chunk: r
+    todo &= todo - 1;
+    const bool more = todo != 0;
+    const int rn = more ? r0 + __builtin_ctz(todo) : r;
     // opaque copies: the addresses of the six sums are formed where they are
     // used, not kept in registers across the loop
     int li = lane, ii = i;
     asm volatile("" : "+v"(li), "+v"(ii));
     const int slot = w * 6 * SPLIT_SITES + li;
-    const bool on = live(r);
-    SplitLds<P> &L = lds[NB == 2 ? (r - r0) & 1 : 0];
+    SplitLds<P> &L = lds[NB == 2 ? n & 1 : 0];
     // the next right-hand side's neighbour is loaded, by one load for all
     // directions, before this one's products
-    const char *next = k.in + (size_t)(r + 1) * m.rhs_stride;
+    const char *next = k.in + (size_t)rn * m.rhs_stride;
     cplx<T> *q = L.g + slot;
     if constexpr (P == WD_F16) {
       cplx<T> psi[12];
-      nx.unpack(psi, time, lower);
-      if (r + 1 < r1) nx.load(next, nb, time, lower);
-      if (on) {
+      nx.unpack(psi, lower);
+      if (more) nx.load(next, nb, time, lower);
 #define WD_HOP(D) mrhs_split_hop16<DAG, D>(psi, f, u, r2, q)
-        switch (w) {
-          case 0: WD_HOP(0); break;
-          case 1: WD_HOP(1); break;
-          case 2: WD_HOP(2); break;
-          case 3: WD_HOP(3); break;
-          case 4: WD_HOP(4); break;
-          case 5: WD_HOP(5); break;
-          case 6: WD_HOP(6); break;
-          default: WD_HOP(7); break;
-        }
-#undef WD_HOP
+      switch (w) {
+        case 0: WD_HOP(0); break;
+        case 1: WD_HOP(1); break;
+        case 2: WD_HOP(2); break;
+        case 3: WD_HOP(3); break;
+        case 4: WD_HOP(4); break;
+        case 5: WD_HOP(5); break;
+        case 6: WD_HOP(6); break;
+        default: WD_HOP(7); break;
       }
+#undef WD_HOP
     } else {
       cplx<T> h[6];
 #define WD_HOP(D) mrhs_split_project<P, DAG, D>(nx, f, h)
@@ -494,46 +506,48 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
         default: WD_HOP(7); break;
       }
 #undef WD_HOP
-      if (r + 1 < r1) nx.load(next, nb, time, lower);
-      if (on) mrhs_split_mul<P>(u, r2, h, q);
+      if (more) nx.load(next, nb, time, lower);
+      mrhs_split_mul<P>(u, r2, h, q);
     }
-    const int ws = NB == 2 ? (w + NW * (r - r0)) & 7 : w;  // the waves take turns
+    const int ws = NB == 2 ? (w + NW * n) & 7 : w;  // the waves take turns
     const size_t off = (size_t)r * m.rhs_stride;
     cplx<T> x[CW], y[CW];  // loaded before the barrier (FP64, short of registers: after the sums)
-    if (P != WD_F64 && on && ws < NW && ii < k.g.vh) {
+    if (P != WD_F64 && ws < NW && ii < k.g.vh) {
       if constexpr (EPI >= 1) split_load<P>(k.X + off, ii, ws, x);
       if constexpr (EPI == 2) split_load<P>(k.Y + off, ii, ws, y);
     }
     __syncthreads();
-    double n = 0.0;
-    if (on) {
-      constexpr auto J = std::make_integer_sequence<int, CW>{};
-      if (ws == 0) n = mrhs_split_finish<P, DAG, EPI, NORM, 0>(k, off, ii, li, L, x, y, J);
-      if constexpr (NW > 1) {
-        if (ws == 1) n = mrhs_split_finish<P, DAG, EPI, NORM, 1>(k, off, ii, li, L, x, y, J);
-        if (ws == 2) n = mrhs_split_finish<P, DAG, EPI, NORM, 2>(k, off, ii, li, L, x, y, J);
-      }
-      if constexpr (NW > 3) {
-        if (ws == 3) n = mrhs_split_finish<P, DAG, EPI, NORM, 3>(k, off, ii, li, L, x, y, J);
-        if (ws == 4) n = mrhs_split_finish<P, DAG, EPI, NORM, 4>(k, off, ii, li, L, x, y, J);
-        if (ws == 5) n = mrhs_split_finish<P, DAG, EPI, NORM, 5>(k, off, ii, li, L, x, y, J);
-      }
+    double nrm = 0.0;
+    constexpr auto J = std::make_integer_sequence<int, CW>{};
+    if (ws == 0) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 0>(k, off, ii, li, L, x, y, J);
+    if constexpr (NW > 1) {
+      if (ws == 1) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 1>(k, off, ii, li, L, x, y, J);
+      if (ws == 2) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 2>(k, off, ii, li, L, x, y, J);
+    }
+    if constexpr (NW > 3) {
+      if (ws == 3) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 3>(k, off, ii, li, L, x, y, J);
+      if (ws == 4) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 4>(k, off, ii, li, L, x, y, J);
+      if (ws == 5) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 5>(k, off, ii, li, L, x, y, J);
     }
     if constexpr (NORM) {
       if (ws < NW) {
-        n = wave_sum(n);
-        if (lane == 0) sred[r - r0][ws] = n;
+        nrm = wave_sum(nrm);
+        if (lane == 0) sred[r - r0][ws] = nrm;
       }
     }
+    if (!more) break;
     if constexpr (NB == 1) __syncthreads();  // before the next right-hand side overwrites the buffer
+    r = rn;
   }
   if constexpr (NORM) {
     __syncthreads();
-    for (int r = r0 + (int)threadIdx.x; r < r1; r += SPLIT_BS) {
+    for (int q = (int)threadIdx.x; q < r1 - r0; q += SPLIT_BS) {
       double s = 0.0;
+      if (chosen >> q & 1) {
 #pragma unroll
-      for (int q = 0; q < NW; ++q) s += sred[r - r0][q];
-      k.partials[(size_t)r * m.ntiles + tile] = s;
+        for (int v = 0; v < NW; ++v) s += sred[q][v];
+      }
+      k.partials[(size_t)(r0 + q) * m.ntiles + tile] = s;
     }
   }
 }
