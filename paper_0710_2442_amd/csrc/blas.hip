@@ -529,13 +529,15 @@ wd_status blas_accum(const Geom &g, wd_prec pe, const VecRef &e, const VecRef &x
 // CG_UNROLL items per thread.  Where every block first adds up the system's
 // nparts partials, 2048 blocks of all systems together, with the one that ends
 // the iteration, are enough: 12 systems of 12^3x24 in FP32 take 11.8 ms, 12.2
-// with twice as many.  Without that list more blocks only help: 12 systems of
-// 24^3x48 in BF16 102.3 ms, 105.1 with the cap.
+// with twice as many.  Without that list 2047 of each system: 12 systems of
+// 24^3x48 in BF16 102.3 ms, 105.1 with the cap of all together.  (2048 and the
+// one that ends the iteration are one more than is resident at once: FP64 CG on
+// 32^3x64 83.1 ms, 82.0 with 2047.)
 static unsigned cg_blocks(const Geom &g, wd_prec pv, int nhalf, int nsys, unsigned nparts, size_t &npk) {
   const int np = pv == WD_F64 ? 12 : pv == WD_F32 ? 6 : 3;
   npk = (size_t)g.vpad * np * nhalf;
   const unsigned b = blocks_for((long)(pv == WD_F16 ? (size_t)g.vh * nhalf : npk));
-  return nparts ? std::min(b, std::max(2u, BLAS_MAX_BLOCKS / (unsigned)nsys) - 1) : b;
+  return std::min(b, nparts ? std::max(2u, BLAS_MAX_BLOCKS / (unsigned)nsys) - 1 : BLAS_MAX_BLOCKS - 1);
 }
 
 wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv, const VecRef &p, const VecRef &s,
