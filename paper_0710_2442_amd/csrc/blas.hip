@@ -345,10 +345,35 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
   block_sum_store<1>(v, k.partials + (size_t)sys * k.nblk, k.nblk, blockIdx.x);
 }
 
-// beta = rr[1-j] / rr[j];  P = R + beta P.   x = R, out = P.  One more block
-// per system (blockIdx.x = 0) ends the iteration: rr[1-j], ss = sum of the
-// update's partials, iteration count and convergence flag.  A system that
-// converged in this iteration still gets its P here, which nothing reads.
+// What ends an iteration of system *sc: |s|^2, iteration count, convergence.
+__device__ __forceinline__ void cg_end(CgScalars *sc, int j, double ss) {
+  const double qq = sc->qq, rr = sc->rr[j];
+  sc->ss = ss;
+  if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
+    sc->done = 2;  // breakdown / non-finite
+  } else {
+    sc->iters += 1;
+    if (ss <= sc->stop2) sc->done = 1;
+    else if (sc->iters >= sc->max_iters) sc->done = 3;
+  }
+}
+
+// The end of the iteration right after the update (early_end): one block per
+// system.  A system that converged is masked from here on.
+__global__ __launch_bounds__(BLAS_BS) void k_cg_end(KBlas k) {
+  CgScalars *sc = k.sc + blockIdx.x;
+  if (!sc->live) return;
+  const double ss = sum_partials(k.ss_parts + (size_t)blockIdx.x * k.nss, k.nss);
+  if (threadIdx.x != 0) return;
+  cg_end(sc, k.j, ss);
+  sc->live = sc->done == 0;
+}
+
+// beta = rr[1-j] / rr[j];  P = R + beta P.   x = R, out = P.  Unless k_cg_end
+// did (nss = 0), one more block per system (blockIdx.x = 0) ends the iteration:
+// rr[1-j], ss = sum of the update's partials, iteration count and convergence
+// flag.  A system that converged in this iteration then still gets its P here,
+// which nothing reads.
 template <int PV>
 __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   using TV = RealOf<PV>;
@@ -360,19 +385,12 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   double rrn;
   if (k.nparts) rrn = sum_partials(k.parts + (size_t)sys * k.nparts, k.nparts);
   else rrn = sc->rr[1 - k.j];
-  if (blockIdx.x == 0) {
+  const unsigned first = k.nss ? 1 : 0;
+  if (blockIdx.x < first) {
     const double ss = sum_partials(k.ss_parts + (size_t)sys * k.nss, k.nss);
     if (threadIdx.x == 0) {
-      const double qq = sc->qq, rr = sc->rr[k.j];
       if (k.nparts) sc->rr[1 - k.j] = rrn;
-      sc->ss = ss;
-      if (!(qq > 0.0) || !(qq < 1e300) || !(rr < 1e300)) {
-        sc->done = 2;  // breakdown / non-finite
-      } else {
-        sc->iters += 1;
-        if (ss <= sc->stop2) sc->done = 1;
-        else if (sc->iters >= sc->max_iters) sc->done = 3;
-      }
+      cg_end(sc, k.j, ss);
     }
     return;
   }
@@ -381,7 +399,7 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   char *Pp = k.out + sys * k.so;
   if constexpr (PV == WD_F16) {
     const long n = (long)k.v.vh * k.v.nhalf;
-    for (long f = (long)(blockIdx.x - 1) * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
+    for (long f = (long)(blockIdx.x - first) * BLAS_BS + threadIdx.x; f < n; f += (long)k.nblk * BLAS_BS) {
       int h, i;
       site_of(k.v, f, h, i);
       cplx<TV> r[12], p[12];
@@ -397,7 +415,7 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   } else {
     using KV = Packet<PV>;
     const size_t step = (size_t)k.nblk * BLAS_BS;
-    for (size_t f0 = (size_t)(blockIdx.x - 1) * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
+    for (size_t f0 = (size_t)(blockIdx.x - first) * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
       cplx<TV> r[CG_UNROLL][KV::CW], p[CG_UNROLL][KV::CW];
 #pragma unroll
       for (int e = 0; e < CG_UNROLL; ++e) {
@@ -540,6 +558,16 @@ static unsigned cg_blocks(const Geom &g, wd_prec pv, int nhalf, int nsys, unsign
   return std::min(b, nparts ? std::max(2u, BLAS_MAX_BLOCKS / (unsigned)nsys) - 1 : BLAS_MAX_BLOCKS - 1);
 }
 
+// Whether a launch of its own ends the iteration right after the update: where
+// the sums take finishing launches anyway, and half an iteration of a system
+// that has just converged (two hops and the p update, once an inner solve) costs
+// more than that launch in each iteration.  BF16 defect correction, end in the
+// p update against after the update: 20^3x40 7.9 / 8.1 ms, 24^3x48 13.6 / 13.6,
+// 32^3x64 37.8 / 37.2; 12 systems of 20^3x40 44.9 / 44.2, of 24^3x48 90.5 / 88.9.
+static bool early_end(const Geom &g, wd_prec px, int nhalf, int nsys, unsigned nparts) {
+  return px == WD_F32 && !nparts && (size_t)g.vh * nhalf * nsys >= ((size_t)1 << 19);
+}
+
 wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv, const VecRef &p, const VecRef &s,
                          const VecRef &q, CgScalars *sc, int j, int nsys, CgParts &cp, hipStream_t st) {
   if (!((px == WD_F64 && pv == WD_F64) || (px == WD_F32 && pv != WD_F64)))
@@ -563,7 +591,13 @@ wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv,
     case WD_F16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F16>), grid, dim3(BLAS_BS), 0, st, k); break;
     case WD_BF16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_BF16>), grid, dim3(BLAS_BS), 0, st, k); break;
   }
-  return hip_check(hipGetLastError(), "cg_update launch");
+  WD_TRY(hip_check(hipGetLastError(), "cg_update launch"));
+  if (!early_end(g, px, p.nhalf, nsys, cp.nnorm)) return WD_OK;
+  k.ss_parts = cp.ss;
+  k.nss = cp.nss;
+  cp.nss = 0;
+  hipLaunchKernelGGL(k_cg_end, dim3((unsigned)nsys), dim3(BLAS_BS), 0, st, k);
+  return hip_check(hipGetLastError(), "cg end launch");
 }
 
 wd_status blas_cg_pupdate(const Geom &g, wd_prec pv, const VecRef &r, const VecRef &p, CgScalars *sc, int j,
@@ -578,7 +612,7 @@ wd_status blas_cg_pupdate(const Geom &g, wd_prec pv, const VecRef &r, const VecR
   k.nparts = cp.nnorm;
   k.ss_parts = cp.ss;
   k.nss = cp.nss;
-  dim3 grid(k.nblk + 1, (unsigned)nsys);
+  dim3 grid(k.nblk + (cp.nss ? 1 : 0), (unsigned)nsys);
   WD_DISPATCH_P(pv, k_cg_pupdate, grid, k, st);
   return hip_check(hipGetLastError(), "cg_pupdate launch");
 }

@@ -77,3 +77,31 @@ def test_finished_systems_are_nearly_free():
             assert rc == 0
     assert secs["one"] < 0.48 * secs["all"], secs
     g.close()
+
+
+@pytest.mark.parametrize("inner", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("cap", [1000, 7])
+def test_where_an_iteration_ends_does_not_change_a_system(inner, cap):
+    """135168 sites a parity, one more tile than the consumers add up: 4 systems
+    end an iteration in a launch of their own, 3 in the p update.  Same bits,
+    same counts, also at the iteration cap and for a zero source."""
+    dims = (16, 16, 16, 66)
+    U = syn.gauge_field((16, 16, 16, 2), 0.3, 95).repeat(33, axis=0)
+    g = wd.Gauge(U, dims, -1, "f64")
+    fields = [wd.wd_new_field(dims, "f64") for _ in range(4)]
+    for r, f in enumerate(fields):
+        wd.wd_gaussian_field(g, f, wd.WD_FULL, "f64", 9, r)
+    fields[1].zero_()
+    m = fields[0].numel()
+    p = _params(inner)
+    p.max_iter = cap
+    got = {}
+    for n in (3, 4):
+        x = torch.full((n * m,), 0xAB, dtype=torch.uint8, device="cuda")
+        rc, infos = wd.wd_solve_mrhs(g, torch.cat(fields[:n]), x, n, KAPPA, 1e-10, p)
+        assert (rc == 0) == (cap == 1000)
+        got[n] = x, [(i["iters"], i["outer_iters"], i["status"]) for i in infos]
+        assert cap == 7 or max(i["true_rel_resid"] for i in infos) <= 1e-10
+    assert got[4][1][:3] == got[3][1] and got[3][1][1][0] == 0
+    assert torch.equal(got[4][0][:3 * m], got[3][0])
+    g.close()
