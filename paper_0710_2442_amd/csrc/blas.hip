@@ -227,8 +227,13 @@ __global__ __launch_bounds__(BLAS_BS) void k_accum(KBlas k) {
 // fields spread over more threads than sites, and every access is contiguous.
 
 // Packets a thread has in flight at a time (the fields may alias for the
-// compiler, so the loads are grouped by hand).
-constexpr int CG_UNROLL = 2;
+// compiler, so the loads are grouped by hand): 2, a grid apart, where that
+// spreads a small field over more threads; 4 runs of the block side by side
+// where the field has them for every thread (cg_side), so that what is in
+// flight from each field is contiguous.  2 apart / 4 side by side, ms: FP64 CG
+// on full fields 32^3x64 236.3 / 232.2, 24^3x48 78.3 / 77.7, FP64 CG 32^3x64
+// 82.0 / 80.9; on 16^3x32, where 4 would leave threads idle, 6.03 / 6.08.
+constexpr int CG_APART = 2, CG_SIDE = 4;
 
 // |M p|^2 of system sys: done = breakdown on a value that is no norm.
 __device__ __forceinline__ bool cg_alpha(const KBlas &k, int sys, double &alpha) {
@@ -249,7 +254,7 @@ __device__ __forceinline__ bool cg_alpha(const KBlas &k, int sys, double &alpha)
 // alpha = rr[j] / qq;  X += alpha P;  S -= alpha Q;  ss = |S|^2.
 // x = X (precision PX), y = P, out = S, out2 = Q (precision PV) -- Q is read only.
 // FP16 storage (a scale per site): one site per thread.
-template <int PX, int PV>
+template <int PX, int PV, int U>
 __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
   using TV = RealOf<PV>;
   using TX = RealOf<PX>;
@@ -293,13 +298,14 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
     using KV = Packet<PV>;
     using KX = Packet<PX>;
     constexpr int R = KV::CW / KX::CW;  // X packets per V packet
-    const size_t step = (size_t)k.nblk * BLAS_BS;
-    for (size_t f0 = (size_t)blockIdx.x * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
-      cplx<TV> p[CG_UNROLL][KV::CW], s[CG_UNROLL][KV::CW], q[CG_UNROLL][KV::CW];
-      cplx<TX> x[CG_UNROLL][KV::CW];
-      size_t fx[CG_UNROLL];
+    const size_t grid = (size_t)k.nblk * BLAS_BS, step = U == CG_SIDE ? BLAS_BS : grid;
+    const size_t b = (size_t)blockIdx.x * BLAS_BS * (U == CG_SIDE ? U : 1);
+    for (size_t f0 = b + threadIdx.x; f0 < k.npk; f0 += U * grid) {
+      cplx<TV> p[U][KV::CW], s[U][KV::CW], q[U][KV::CW];
+      cplx<TX> x[U][KV::CW];
+      size_t fx[U];
 #pragma unroll
-      for (int e = 0; e < CG_UNROLL; ++e) {
+      for (int e = 0; e < U; ++e) {
         const size_t f = min(f0 + e * step, k.npk - 1);  // (past the end: loaded, not stored)
         KV::load(Pv, f, p[e]);
         KV::load(Q, f, q[e]);
@@ -316,7 +322,7 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_update(KBlas k) {
         }
       }
 #pragma unroll
-      for (int e = 0; e < CG_UNROLL; ++e) {
+      for (int e = 0; e < U; ++e) {
         const size_t f = f0 + e * step;
         if (f >= k.npk) break;
 #pragma unroll
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_end(KBlas k) {
 // rr[1-j], ss = sum of the update's partials, iteration count and convergence
 // flag.  A system that converged in this iteration then still gets its P here,
 // which nothing reads.
-template <int PV>
+template <int PV, int U>
 __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
   using TV = RealOf<PV>;
   const int sys = blockIdx.y;
@@ -414,17 +420,18 @@ __global__ __launch_bounds__(BLAS_BS) void k_cg_pupdate(KBlas k) {
     }
   } else {
     using KV = Packet<PV>;
-    const size_t step = (size_t)k.nblk * BLAS_BS;
-    for (size_t f0 = (size_t)(blockIdx.x - first) * BLAS_BS + threadIdx.x; f0 < k.npk; f0 += CG_UNROLL * step) {
-      cplx<TV> r[CG_UNROLL][KV::CW], p[CG_UNROLL][KV::CW];
+    const size_t grid = (size_t)k.nblk * BLAS_BS, step = U == CG_SIDE ? BLAS_BS : grid;
+    const size_t b0 = (size_t)(blockIdx.x - first) * BLAS_BS * (U == CG_SIDE ? U : 1);
+    for (size_t f0 = b0 + threadIdx.x; f0 < k.npk; f0 += U * grid) {
+      cplx<TV> r[U][KV::CW], p[U][KV::CW];
 #pragma unroll
-      for (int e = 0; e < CG_UNROLL; ++e) {
+      for (int e = 0; e < U; ++e) {
         const size_t f = min(f0 + e * step, k.npk - 1);  // (past the end: loaded, not stored)
         KV::load(R, f, r[e]);
         KV::load(Pp, f, p[e]);
       }
 #pragma unroll
-      for (int e = 0; e < CG_UNROLL; ++e) {
+      for (int e = 0; e < U; ++e) {
         if (f0 + e * step >= k.npk) break;
 #pragma unroll
         for (int c = 0; c < KV::CW; ++c) {
@@ -544,7 +551,7 @@ wd_status blas_accum(const Geom &g, wd_prec pe, const VecRef &e, const VecRef &x
 }
 
 // Blocks per system of a CG recurrence over npk packets (FP16: sites): up to
-// CG_UNROLL items per thread.  Where every block first adds up the system's
+// CG_APART items per thread.  Where every block first adds up the system's
 // nparts partials, 2048 blocks of all systems together, with the one that ends
 // the iteration, are enough: 12 systems of 12^3x24 in FP32 take 11.8 ms, 12.2
 // with twice as many.  Without that list 2047 of each system: 12 systems of
@@ -556,6 +563,11 @@ static unsigned cg_blocks(const Geom &g, wd_prec pv, int nhalf, int nsys, unsign
   npk = (size_t)g.vpad * np * nhalf;
   const unsigned b = blocks_for((long)(pv == WD_F16 ? (size_t)g.vh * nhalf : npk));
   return std::min(b, nparts ? std::max(2u, BLAS_MAX_BLOCKS / (unsigned)nsys) - 1 : BLAS_MAX_BLOCKS - 1);
+}
+
+// Whether every thread of the grid has CG_SIDE packets.
+static bool cg_side(wd_prec pv, const KBlas &k) {
+  return pv != WD_F16 && k.npk >= (size_t)CG_SIDE * BLAS_BS * k.nblk;
 }
 
 // Whether a launch of its own ends the iteration right after the update: where
@@ -585,12 +597,17 @@ wd_status blas_cg_update(const Geom &g, wd_prec px, const VecRef &x, wd_prec pv,
   k.partials = cp.ss;
   cp.nss = k.nblk;
   dim3 grid(k.nblk, (unsigned)nsys);
+  const bool side = cg_side(pv, k);
+#define WD_CGU(PX, PV)                                                                                       \
+  if (side) hipLaunchKernelGGL((k_cg_update<PX, PV, CG_SIDE>), grid, dim3(BLAS_BS), 0, st, k);             \
+  else hipLaunchKernelGGL((k_cg_update<PX, PV, CG_APART>), grid, dim3(BLAS_BS), 0, st, k)
   switch (pv) {
-    case WD_F64: hipLaunchKernelGGL((k_cg_update<WD_F64, WD_F64>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_F32: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F32>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_F16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F16>), grid, dim3(BLAS_BS), 0, st, k); break;
-    case WD_BF16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_BF16>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_F64: WD_CGU(WD_F64, WD_F64); break;
+    case WD_F32: WD_CGU(WD_F32, WD_F32); break;
+    case WD_F16: hipLaunchKernelGGL((k_cg_update<WD_F32, WD_F16, CG_APART>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_BF16: WD_CGU(WD_F32, WD_BF16); break;
   }
+#undef WD_CGU
   WD_TRY(hip_check(hipGetLastError(), "cg_update launch"));
   if (!early_end(g, px, p.nhalf, nsys, cp.nnorm)) return WD_OK;
   k.ss_parts = cp.ss;
@@ -613,7 +630,17 @@ wd_status blas_cg_pupdate(const Geom &g, wd_prec pv, const VecRef &r, const VecR
   k.ss_parts = cp.ss;
   k.nss = cp.nss;
   dim3 grid(k.nblk + (cp.nss ? 1 : 0), (unsigned)nsys);
-  WD_DISPATCH_P(pv, k_cg_pupdate, grid, k, st);
+  const bool side = cg_side(pv, k);
+#define WD_CGP(PV)                                                                                 \
+  if (side) hipLaunchKernelGGL((k_cg_pupdate<PV, CG_SIDE>), grid, dim3(BLAS_BS), 0, st, k);      \
+  else hipLaunchKernelGGL((k_cg_pupdate<PV, CG_APART>), grid, dim3(BLAS_BS), 0, st, k)
+  switch (pv) {
+    case WD_F64: WD_CGP(WD_F64); break;
+    case WD_F32: WD_CGP(WD_F32); break;
+    case WD_F16: hipLaunchKernelGGL((k_cg_pupdate<WD_F16, CG_APART>), grid, dim3(BLAS_BS), 0, st, k); break;
+    case WD_BF16: WD_CGP(WD_BF16); break;
+  }
+#undef WD_CGP
   return hip_check(hipGetLastError(), "cg_pupdate launch");
 }
 
