@@ -600,7 +600,9 @@ __device__ __forceinline__ void dirac_split_finish(const KDirac &k, int i, char 
 #pragma unroll
     for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
   }
-  split_store<P, W, true, NORM>(out, i, o);
+  float m = 0.f;
+  if constexpr (P == WD_F16) m = split_max<W>(o, lds, lane);
+  split_store<P, W, true, NORM>(out, i, o, m);
   if constexpr (NORM)
     ((lds.template n2<DAG, W * CW + J>(lane) = (double)o[J].re * o[J].re + (double)o[J].im * o[J].im), ...);
 }
@@ -666,7 +668,10 @@ __global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDi
     case 3: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 3>(k, i, p, lane, lds); break; }
     case 4: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 4>(k, i, p, lane, lds); break; }
     case 5: if constexpr (NW > 3) { dirac_split_wave<P, DAG, EPI, NORM, LATE, 5>(k, i, p, lane, lds); break; }
-    default: __syncthreads(); break;
+    default:
+      __syncthreads();
+      split_max_rest<P>();
+      break;
   }
   if constexpr (NORM) {
     __syncthreads();
@@ -804,7 +809,9 @@ wd_status dirac_init(wd_gauge *g) {
 // us per launch, tile 4 against the march's default: FP64 8^3x16 4.5 / 64,
 // 16^3x32 23 / 69, 24^3x48 127 / 175 (no bricks), 16x32x32x96 274 / 321 (192
 // of 256 slots), 32^3x32 189 / 180 and 32^3x64 373 / 349 (all slots); FP32
-// 24^3x48 55 / 82, 32^3x64 185 / 174; BF16 (no staging) 32^3x64 143 / 213.
+// 24^3x48 55 / 82, 32^3x64 185 / 174; BF16 (no staging) 32^3x64 143 / 213; FP16
+// 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81 and 180 for a hop of each parity,
+// which WD_FULL without WD_ONE_PASS was).
 static bool dirac_uses_split(const wd_gauge *g, wd_prec prec) {
   if (!g->dirac_auto[prec]) return g->dirac_tile[prec] == 4;
   return g->dirac_tile[prec] != 3 || march_grid_of(g, prec).items < 0.95 * march_capacity(g, prec);

@@ -228,9 +228,10 @@ bool dslash_variant_ok(const Geom &G, int bs, int groups, int spl) {
 // 6.3 / 5.6.  Stores: cached with ranges, where the next kernel finds a small
 // field in the caches (12^3x24 FP32 4.6 against 4.8), streaming else (no
 // difference measured).
-// FP16 from 2^18 sites on: one thread per site.  There one wave alone adds a
-// site's twelve components (the scale needs them all), which a full device does
-// not hide behind a norm: defect correction on 24^3x48 18.7 against 19.5 ms.
+// FP16: 20^3x40 15.1 / 19.4, 24^3x48 29 / 38, 32^3x64 82 / 92, and a defect
+// correction 8.6 / 8.9, 14.1 / 16.1 and 38.6 / 39.7 ms.  (With all of a site's
+// components in one wave, for its scale, the corrections took 10.0, 19.5 and
+// 41 ms.)
 void dslash_default_variant(wd_gauge *g, int p) {
   const bool regions = g->geom.vh >= (1 << 18) && dslash_variant_ok(g->geom, SPLIT_SITES, 8);
   g->hop_block[p] = SPLIT_SITES;
@@ -242,12 +243,6 @@ void dslash_default_variant(wd_gauge *g, int p) {
   g->hop_spl[p] = 1;
   g->hop_stage[p] = 0;
   g->hop_split[p] = 1;
-  if (p == WD_F16 && g->geom.vh >= (1 << 18)) {
-    g->hop_block[p] = 256;
-    g->hop_groups[p] = 0;
-    g->hop_ntst[p] = 1;
-    g->hop_split[p] = 0;
-  }
 }
 
 wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hipStream_t st) {

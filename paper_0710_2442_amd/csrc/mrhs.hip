@@ -349,17 +349,25 @@ __device__ __forceinline__ void mrhs_split_hop16(const cplx<float> (&psi)[12], f
   mrhs_split_mul<WD_F16>(u, r2, h, q);
 }
 
+// The components per summing wave: as in the single hop, but FP16 keeps a site
+// in one wave, for the waves take turns (another one for each right-hand side)
+// and a barrier more would stop them all.
+template <int P>
+struct MrhsOut {
+  static constexpr int CW = P == WD_F16 ? 12 : SplitOut<P>::CW, NW = 12 / CW;
+};
+
 // The sums and the epilogue of wave slot W for one right-hand side (out at
 // byte offset off, epilogue operands x, y); returns the lane's |components|^2
 // when NORM.
 template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
 __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off, int i, int lane,
                                                     const SplitLds<P> &lds,
-                                                    cplx<RealOf<P>> (&x)[SplitOut<P>::CW],
-                                                    cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
+                                                    cplx<RealOf<P>> (&x)[MrhsOut<P>::CW],
+                                                    cplx<RealOf<P>> (&y)[MrhsOut<P>::CW],
                                                     std::integer_sequence<int, J...>) {
   using T = RealOf<P>;
-  constexpr int CW = SplitOut<P>::CW;
+  constexpr int CW = MrhsOut<P>::CW;
   cplx<T> o[CW];
   if (i < k.g.vh) {
     const T a = (T)k.a;
@@ -406,7 +414,7 @@ __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off
 template <int P, bool DAG, int EPI, bool NORM>
 __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) void k_dslash_mrhs_split(KMrhs m) {
   using T = RealOf<P>;
-  constexpr int NB = P == WD_F64 ? 1 : 2, NW = SplitOut<P>::NW, CW = SplitOut<P>::CW;
+  constexpr int NB = P == WD_F64 ? 1 : 2, NW = MrhsOut<P>::NW, CW = MrhsOut<P>::CW;
   __shared__ SplitLds<P> lds[NB];
   __shared__ double sred[NORM ? MR_CHUNK : 1][NW];
   const KDslash &k = m.k;

@@ -469,7 +469,13 @@ __device__ __forceinline__ double dslash_site(const KDslash &k, int i, Stage<Rea
 constexpr int SPLIT_SITES = 64;
 constexpr int SPLIT_BS = 512;
 template <int P>
-struct SplitLds {
+struct SplitMax {};
+template <>
+struct SplitMax<WD_F16> {
+  float mx[3][SPLIT_SITES];  // a site's largest number among each summing wave's components
+};
+template <int P>
+struct SplitLds : SplitMax<P> {
   cplx<RealOf<P>> g[8 * 6 * SPLIT_SITES];
   // |component C|^2 of an output (norm epilogue): in the time-hop element that
   // only component C adds up, free once it has
@@ -481,7 +487,7 @@ struct SplitLds {
 };
 // waves per SIMD the register budget is held to (a block adds 2 to each SIMD)
 constexpr int split_occ(int prec, int epi) {
-  return prec == WD_F64 ? 6 : prec == WD_F16 ? (epi == 2 ? 4 : 6) : (prec == WD_BF16 && epi == 2) ? 6 : 8;
+  return prec == WD_F64 ? 6 : 8;
 }
 
 // Checkerboard index of the neighbour of site i (parity p) in direction MU,
@@ -598,17 +604,18 @@ __device__ __forceinline__ cplx<RealOf<P>> split_sum(const SplitLds<P> &lds, int
 }
 
 // Components [0, 12) are summed by NW waves, CW components each: whole
-// 16-byte packets of the storage format (FP16 needs the site's largest
-// component for its scale, so one wave takes them all).
+// 16-byte packets of the storage format.  (FP16's scale is the site's largest
+// number: the waves exchange theirs in LDS before they store.)
 template <int P>
 struct SplitOut {
-  static constexpr int CW = (P == WD_F64 || P == WD_F32) ? 2 : (P == WD_BF16 ? 4 : 12);
+  static constexpr int CW = (P == WD_F64 || P == WD_F32) ? 2 : 4;
   static constexpr int NW = 12 / CW;
 };
 
-// Components W CW .. of a stored spinor (w = W may be a run-time value).
-template <int P>
-__device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
+// Components W CW .. of a stored spinor (w = W may be a run-time value); CW = 12
+// for FP16 where one wave sums them all.
+template <int P, int CW>
+__device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<RealOf<P>> (&x)[CW]) {
   if constexpr (P == WD_F64) {
     const v2d *p = (const v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * w;
     const v2d a = p[0], b = p[64];
@@ -620,14 +627,22 @@ __device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<
     x[1] = {v.z, v.w};
   } else if constexpr (P == WD_BF16) {
     Packet<WD_BF16>::unpack(*((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w), x);
-  } else {
+  } else if constexpr (CW == 12) {
     Spinor<P>::load(base, i, x);
+  } else {
+    const v4u v = *((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w);
+    const float n = Spinor<P>::scale(base, (size_t)i);
+    const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      x[j] = {n * f16_to_f32((uint16_t)(q[j] & 0xffffu)), n * f16_to_f32((uint16_t)(q[j] >> 16))};
   }
 }
 
-// Stores them; on return x holds the stored (rounded) values when NORM.
-template <int P, int W, bool NT, bool NORM>
-__device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
+// Stores them (FP16, CW = 4: with the site's scale m); on return x holds the
+// stored (rounded) values when NORM.
+template <int P, int W, bool NT, bool NORM, int CW>
+__device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (&x)[CW], float m = 0.f) {
   if constexpr (P == WD_F64) {
     v2d *p = (v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * W;
     st_policy<NT>(v2d{x[0].re, x[0].im}, p);
@@ -645,10 +660,41 @@ __device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (
       for (int j = 0; j < 4; ++j)
         x[j] = {bf16_to_f32((uint16_t)(w[j] & 0xffffu)), bf16_to_f32((uint16_t)(w[j] >> 16))};
     }
-  } else {
+  } else if constexpr (CW == 12) {
     Spinor<P>::template store<NT>(base, i, x);
     if constexpr (NORM) Spinor<P>::load(base, i, x);
+  } else {
+    const float inv = m > 0.f ? 1.0f / m : 0.f;
+    v4u *p = (v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i);
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      w[j] = (uint32_t)f32_to_f16(x[j].re * inv) | ((uint32_t)f32_to_f16(x[j].im * inv) << 16);
+    st_policy<NT>(v4u{w[0], w[1], w[2], w[3]}, p + 64 * W);
+    if constexpr (W == 0)
+      st_policy<NT>(m, (float *)((v4u *)base + ((size_t)i >> 6) * Spinor<P>::CHUNK + 3 * 64) + (i & 63));
+    if constexpr (NORM) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[j] = {m * f16_to_f32((uint16_t)(w[j] & 0xffffu)), m * f16_to_f32((uint16_t)(w[j] >> 16))};
+    }
   }
+}
+
+// FP16: the site's largest number, from the components of the NW summing waves
+// (a barrier of the block, which the other waves join with split_max_rest).
+template <int W>
+__device__ __forceinline__ float split_max(const cplx<float> (&x)[4], SplitLds<WD_F16> &lds, int lane) {
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) m = fmaxf(m, fmaxf(fabsf(x[j].re), fabsf(x[j].im)));
+  lds.mx[W][lane] = m;
+  __syncthreads();
+  return fmaxf(fmaxf(lds.mx[0][lane], lds.mx[1][lane]), lds.mx[2][lane]);
+}
+template <int P>
+__device__ __forceinline__ void split_max_rest() {
+  if constexpr (P == WD_F16) __syncthreads();
 }
 
 // The epilogue of wave W's components of site i (see dslash_site).
@@ -673,8 +719,10 @@ __device__ __forceinline__ void split_finish_w(const KDslash &k, int i, int lane
 #pragma unroll
     for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
   }
-  if (k.nt_store) split_store<P, W, true, NORM>(k.out, i, o);
-  else split_store<P, W, false, NORM>(k.out, i, o);
+  float m = 0.f;
+  if constexpr (P == WD_F16) m = split_max<W>(o, lds, lane);
+  if (k.nt_store) split_store<P, W, true, NORM>(k.out, i, o, m);
+  else split_store<P, W, false, NORM>(k.out, i, o, m);
   if constexpr (NORM)
     ((lds.template n2<DAG, W * CW + J>(lane) = (double)o[J].re * o[J].re + (double)o[J].im * o[J].im), ...);
 }
@@ -726,7 +774,10 @@ __device__ __forceinline__ double dslash_split_tile(const KDslash &k, int tile, 
     case 3: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 3>(k, i, lane, lds); break; }
     case 4: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 4>(k, i, lane, lds); break; }
     case 5: if constexpr (NW > 3) { split_wave<P, DAG, EPI, NORM, 5>(k, i, lane, lds); break; }
-    default: __syncthreads(); break;
+    default:
+      __syncthreads();
+      split_max_rest<P>();
+      break;
   }
   double nrm = 0.0;
   if constexpr (NORM) {
