@@ -419,13 +419,14 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs,
                               int *groups, int *rpl, double *us);
 
 /* Set / read the multi-RHS hop variant used for precision prec: block (512,
- * the default, with rpl 1..16, see above: until a variant is set or tuned, rpl
- * counts as the most and small lattices take fewer; FP64: 16; others 64, 128
+ * the default, with rpl 1..16, see above; the values of a new handle, rpl 12 in
+ * its order, are the most, and small lattices take fewer; FP64: 16; others 64, 128
  * or 256 sites), groups (block -> tile order, as for
  * wd_set_dslash_variant) and rpl (FP64: 4; others 1..16 right-hand sides per
  * lane).  WD_ERR_ARG for a value
  * outside these or a variant that does not fit the lattice.  The variants
- * compute the same bytes; only the time differs. */
+ * compute the same bytes; only the time differs.  What get returns can be set
+ * again without a change. */
 wd_status wd_set_dslash_mrhs_variant(wd_gauge *g, wd_prec prec, int block, int groups, int rpl);
 wd_status wd_get_dslash_mrhs_variant(const wd_gauge *g, wd_prec prec, int *block, int *groups, int *rpl);
 
@@ -494,11 +495,16 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
 /* Set / read the one-launch D_W variant of precision prec: slices 0 (the
  * default: the shortest range of 8, 16, ... for which every work item is
  * resident on the device at once) or 1..L4, tile 0, 2, 3 or 4 as above (the
- * default: 3 where it fits, else 2 where bricks fit, else 0).  While neither
- * was set nor tuned, the default runs as tile 4 on lattices whose tile-3
- * ranges do not fill the device.
+ * default: 3 where it fits, else 2 where bricks fit, else 0).  The default pair
+ * (slices 0 and that tile) runs as tile 4 on lattices whose tile-3 ranges do
+ * not fill the device; with slices given, or another tile, the launch is what
+ * it says.  What get returns can be set again without a change.
  * WD_ERR_ARG for a value outside these or a brick that does not fit the
- * lattice.  The variants compute the same bytes; only the time differs. */
+ * lattice.  With WD_ONE_PASS the variants compute the same bytes; only the time
+ * differs.  The solvers on full fields (WD_SOLVER_CGLS_FULL, WD_SOLVER_FGCR and
+ * the FP64 residuals) take tile 4 with the hops added first, so there a march
+ * and tile 4 differ by rounding.  WD_FULL without WD_ONE_PASS runs the same
+ * launch whatever this or the hop's variant is. */
 wd_status wd_set_dirac_variant(wd_gauge *g, wd_prec prec, int slices, int tile);
 wd_status wd_get_dirac_variant(const wd_gauge *g, wd_prec prec, int *slices, int *tile);
 

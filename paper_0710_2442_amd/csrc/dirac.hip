@@ -785,7 +785,6 @@ bool dirac_variant_ok(const wd_gauge *g, wd_prec prec, int slices, int tile) {
 wd_status dirac_init(wd_gauge *g) {
   // default tiles: bricks staged in LDS where they fit (FP64, FP32), else bricks, else consecutive sites
   for (int p = 0; p < 4; ++p) {
-    g->dirac_auto[p] = 1;
     g->dirac_slices[p] = 0;
     g->dirac_tile[p] = march_brick_n2(g->geom) ? 2 : 0;
   }
@@ -800,11 +799,12 @@ wd_status dirac_init(wd_gauge *g) {
     g->dirac_bpc_lds[WD_F32] = march_blocks_per_cu<WD_F32, true>(march_lds_bytes(g->geom, WD_F32));
   for (int p = 0; p < 2; ++p)
     if (g->dirac_bpc_lds[p] > 0) g->dirac_tile[p] = 3;
+  for (int p = 0; p < 4; ++p) g->dirac_tile0[p] = g->dirac_tile[p];
   return WD_OK;
 }
 
-// A handle whose variant was neither set nor tuned runs tile 4 unless the
-// staged bricks fit and fill the device (one block on at least 95% of the
+// The default variant (slices 0 and the default tile, whether set or never
+// touched) runs tile 4 unless the staged bricks fit and fill the device (one block on at least 95% of the
 // resident slots): then the march, which fetches nothing twice, is ahead.
 // us per launch, tile 4 against the march's default: FP64 8^3x16 4.5 / 64,
 // 16^3x32 23 / 69, 24^3x48 127 / 175 (no bricks), 16x32x32x96 274 / 321 (192
@@ -813,7 +813,7 @@ wd_status dirac_init(wd_gauge *g) {
 // 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81 and 180 for a hop of each parity,
 // which WD_FULL without WD_ONE_PASS was).
 static bool dirac_uses_split(const wd_gauge *g, wd_prec prec) {
-  if (!g->dirac_auto[prec]) return g->dirac_tile[prec] == 4;
+  if (g->dirac_slices[prec] != 0 || g->dirac_tile[prec] != g->dirac_tile0[prec]) return g->dirac_tile[prec] == 4;
   return g->dirac_tile[prec] != 3 || march_grid_of(g, prec).items < 0.95 * march_capacity(g, prec);
 }
 

@@ -681,14 +681,13 @@ static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
 // against 166 with regions); from 2^18 sites in FP64 and FP32 regions of each
 // slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 540 / 573, 32^3x64
 // 1610 / 1777).
+constexpr int MRHS_SPLIT_RPL = 12;
 void mrhs_default_variant(wd_gauge *g, int p) {
   const Geom &G = g->geom;
-  g->mrhs_auto[p] = 1;
-  g->mrhs_rpl[p] = 12;
+  g->mrhs_rpl[p] = MRHS_SPLIT_RPL;
   g->mrhs_block[p] = SPLIT_BS;
   g->mrhs_groups[p] = SPLIT_RANGES;
   if (p == WD_F16 && G.vpad / SPLIT_SITES >= 512) {
-    g->mrhs_auto[p] = 0;
     g->mrhs_rpl[p] = 4;
     g->mrhs_block[p] = 128;
     g->mrhs_groups[p] = dslash_variant_ok(G, 128, 4) ? 4 : 0;
@@ -696,15 +695,16 @@ void mrhs_default_variant(wd_gauge *g, int p) {
     if (dslash_variant_ok(G, SPLIT_SITES, 8)) g->mrhs_groups[p] = 8;
     else if (p <= WD_F32 && dslash_variant_ok(G, SPLIT_SITES, 4)) g->mrhs_groups[p] = 4;
   }
+  g->mrhs_groups0[p] = g->mrhs_groups[p];
 }
 
-// Right-hand sides per block of a default variant: chunks are added until the
-// blocks are two a CU, for fewer would leave the chain of right-hand sides as
+// Right-hand sides per block.  The default variant (its block, order and rpl,
+// whether set or never touched) adds chunks until the blocks are two a CU, for fewer would leave the chain of right-hand sides as
 // the run time: 8^4 (32 tiles), 12 right-hand sides BF16: 3 per block 6.7 us,
 // 12 per block 15.2; 16^4 (512 tiles) FP64: 12 per block 52, 4 per block 62.
 static int mrhs_split_rpl(const wd_gauge *g, int prec, int nrhs, int ntiles) {
   const int most = g->mrhs_rpl[prec];
-  if (!g->mrhs_auto[prec]) return most;
+  if (most != MRHS_SPLIT_RPL || g->mrhs_groups[prec] != g->mrhs_groups0[prec]) return most;
   const int chunks = std::max((nrhs + most - 1) / most, std::min(nrhs, (512 + ntiles - 1) / ntiles));
   return (nrhs + chunks - 1) / chunks;
 }

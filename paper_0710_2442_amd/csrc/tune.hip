@@ -199,7 +199,6 @@ wd_status wd_set_dslash_mrhs_variant(wd_gauge *g, wd_prec prec, int block, int g
   g->mrhs_block[prec] = block;
   g->mrhs_groups[prec] = groups;
   g->mrhs_rpl[prec] = rpl;
-  g->mrhs_auto[prec] = 0;
   return WD_OK;
 }
 
@@ -415,7 +414,6 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
   wd_status rc = WD_OK;
   int *flag = nullptr;
   const int save = g->mrhs_groups[prec], save_b = g->mrhs_block[prec], save_r = g->mrhs_rpl[prec];
-  const int save_a = g->mrhs_auto[prec];
   const int ref_b = (prec == WD_F64) ? 16 : 128;
   int best_g = 0, best_b = ref_b, best_r = 4;
   double best_us = 1e30;
@@ -438,7 +436,6 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
     }
     if ((rc = hip_check(hipEventCreate(&e0), "event")) != WD_OK) break;
     if ((rc = hip_check(hipEventCreate(&e1), "event")) != WD_OK) break;
-    g->mrhs_auto[prec] = 0;
     g->mrhs_groups[prec] = 0;
     g->mrhs_block[prec] = ref_b;
     g->mrhs_rpl[prec] = 4;
@@ -497,7 +494,6 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
   g->mrhs_groups[prec] = (rc == WD_OK) ? best_g : save;
   g->mrhs_block[prec] = (rc == WD_OK) ? best_b : save_b;
   g->mrhs_rpl[prec] = (rc == WD_OK) ? best_r : save_r;
-  g->mrhs_auto[prec] = (rc == WD_OK) ? 0 : save_a;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (in) (void)hipFree(in);
@@ -521,7 +517,6 @@ wd_status wd_set_dirac_variant(wd_gauge *g, wd_prec prec, int slices, int tile) 
                      tile, g->dims[0], g->dims[1], g->dims[2], g->dims[3]);
   g->dirac_slices[prec] = slices;
   g->dirac_tile[prec] = tile;
-  g->dirac_auto[prec] = 0;
   return WD_OK;
 }
 
@@ -557,7 +552,7 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
   hipEvent_t e0 = nullptr, e1 = nullptr;
   wd_status rc = WD_OK;
   int *flag = nullptr;
-  const int save_s = g->dirac_slices[prec], save_t = g->dirac_tile[prec], save_a = g->dirac_auto[prec];
+  const int save_s = g->dirac_slices[prec], save_t = g->dirac_tile[prec];
   int best_s = save_s, best_t = save_t;
   double best_us = 1e30;
   DiracArgs a;
@@ -597,7 +592,6 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
     for (const auto &c : cands) {
       g->dirac_slices[prec] = c[0];
       g->dirac_tile[prec] = c[1];
-      g->dirac_auto[prec] = 0;
       if ((rc = hip_check(hipMemsetAsync(cand, 0xff, fb, st), "memset")) != WD_OK) break;
       if ((rc = launch_dirac(g, prec, a, st)) != WD_OK) break;
       bool same = false;
@@ -619,7 +613,6 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
   } while (0);
   g->dirac_slices[prec] = (rc == WD_OK) ? best_s : save_s;
   g->dirac_tile[prec] = (rc == WD_OK) ? best_t : save_t;
-  g->dirac_auto[prec] = (rc == WD_OK) ? 0 : save_a;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (in) (void)hipFree(in);

@@ -90,7 +90,7 @@ struct wd_gauge {
   int dirac_bpc_lds[2];    // FP64, FP32: the same for its LDS-staged form (0: does not fit)
   int dirac_slices[4];     // per precision: time slices per range of the one-launch D_W (0: from occupancy)
   int dirac_tile[4];       // per precision: its tiles, 2 = bricks of L1 x n2 x 2 sites, 0 = consecutive sites
-  int dirac_auto[4];       // per precision: 1 = variant neither set nor tuned (tile 4 by the lattice's size)
+  int dirac_tile0[4];      // per precision: the default tile; with slices 0, tile 4 by the lattice's size
   hipStream_t stream;      // caller's stream for dslash / pack
   hipStream_t own_stream;  // library stream for synchronous solves (default priority)
   void *links64;
@@ -102,7 +102,7 @@ struct wd_gauge {
   int mrhs_groups[4];      // per precision: block -> tile order of the multi-RHS hop
   int mrhs_block[4];       // per precision: sites per block of the FP32/16-bit multi-RHS hop
   int mrhs_rpl[4];         // per precision: right-hand sides per lane of that kernel
-  int mrhs_auto[4];        // per precision: 1 = variant neither set nor tuned (rpl by the lattice's size)
+  int mrhs_groups0[4];     // per precision: the default order; with the default block and rpl, rpl by the lattice's size
   int hop_lds[4];          // per precision: dynamic LDS bytes per block (caps blocks per CU)
   int hop_pre[4];          // per precision: 1 = links loaded before the first hop (not FP64)
   int hop_spl[4];          // per precision: output sites per lane along x4 (1, 2, 4)
