@@ -632,7 +632,7 @@ __device__ __forceinline__ void dirac_split_wave(const KDirac &k, int i, int p, 
 
 // EPI 1: out = X + a H in;  2: out = X - Y + a H in.
 template <int P, bool DAG, int EPI, bool NORM, bool LATE>
-__global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dirac_split(KDirac k) {
+__global__ __launch_bounds__(SPLIT_BS, split_occ(P)) void k_dirac_split(KDirac k) {
   __shared__ SplitLds<P> lds;
   if (k.skip && *k.skip) return;
   const int b = (int)blockIdx.x, r = b & 7, q = b >> 3, p = q & 1;
@@ -863,7 +863,7 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
 #undef WD_DP
     WD_TRY(hip_check(hipGetLastError(), "dirac launch"));
     if (norm && !leave_partials(a.red, 2u * (unsigned)k.nt))
-      return launch_finish_sums(k.partials, 2u * (unsigned)k.nt, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
+      return launch_finish_sums(k.partials, 2u * (unsigned)k.nt, 1, a.norm_out, 1, 0, a.skip, 1, st);
     return WD_OK;
   }
   const MarchGrid mg = march_grid_of(g, prec);
@@ -902,7 +902,7 @@ wd_status launch_dirac(const wd_gauge *g, wd_prec prec, const DiracArgs &a, hipS
 #undef WD_DP
   WD_TRY(hip_check(hipGetLastError(), "dirac launch"));
   if (norm && !leave_partials(a.red, nblk))
-    return launch_finish_sums(k.partials, nblk, 1, a.norm_out, 1, a.norm_accumulate, a.skip, 1, st);
+    return launch_finish_sums(k.partials, nblk, 1, a.norm_out, 1, 0, a.skip, 1, st);
   return WD_OK;
 }
 

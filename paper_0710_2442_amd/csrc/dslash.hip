@@ -99,7 +99,7 @@ __global__ __launch_bounds__(512) void k_dslash_stage(KDslash k) {
 
 // One wave per hop direction (see wd_hop.h).
 template <int P, bool DAG, int EPI, bool NORM>
-__global__ __launch_bounds__(SPLIT_BS, split_occ(P, EPI)) void k_dslash_split(KDslash k) {
+__global__ __launch_bounds__(SPLIT_BS, split_occ(P)) void k_dslash_split(KDslash k) {
   __shared__ SplitLds<P> lds;
   if (k.skip && *k.skip) return;
   const int tile = split_tile_of(k, (int)blockIdx.x);
@@ -251,7 +251,6 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
   k.out = (char *)a.out;
   k.X = (const char *)a.X;
   k.a = a.a;
-  k.norm_out = a.norm_out;
   k.skip = a.skip;
   k.partials = a.red.partials;
   const int epi = a.X ? 1 : 0;
@@ -288,7 +287,7 @@ wd_status launch_dslash(const wd_gauge *g, wd_prec prec, const DslashArgs &a, hi
   }
   WD_TRY(hip_check(hipGetLastError(), "dslash launch"));
   if (norm && !leave_partials(a.red, nblk))
-    return launch_finish_sums(k.partials, nblk, 1, k.norm_out, 1, 0, k.skip, 1, st);
+    return launch_finish_sums(k.partials, nblk, 1, a.norm_out, 1, 0, k.skip, 1, st);
   return WD_OK;
 }
 

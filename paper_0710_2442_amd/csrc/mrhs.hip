@@ -16,7 +16,6 @@ struct KMrhs {
   KDslash k;
   int nrhs;
   size_t rhs_stride;   // bytes between right-hand sides (all operands)
-  int norm_stride;     // doubles between consecutive RHS norm slots
   int skip_stride;     // ints between consecutive RHS skip flags
   int rpl;             // right-hand sides per lane (FP32-arithmetic kernel)
   int nx3;             // > 0: box order with tile-major RHS chunks (mrhs_box)
@@ -273,6 +272,20 @@ struct NbRaw16 {
     if constexpr (P == WD_F16) return {n * f16_to_f32((uint16_t)(w & 0xffffu)), n * f16_to_f32((uint16_t)(w >> 16))};
     else return {bf16_to_f32((uint16_t)(w & 0xffffu)), bf16_to_f32((uint16_t)(w >> 16))};
   }
+};
+template <>
+struct NbRaw<WD_F16> : NbRaw16<WD_F16> {
+  // the spinor, or in its first 6 components the half that was loaded
+  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool lower) const {
+    s[0] = num(lower ? a.z : a.x); s[1] = num(lower ? a.w : a.y);
+    s[2] = num(lower ? b.x : a.z); s[3] = num(lower ? b.y : a.w);
+    s[4] = num(lower ? b.z : b.x); s[5] = num(lower ? b.w : b.y);
+    s[6] = num(b.z); s[7] = num(b.w);
+    s[8] = num(c.x); s[9] = num(c.y); s[10] = num(c.z); s[11] = num(c.w);
+  }
+};
+template <>
+struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {
   __device__ __forceinline__ void whole(cplx<float> (&s)[12]) const {
     s[0] = num(a.x); s[1] = num(a.y); s[2] = num(a.z); s[3] = num(a.w);
     s[4] = num(b.x); s[5] = num(b.y); s[6] = num(b.z); s[7] = num(b.w);
@@ -286,19 +299,7 @@ struct NbRaw16 {
       h[0] = num(a.x); h[1] = num(a.y); h[2] = num(a.z); h[3] = num(a.w); h[4] = num(b.x); h[5] = num(b.y);
     }
   }
-  // the spinor, or in its first 6 components the half that was loaded
-  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool lower) const {
-    s[0] = num(lower ? a.z : a.x); s[1] = num(lower ? a.w : a.y);
-    s[2] = num(lower ? b.x : a.z); s[3] = num(lower ? b.y : a.w);
-    s[4] = num(lower ? b.z : b.x); s[5] = num(lower ? b.w : b.y);
-    s[6] = num(b.z); s[7] = num(b.w);
-    s[8] = num(c.x); s[9] = num(c.y); s[10] = num(c.z); s[11] = num(c.w);
-  }
 };
-template <>
-struct NbRaw<WD_F16> : NbRaw16<WD_F16> {};
-template <>
-struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {};
 
 // h = the half spinor that hop D projects from the loaded neighbour.
 template <int P, bool DAG, int D>
@@ -719,13 +720,10 @@ wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs 
   m.k.X = (const char *)a.X;
   m.k.Y = (const char *)a.Y;
   m.k.a = a.a;
-  m.k.norm_out = a.norm_out;
-  m.k.norm_accumulate = a.norm_accumulate;
   m.k.skip = a.skip;
   m.k.partials = a.red.partials;
   m.nrhs = a.nrhs;
   m.rhs_stride = a.rhs_stride ? a.rhs_stride : half_bytes(g->geom, prec);
-  m.norm_stride = a.norm_stride;
   m.skip_stride = a.skip_stride;
   const bool norm = a.norm_out != nullptr;
   if (norm && !m.k.partials) return set_error(WD_ERR_ARG, "dslash_mrhs norm: no reduction buffer");
@@ -785,8 +783,8 @@ wd_status launch_dslash_mrhs_ex(const wd_gauge *g, wd_prec prec, const MrhsArgs 
   WD_TRY(hip_check(hipGetLastError(), "dslash_mrhs launch"));
   const unsigned nparts = m.ntiles > 0 ? (unsigned)m.ntiles : grid.x;
   if (norm && !leave_partials(a.red, nparts))
-    return launch_finish_sums(m.k.partials, nparts, a.nrhs, m.k.norm_out,
-                              m.norm_stride, m.k.norm_accumulate, m.k.skip, m.skip_stride, st);
+    return launch_finish_sums(m.k.partials, nparts, a.nrhs, a.norm_out,
+                              a.norm_stride, a.norm_accumulate, m.k.skip, m.skip_stride, st);
   return WD_OK;
 }
 

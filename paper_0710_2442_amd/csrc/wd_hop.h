@@ -20,8 +20,6 @@ struct KDslash {
   const char *links;  // hop-link arrays of this output parity
   double a;
   int parity;
-  int norm_accumulate;
-  double *norm_out;
   const int *skip;
   double *partials;
   // block -> tile mapping (see tile_of)
@@ -486,7 +484,7 @@ struct SplitLds : SplitMax<P> {
   }
 };
 // waves per SIMD the register budget is held to (a block adds 2 to each SIMD)
-constexpr int split_occ(int prec, int epi) {
+constexpr int split_occ(int prec) {
   return prec == WD_F64 ? 6 : 8;
 }
 
@@ -697,11 +695,10 @@ __device__ __forceinline__ void split_max_rest() {
   if constexpr (P == WD_F16) __syncthreads();
 }
 
-// The epilogue of wave W's components of site i (see dslash_site).
+// The epilogue of wave W's components of site i (EPI 0 and 1 of dslash_site).
 template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
 __device__ __forceinline__ void split_finish_w(const KDslash &k, int i, int lane, SplitLds<P> &lds,
                                                const cplx<RealOf<P>> (&x)[SplitOut<P>::CW],
-                                               const cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
                                                std::integer_sequence<int, J...>) {
   using T = RealOf<P>;
   constexpr int CW = SplitOut<P>::CW;
@@ -713,7 +710,6 @@ __device__ __forceinline__ void split_finish_w(const KDslash &k, int i, int lane
     for (int j = 0; j < CW; ++j) {
       o[j] = a * o[j];
       if constexpr (EPI >= 1) o[j] = o[j] + x[j];
-      if constexpr (EPI == 2) o[j] = o[j] - y[j];
     }
   } else {
 #pragma unroll
@@ -731,14 +727,12 @@ template <int P, bool DAG, int EPI, bool NORM, int W>
 __device__ __forceinline__ void split_wave(const KDslash &k, int i, int lane, SplitLds<P> &lds) {
   using T = RealOf<P>;
   constexpr int CW = SplitOut<P>::CW;
-  // the epilogue operands are loaded before the barrier
-  cplx<T> x[CW], y[CW];
+  // the epilogue operand is loaded before the barrier
+  cplx<T> x[CW];
   if constexpr (EPI >= 1)
     if (i < k.g.vh) split_load<P>(k.X, i, W, x);
-  if constexpr (EPI == 2)
-    if (i < k.g.vh) split_load<P>(k.Y, i, W, y);
   __syncthreads();
-  split_finish_w<P, DAG, EPI, NORM, W>(k, i, lane, lds, x, y, std::make_integer_sequence<int, CW>{});
+  split_finish_w<P, DAG, EPI, NORM, W>(k, i, lane, lds, x, std::make_integer_sequence<int, CW>{});
 }
 
 template <int P, bool DAG, int... C>

@@ -187,7 +187,6 @@ struct DiracArgs {
   double a = 1.0;
   int dagger = 0;
   double *norm_out = nullptr;
-  int norm_accumulate = 0;
   const int *skip = nullptr;  // device flag: when set, the launch does nothing
   RedBuf red{};
 };
