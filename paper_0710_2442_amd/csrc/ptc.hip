@@ -1318,6 +1318,8 @@ __global__ __launch_bounds__(256) void k_ptc_links_bf16(const char *links32, siz
 }  // namespace wd
 
 // ============================================================ host side
+constexpr int TRAIN_BUFS = 16;  // most buffers of a handle: 1, 2, 4 .. 1024 samples, and a few where memory was short
+
 struct wd_ptc {
   const wd_gauge *g;
   float *Wc;       // device, the parameters: chiral-basis weights, 1152 floats
@@ -1329,10 +1331,12 @@ struct wd_ptc {
   wd_prec act;     // activation storage (WD_BF16 or WD_F32)
   void *x0, *y1;   // input and hidden layer of one application
   // training: the input, hidden layer and both gradients of tcap samples (one
-  // allocation, made for the first batch and for a larger one), and the
-  // partial sums of the weight gradients (both layers) and of the loss
-  char *tbuf;
-  int tcap;
+  // allocation; one sample from the start, more for the first larger batch), and
+  // the partial sums of the weight gradients (both layers) and of the loss.  A
+  // captured step may hold the address of a buffer that a later batch outgrew,
+  // so those are kept with the handle (tbuf[0 .. ntbuf), the last one in use).
+  char *tbuf[TRAIN_BUFS];
+  int ntbuf, tcap;
   double *partials;                // [layer][WG_BLOCKS][576]
   double *scal;                    // [0] loss; [64..] its partials, one per block of the layer launch
   // FP16-product inference (made on first use): FP16 hop links of both
@@ -1641,16 +1645,25 @@ static size_t train_sample_bytes(const wd_ptc *n) {
   return (n->act == WD_F32 ? 0 : fa) + 2 * fa + 3 * f32;
 }
 // The samples that go through the kernels together: all of a batch that the
-// workspace holds.  Where memory is short it is halved down to one sample.
-static wd_status train_reserve(wd_ptc *n, int want) {
-  want = std::min(want, train_samples(n->g->geom));
+// workspace holds.  It grows by powers of two (all buffers together take about
+// twice the largest).  Where memory is short the growth is halved, and on a
+// stream that is being captured, where nothing can be allocated, there is none.
+static wd_status train_reserve(wd_ptc *n, int want, hipStream_t st) {
+  const int most = train_samples(n->g->geom);
+  want = std::min(want, most);
   if (n->tcap >= want) return WD_OK;
-  for (; want > n->tcap; want /= 2) {
+  if (n->tcap > 0) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError(), cs = hipStreamCaptureStatusActive;
+    if (cs != hipStreamCaptureStatusNone) return WD_OK;
+  }
+  int cap = 1;
+  while (cap < want) cap *= 2;
+  for (cap = std::min(cap, most); cap > n->tcap && n->ntbuf < TRAIN_BUFS; cap /= 2) {
     char *p = nullptr;
-    if (hipMalloc(&p, want * train_sample_bytes(n)) == hipSuccess) {
-      if (n->tbuf) (void)hipFree(n->tbuf);
-      n->tbuf = p;
-      n->tcap = want;
+    if (hipMalloc(&p, cap * train_sample_bytes(n)) == hipSuccess) {
+      n->tbuf[n->ntbuf++] = p;
+      n->tcap = cap;
       return WD_OK;
     }
     (void)hipGetLastError();
@@ -1660,9 +1673,10 @@ static wd_status train_reserve(wd_ptc *n, int want) {
 
 static void ptc_free(wd_ptc *n) {
   void *ps[] = {n->Wc, n->gradc, n->W,    n->Wadj,    n->m,   n->v,     n->x0,     n->y1,
-                n->tbuf, n->partials, n->scal, n->links16, n->W16, n->hnorm, n->linksb, n->tabs};
+                n->partials, n->scal, n->links16, n->W16, n->hnorm, n->linksb, n->tabs};
   for (void *p : ps)
     if (p) (void)hipFree(p);
+  for (int q = 0; q < n->ntbuf; ++q) (void)hipFree(n->tbuf[q]);
   delete n;
 }
 
@@ -1672,9 +1686,9 @@ static void ptc_free(wd_ptc *n) {
 static wd_status ptc_loss_grad(wd_ptc *n, const void *r, const void *e, int B, hipStream_t st) {
   const Geom &G = n->g->geom;
   const size_t fa = 2 * half_bytes(G, n->act), f32 = 2 * half_bytes(G, WD_F32);
-  WD_TRY(train_reserve(n, B));
+  WD_TRY(train_reserve(n, B, st));
   const int S = std::min(B, n->tcap);  // samples per launch
-  char *gy2 = n->tbuf, *gy1 = gy2 + S * f32, *y1 = gy1 + 2 * S * f32, *x0 = y1 + 2 * S * fa;
+  char *gy2 = n->tbuf[n->ntbuf - 1], *gy1 = gy2 + S * f32, *y1 = gy1 + 2 * S * f32, *x0 = y1 + 2 * S * fa;
   const long units = (long)S * 2 * ((G.vh + 63) / 64);
   const unsigned nblk = (unsigned)std::min<long>((units + PTC_BS / 64 - 1) / (PTC_BS / 64), WG_BLOCKS);
   hipLaunchKernelGGL(k_ptc_adjoint, dim3(1), dim3(64), 0, st, (const float *)(n->W + 576), n->Wadj, 1, 2);
@@ -1733,6 +1747,7 @@ wd_status wd_ptc_create(const wd_gauge *g, const float *W_host, wd_prec act_prec
   n->g = g;
   n->act = act_prec;
   wd_status rc = ptc_alloc(n);
+  if (rc == WD_OK) rc = train_reserve(n, 1, g->stream);
   if (rc == WD_OK) rc = hip_check(hipMemcpy(n->Wc, W_host, PTC_NW * sizeof(float), hipMemcpyHostToDevice), "weights");
   if (rc == WD_OK) rc = ptc_sync_weights(n, g->stream);
   if (rc == WD_OK) rc = hip_check(hipStreamSynchronize(g->stream), "weights");
