@@ -409,7 +409,7 @@ wd_status wd_tune_dslash(wd_gauge *g, wd_prec prec, const char *cache_path,
  * tuned: block size (64, 128, 256 sites), rpl (1..16) and block -> tile
  * order (groups as above).  FP64: fixed 16-site x RHS tiles; tuned: tile
  * order.  Candidates are checked byte for byte against the linear variant,
- * then timed; the fastest is kept in the handle.  In every precision also
+ * then timed, H and H^dag in turn; the fastest is kept in the handle.  In every precision also
  * block 512: one wave per hop direction, 64 sites per block, rpl right-hand
  * sides one after the other, orders as above or WD_ORDER_RANGES.  cache_path
  * and force as for wd_tune_dslash (the key adds nrhs; the cache line's third field is

@@ -479,7 +479,9 @@ wd_status wd_tune_dslash_mrhs(wd_gauge *g, wd_prec prec, int nrhs, const char *c
       const int reps = 6;
       for (int w = 0; w < 2; ++w) (void)launch_dslash_mrhs(g, prec, in, cand, 1.0, WD_EVEN, 0, nrhs, st);
       (void)hipEventRecord(e0, st);
-      for (int r = 0; r < reps; ++r) (void)launch_dslash_mrhs(g, prec, in, cand, 1.0, WD_EVEN, 0, nrhs, st);
+      // H and H^dag in turn, as a solve applies them (24^3x48, 12 right-hand sides
+      // in BF16: a variant ahead by 2% in H was 5% behind in the solve)
+      for (int r = 0; r < reps; ++r) (void)launch_dslash_mrhs(g, prec, in, cand, 1.0, WD_EVEN, r & 1, nrhs, st);
       (void)hipEventRecord(e1, st);
       if ((rc = hip_check(hipEventSynchronize(e1), "tune timing")) != WD_OK) break;
       float ms = 0.f;
