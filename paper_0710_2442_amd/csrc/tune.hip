@@ -599,8 +599,8 @@ wd_status wd_tune_dirac(wd_gauge *g, wd_prec prec, const char *cache_path, int f
       bool same = false;
       if ((rc = same_bytes(ref, cand, fb, flag, same, st)) != WD_OK) break;
       if (!same) continue;
-      const int reps = 6;
-      for (int w = 0; w < 2; ++w) (void)launch_dirac(g, prec, a, st);
+      const int reps = 24;  // the march settles over some launches: FP32 32^3x64 194 us over 6, 177 over 20
+      for (int w = 0; w < 6; ++w) (void)launch_dirac(g, prec, a, st);
       (void)hipEventRecord(e0, st);
       for (int r = 0; r < reps; ++r) (void)launch_dirac(g, prec, a, st);
       (void)hipEventRecord(e1, st);
