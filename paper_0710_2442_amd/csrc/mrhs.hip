@@ -272,20 +272,6 @@ struct NbRaw16 {
     if constexpr (P == WD_F16) return {n * f16_to_f32((uint16_t)(w & 0xffffu)), n * f16_to_f32((uint16_t)(w >> 16))};
     else return {bf16_to_f32((uint16_t)(w & 0xffffu)), bf16_to_f32((uint16_t)(w >> 16))};
   }
-};
-template <>
-struct NbRaw<WD_F16> : NbRaw16<WD_F16> {
-  // the spinor, or in its first 6 components the half that was loaded
-  __device__ __forceinline__ void unpack(cplx<float> (&s)[12], bool lower) const {
-    s[0] = num(lower ? a.z : a.x); s[1] = num(lower ? a.w : a.y);
-    s[2] = num(lower ? b.x : a.z); s[3] = num(lower ? b.y : a.w);
-    s[4] = num(lower ? b.z : b.x); s[5] = num(lower ? b.w : b.y);
-    s[6] = num(b.z); s[7] = num(b.w);
-    s[8] = num(c.x); s[9] = num(c.y); s[10] = num(c.z); s[11] = num(c.w);
-  }
-};
-template <>
-struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {
   __device__ __forceinline__ void whole(cplx<float> (&s)[12]) const {
     s[0] = num(a.x); s[1] = num(a.y); s[2] = num(a.z); s[3] = num(a.w);
     s[4] = num(b.x); s[5] = num(b.y); s[6] = num(b.z); s[7] = num(b.w);
@@ -300,6 +286,10 @@ struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {
     }
   }
 };
+template <>
+struct NbRaw<WD_F16> : NbRaw16<WD_F16> {};
+template <>
+struct NbRaw<WD_BF16> : NbRaw16<WD_BF16> {};
 
 // h = the half spinor that hop D projects from the loaded neighbour.
 template <int P, bool DAG, int D>
@@ -332,43 +322,16 @@ __device__ __forceinline__ void mrhs_split_mul(const cplx<RealOf<P>> (&u)[6], co
   }
 }
 
-// FP16: project and multiply per direction (24^3x48, 12 right-hand sides: 222
-// us against 260 when the directions are joined in between, which copies every
-// operand); the others join them and load the next neighbour once this one's
-// registers are free (BF16 161 against 166, FP32 and FP64 would spill).
-template <bool DAG, int D>
-__device__ __forceinline__ void mrhs_split_hop16(const cplx<float> (&psi)[12], float f, const cplx<float> (&u)[6],
-                                                 const cplx<float> (&r2)[3], cplx<float> *q) {
-  constexpr int S = ((D < 4) != DAG) ? 1 : -1;
-  cplx<float> h[6];
-  if constexpr ((D & 3) == 3) {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) h[c] = f * psi[c];
-  } else {
-    project<D & 3, S>(psi, h);
-  }
-  mrhs_split_mul<WD_F16>(u, r2, h, q);
-}
-
-// The components per summing wave: as in the single hop, but FP16 keeps a site
-// in one wave, for the waves take turns (another one for each right-hand side)
-// and a barrier more would stop them all.
-template <int P>
-struct MrhsOut {
-  static constexpr int CW = P == WD_F16 ? 12 : SplitOut<P>::CW, NW = 12 / CW;
-};
-
 // The sums and the epilogue of wave slot W for one right-hand side (out at
 // byte offset off, epilogue operands x, y); returns the lane's |components|^2
 // when NORM.
 template <int P, bool DAG, int EPI, bool NORM, int W, int... J>
 __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off, int i, int lane,
-                                                    const SplitLds<P> &lds,
-                                                    cplx<RealOf<P>> (&x)[MrhsOut<P>::CW],
-                                                    cplx<RealOf<P>> (&y)[MrhsOut<P>::CW],
+                                                    SplitLds<P> &lds, cplx<RealOf<P>> (&x)[SplitOut<P>::CW],
+                                                    cplx<RealOf<P>> (&y)[SplitOut<P>::CW],
                                                     std::integer_sequence<int, J...>) {
   using T = RealOf<P>;
-  constexpr int CW = MrhsOut<P>::CW;
+  constexpr int CW = SplitOut<P>::CW;
   cplx<T> o[CW];
   if (i < k.g.vh) {
     const T a = (T)k.a;
@@ -389,7 +352,9 @@ __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off
 #pragma unroll
     for (int j = 0; j < CW; ++j) o[j] = {(T)0, (T)0};
   }
-  split_store<P, W, true, NORM>(k.out + off, i, o);
+  float m = 0.f;
+  if constexpr (P == WD_F16) m = split_max<W>(o, lds, lane);  // (the second barrier)
+  split_store<P, W, true, NORM>(k.out + off, i, o, m);
   double n = 0.0;
   if constexpr (NORM) {
     if (i < k.g.vh) {
@@ -406,16 +371,18 @@ __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off
 // transports one neighbour into LDS (the next neighbour is already on its
 // way), and after a barrier NW of the waves, another set for each right-hand
 // side, add up and store.  Two LDS buffers, so one barrier a right-hand side
-// (FP64: one buffer and two barriers, two blocks a CU instead of one).  80
-// registers a lane and 24 waves a CU (FP64, FP16 128 and 16); all eight links
-// in one lane took 232 registers, 8 waves a CU.  Bound by VALU issue in BF16
+// (FP64: one buffer and two barriers, two blocks a CU instead of one; FP16 has
+// the second barrier for the scale, and so one buffer).  80 registers a lane and
+// 24 waves a CU (FP64 128 and 16); all eight links in one lane took 232
+// registers, 8 waves a CU.  FP16 24^3x48 with 12: 187 us; 218 with a site's sums
+// in one wave, another one for each right-hand side.  Bound by VALU issue in BF16
 // (about 1400 instructions per 64 sites and right-hand side, 158 us of the 161
 // at 24^3x48 with 12) and by fetches in FP64 (1.8 times the algorithmic bytes
 // at 6 TB/s).
 template <int P, bool DAG, int EPI, bool NORM>
-__global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) void k_dslash_mrhs_split(KMrhs m) {
+__global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_split(KMrhs m) {
   using T = RealOf<P>;
-  constexpr int NB = P == WD_F64 ? 1 : 2, NW = MrhsOut<P>::NW, CW = MrhsOut<P>::CW;
+  constexpr int NB = (P == WD_F64 || P == WD_F16) ? 1 : 2, NW = SplitOut<P>::NW, CW = SplitOut<P>::CW;
   __shared__ SplitLds<P> lds[NB];
   __shared__ double sred[NORM ? MR_CHUNK : 1][NW];
   const KDslash &k = m.k;
@@ -485,39 +452,21 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
     // directions, before this one's products
     const char *next = k.in + (size_t)rn * m.rhs_stride;
     cplx<T> *q = L.g + slot;
-    if constexpr (P == WD_F16) {
-      cplx<T> psi[12];
-      nx.unpack(psi, lower);
-      if (more) nx.load(next, nb, time, lower);
-#define WD_HOP(D) mrhs_split_hop16<DAG, D>(psi, f, u, r2, q)
-      switch (w) {
-        case 0: WD_HOP(0); break;
-        case 1: WD_HOP(1); break;
-        case 2: WD_HOP(2); break;
-        case 3: WD_HOP(3); break;
-        case 4: WD_HOP(4); break;
-        case 5: WD_HOP(5); break;
-        case 6: WD_HOP(6); break;
-        default: WD_HOP(7); break;
-      }
-#undef WD_HOP
-    } else {
-      cplx<T> h[6];
+    cplx<T> h[6];
 #define WD_HOP(D) mrhs_split_project<P, DAG, D>(nx, f, h)
-      switch (w) {
-        case 0: WD_HOP(0); break;
-        case 1: WD_HOP(1); break;
-        case 2: WD_HOP(2); break;
-        case 3: WD_HOP(3); break;
-        case 4: WD_HOP(4); break;
-        case 5: WD_HOP(5); break;
-        case 6: WD_HOP(6); break;
-        default: WD_HOP(7); break;
-      }
-#undef WD_HOP
-      if (more) nx.load(next, nb, time, lower);
-      mrhs_split_mul<P>(u, r2, h, q);
+    switch (w) {
+      case 0: WD_HOP(0); break;
+      case 1: WD_HOP(1); break;
+      case 2: WD_HOP(2); break;
+      case 3: WD_HOP(3); break;
+      case 4: WD_HOP(4); break;
+      case 5: WD_HOP(5); break;
+      case 6: WD_HOP(6); break;
+      default: WD_HOP(7); break;
     }
+#undef WD_HOP
+    if (more) nx.load(next, nb, time, lower);
+    mrhs_split_mul<P>(u, r2, h, q);
     const int ws = NB == 2 ? (w + NW * n) & 7 : w;  // the waves take turns
     const size_t off = (size_t)r * m.rhs_stride;
     cplx<T> x[CW], y[CW];  // loaded before the barrier (FP64, short of registers: after the sums)
@@ -538,6 +487,7 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
       if (ws == 4) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 4>(k, off, ii, li, L, x, y, J);
       if (ws == 5) nrm = mrhs_split_finish<P, DAG, EPI, NORM, 5>(k, off, ii, li, L, x, y, J);
     }
+    if (ws >= NW) split_max_rest<P>();
     if constexpr (NORM) {
       if (ws < NW) {
         nrm = wave_sum(nrm);
@@ -545,7 +495,8 @@ __global__ __launch_bounds__(SPLIT_BS, (P == WD_F64 || P == WD_F16) ? 4 : 6) voi
       }
     }
     if (!more) break;
-    if constexpr (NB == 1) __syncthreads();  // before the next right-hand side overwrites the buffer
+    // before the next right-hand side overwrites the buffer (FP16: the barrier of its scale)
+    if constexpr (P == WD_F64) __syncthreads();
     r = rn;
   }
   if constexpr (NORM) {
@@ -674,10 +625,9 @@ static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
 // launch against the defaults of the other forms (128 sites, 4 right-hand
 // sides per lane; FP64 16-site tiles), 12 right-hand sides: BF16 8^4 6.7 / 16,
 // 20^3x40 85 / 108, 24^3x48 161 / 208; FP32 20^3x40 120 / 153, 24^3x48 246 /
-// 309; FP64 16^4 52 / 69, 24^3x48 540 / 714, 32^3x64 1610 / 2290.  FP16 keeps
-// the other form where its tiles fill the device (one wave adds up all 12
-// components of a site to find its scale): 24^3x48 222 / 235, but 32^3x32
-// with 3 118 / 102, 16^4 with 24 55 / 49.
+// 309; FP64 16^4 52 / 69, 24^3x48 540 / 714, 32^3x64 1610 / 2290; FP16 8^4 4.7 /
+// 14, 16^4 23.7 / 26.2 (with 24 43.8 / 45.1), 24^3x48 187 / 218, 32^4 296 / 334
+// (with 3 93 / 92).
 // Order as for the single-RHS hop: contiguous ranges per XCD (BF16 24^3x48 161
 // against 166 with regions); from 2^18 sites in FP64 and FP32 regions of each
 // slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 540 / 573, 32^3x64
@@ -688,11 +638,7 @@ void mrhs_default_variant(wd_gauge *g, int p) {
   g->mrhs_rpl[p] = MRHS_SPLIT_RPL;
   g->mrhs_block[p] = SPLIT_BS;
   g->mrhs_groups[p] = SPLIT_RANGES;
-  if (p == WD_F16 && G.vpad / SPLIT_SITES >= 512) {
-    g->mrhs_rpl[p] = 4;
-    g->mrhs_block[p] = 128;
-    g->mrhs_groups[p] = dslash_variant_ok(G, 128, 4) ? 4 : 0;
-  } else if (G.vh >= (1 << 18)) {
+  if (G.vh >= (1 << 18)) {
     if (dslash_variant_ok(G, SPLIT_SITES, 8)) g->mrhs_groups[p] = 8;
     else if (p <= WD_F32 && dslash_variant_ok(G, SPLIT_SITES, 4)) g->mrhs_groups[p] = 4;
   }
