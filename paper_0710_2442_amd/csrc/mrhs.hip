@@ -312,6 +312,21 @@ template <int P>
 __device__ __forceinline__ void mrhs_split_mul(const cplx<RealOf<P>> (&u)[6], const cplx<RealOf<P>> (&r2)[3],
                                                const cplx<RealOf<P>> (&h)[6], cplx<RealOf<P>> *q) {
   using T = RealOf<P>;
+  if constexpr (P == WD_F64) {
+    // One number at a time: 128 registers then hold the links, this half spinor and
+    // the next neighbour.  Three at a time spilled packets of the neighbour as they
+    // came (24^3x48 with 12: 554 us, 478 now).
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        cplx<T> y = (a < 2 ? u[3 * (a & 1)] : r2[0]) * h[3 * s];
+        cfma(y, a < 2 ? u[3 * (a & 1) + 1] : r2[1], h[3 * s + 1]);
+        cfma(y, a < 2 ? u[3 * (a & 1) + 2] : r2[2], h[3 * s + 2]);
+        q[(3 * s + a) * SPLIT_SITES] = y;
+      }
+    return;
+  }
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const cplx<T> v[3] = {h[3 * s], h[3 * s + 1], h[3 * s + 2]};
@@ -435,13 +450,11 @@ __global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_s
   NbRaw<P> nx;  // (padding lanes read site 0)
   const bool time = (w & 3) == 3, lower = time && (w == 3) == DAG;
   unsigned todo = chosen;
-  int r = r0 + __builtin_ctz(todo);
-  nx.load(k.in + (size_t)r * m.rhs_stride, nb, time, lower);
+  nx.load(k.in + (size_t)(r0 + __builtin_ctz(todo)) * m.rhs_stride, nb, time, lower);
 #pragma unroll 1
-  for (int n = 0;; ++n) {  // n-th live system of the chunk: r
+  for (int n = 0; todo; ++n) {  // n-th live system of the chunk: r
+    const int r = r0 + __builtin_ctz(todo);
     todo &= todo - 1;
-    const bool more = todo != 0;
-    const int rn = more ? r0 + __builtin_ctz(todo) : r;
     // opaque copies: the addresses of the six sums are formed where they are
     // used, not kept in registers across the loop
     int li = lane, ii = i;
@@ -450,7 +463,6 @@ __global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_s
     SplitLds<P> &L = lds[NB == 2 ? n & 1 : 0];
     // the next right-hand side's neighbour is loaded, by one load for all
     // directions, before this one's products
-    const char *next = k.in + (size_t)rn * m.rhs_stride;
     cplx<T> *q = L.g + slot;
     cplx<T> h[6];
 #define WD_HOP(D) mrhs_split_project<P, DAG, D>(nx, f, h)
@@ -465,7 +477,7 @@ __global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_s
       default: WD_HOP(7); break;
     }
 #undef WD_HOP
-    if (more) nx.load(next, nb, time, lower);
+    if (todo) nx.load(k.in + (size_t)(r0 + __builtin_ctz(todo)) * m.rhs_stride, nb, time, lower);
     mrhs_split_mul<P>(u, r2, h, q);
     const int ws = NB == 2 ? (w + NW * n) & 7 : w;  // the waves take turns
     const size_t off = (size_t)r * m.rhs_stride;
@@ -494,10 +506,8 @@ __global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_s
         if (lane == 0) sred[r - r0][ws] = nrm;
       }
     }
-    if (!more) break;
     // before the next right-hand side overwrites the buffer (FP16: the barrier of its scale)
     if constexpr (P == WD_F64) __syncthreads();
-    r = rn;
   }
   if constexpr (NORM) {
     __syncthreads();
@@ -625,13 +635,13 @@ static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
 // launch against the defaults of the other forms (128 sites, 4 right-hand
 // sides per lane; FP64 16-site tiles), 12 right-hand sides: BF16 8^4 6.7 / 16,
 // 20^3x40 85 / 108, 24^3x48 161 / 208; FP32 20^3x40 120 / 153, 24^3x48 246 /
-// 309; FP64 16^4 52 / 69, 24^3x48 540 / 714, 32^3x64 1610 / 2290; FP16 8^4 4.7 /
+// 309; FP64 16^4 42 / 67, 24^3x48 480 / 700, 32^3x64 1460 / 2250; FP16 8^4 4.7 /
 // 14, 16^4 23.7 / 26.2 (with 24 43.8 / 45.1), 24^3x48 187 / 218, 32^4 296 / 334
 // (with 3 93 / 92).
 // Order as for the single-RHS hop: contiguous ranges per XCD (BF16 24^3x48 161
 // against 166 with regions); from 2^18 sites in FP64 and FP32 regions of each
-// slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 540 / 573, 32^3x64
-// 1610 / 1777).
+// slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 480 / 507, 32^3x64
+// 1457 / 1608).
 constexpr int MRHS_SPLIT_RPL = 12;
 void mrhs_default_variant(wd_gauge *g, int p) {
   const Geom &G = g->geom;
@@ -648,7 +658,7 @@ void mrhs_default_variant(wd_gauge *g, int p) {
 // Right-hand sides per block.  The default variant (its block, order and rpl,
 // whether set or never touched) adds chunks until the blocks are two a CU, for fewer would leave the chain of right-hand sides as
 // the run time: 8^4 (32 tiles), 12 right-hand sides BF16: 3 per block 6.7 us,
-// 12 per block 15.2; 16^4 (512 tiles) FP64: 12 per block 52, 4 per block 62.
+// 12 per block 15.2; 16^4 (512 tiles) FP64: 12 per block 42, 4 per block 55.
 static int mrhs_split_rpl(const wd_gauge *g, int prec, int nrhs, int ntiles) {
   const int most = g->mrhs_rpl[prec];
   if (most != MRHS_SPLIT_RPL || g->mrhs_groups[prec] != g->mrhs_groups0[prec]) return most;
