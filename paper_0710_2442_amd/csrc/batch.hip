@@ -20,8 +20,9 @@
 // the faster form for one lattice, loses here: each block starts with a chain
 // of reads, list, descriptor, mask, that 64 sites do not hide.  The eight
 // lattices of 8^4 to 20^3x40 in BF16 took 26.7 ms with it, 23.0 without.)
-// Bound by the FP32 links: 528 bytes a site in BF16, 21 us a hop over all eight
-// lattices, 8.6 TB/s from the memory-side cache.
+// Bound by the FP32 links' way through the caches: 528 bytes a site in BF16, 42
+// us a hop with all eight lattices live, 4.3 TB/s (21 us on the average of a
+// solve, whose lattices converge one after the other).
 #include <math.h>
 #include <string.h>
 

@@ -804,13 +804,14 @@ wd_status dirac_init(wd_gauge *g) {
 }
 
 // The default variant (slices 0 and the default tile, whether set or never
-// touched) runs tile 4 unless the staged bricks fit and fill the device (one block on at least 95% of the
-// resident slots): then the march, which fetches nothing twice, is ahead.
+// touched) runs tile 4 unless the staged bricks fit and fill the device (one
+// block on at least 95% of the resident slots): then the march, which fetches
+// nothing twice, is ahead.
 // us per launch, tile 4 against the march's default: FP64 8^3x16 4.5 / 64,
 // 16^3x32 23 / 69, 24^3x48 127 / 175 (no bricks), 16x32x32x96 274 / 321 (192
-// of 256 slots), 32^3x32 189 / 180 and 32^3x64 373 / 349 (all slots); FP32
-// 24^3x48 55 / 82, 32^3x64 185 / 174; BF16 (no staging) 32^3x64 143 / 213; FP16
-// 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81 and 180 for a hop of each parity,
+// of 256 slots), 32^3x32 189 / 180 and 32^3x64 367 / 349 (all slots); FP32
+// 24^3x48 55 / 82, 32^3x64 182 / 182 (177 with ranges of 16 slices, tuned); BF16
+// (no staging) 32^3x64 143 / 213; FP16 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81 and 180 for a hop of each parity,
 // which WD_FULL without WD_ONE_PASS was).
 static bool dirac_uses_split(const wd_gauge *g, wd_prec prec) {
   if (g->dirac_slices[prec] != 0 || g->dirac_tile[prec] != g->dirac_tile0[prec]) return g->dirac_tile[prec] == 4;

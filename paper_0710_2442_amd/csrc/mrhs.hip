@@ -392,8 +392,8 @@ __device__ __forceinline__ double mrhs_split_finish(const KDslash &k, size_t off
 // registers, 8 waves a CU.  FP16 24^3x48 with 12: 187 us; 218 with a site's sums
 // in one wave, another one for each right-hand side.  Bound by VALU issue in BF16
 // (about 1400 instructions per 64 sites and right-hand side, 158 us of the 161
-// at 24^3x48 with 12) and by fetches in FP64 (1.8 times the algorithmic bytes
-// at 6 TB/s).
+// at 24^3x48 with 12) and by fetches in FP64 (tuned order there: 1.59 times the
+// algorithmic bytes, 5.9 TB/s).
 template <int P, bool DAG, int EPI, bool NORM>
 __global__ __launch_bounds__(SPLIT_BS, P == WD_F64 ? 4 : 6) void k_dslash_mrhs_split(KMrhs m) {
   using T = RealOf<P>;
@@ -637,11 +637,14 @@ static int mrhs_block_of(const wd_gauge *g, wd_prec prec, int &groups) {
 // 20^3x40 85 / 108, 24^3x48 161 / 208; FP32 20^3x40 120 / 153, 24^3x48 246 /
 // 309; FP64 16^4 42 / 67, 24^3x48 480 / 700, 32^3x64 1460 / 2250; FP16 8^4 4.7 /
 // 14, 16^4 23.7 / 26.2 (with 24 43.8 / 45.1), 24^3x48 187 / 218, 32^4 296 / 334
-// (with 3 93 / 92).
+// (with 3 93 / 92).  Alone on 24^3x48, one lane per site in box order with all 12
+// (tuned) is faster in BF16, 139 us, but slower in a solve of 12, where systems
+// finish and epilogues add operands: 99.8 ms against 89.5; FP32 235 / 235 us and
+// 158 / 155 ms.
 // Order as for the single-RHS hop: contiguous ranges per XCD (BF16 24^3x48 161
-// against 166 with regions); from 2^18 sites in FP64 and FP32 regions of each
-// slice, 8 or, where 8 do not divide it, 4 (FP64 24^3x48 480 / 507, 32^3x64
-// 1457 / 1608).
+// against 166 with regions); from 2^18 sites eight regions of each slice where
+// they divide it (32^4: FP64 721 / 809, FP32 366 / 397, FP16 306 / 310, BF16 250 /
+// 254), else in FP64 and FP32 four (FP64 24^3x48 480 / 507).
 constexpr int MRHS_SPLIT_RPL = 12;
 void mrhs_default_variant(wd_gauge *g, int p) {
   const Geom &G = g->geom;
