@@ -811,8 +811,8 @@ wd_status dirac_init(wd_gauge *g) {
 // 16^3x32 23 / 69, 24^3x48 127 / 175 (no bricks), 16x32x32x96 274 / 321 (192
 // of 256 slots), 32^3x32 189 / 180 and 32^3x64 367 / 349 (all slots); FP32
 // 24^3x48 55 / 82, 32^3x64 182 / 182 (177 with ranges of 16 slices, tuned); BF16
-// (no staging) 32^3x64 143 / 213; FP16 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81 and 180 for a hop of each parity,
-// which WD_FULL without WD_ONE_PASS was).
+// (no staging) 32^3x64 143 / 213; FP16 24^3x48 42 / 94, 32^3x64 155 / 217 (and 81
+// and 180 for a hop of each parity, which WD_FULL without WD_ONE_PASS was).
 static bool dirac_uses_split(const wd_gauge *g, wd_prec prec) {
   if (g->dirac_slices[prec] != 0 || g->dirac_tile[prec] != g->dirac_tile0[prec]) return g->dirac_tile[prec] == 4;
   return g->dirac_tile[prec] != 3 || march_grid_of(g, prec).items < 0.95 * march_capacity(g, prec);

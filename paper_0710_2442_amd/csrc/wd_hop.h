@@ -459,11 +459,12 @@ __device__ __forceinline__ double dslash_site(const KDslash &k, int i, Stage<Rea
 // arithmetic as hop_all, so the result is the same bit for bit.
 //
 // A lane's chain is one load latency and one link multiply instead of eight,
-// and a CU holds 16 to 24 waves (one hop's operands fit 80 to 128 registers)
-// instead of 8 to 12.
+// and a CU holds 24 (FP64) or 32 waves (one hop's operands fit 80 or 54
+// registers) instead of 8 to 12.
 //
 // LDS: component c of hop d at site s is element (6 d + c) 64 + s, so the
-// lanes of a wave touch consecutive words: 48 KiB in FP64, 24 KiB else.
+// lanes of a wave touch consecutive words: 48 KiB in FP64, 24 KiB else (FP16 768
+// bytes more).
 constexpr int SPLIT_SITES = 64;
 constexpr int SPLIT_BS = 512;
 template <int P>
@@ -610,10 +611,9 @@ struct SplitOut {
   static constexpr int NW = 12 / CW;
 };
 
-// Components W CW .. of a stored spinor (w = W may be a run-time value); CW = 12
-// for FP16 where one wave sums them all.
-template <int P, int CW>
-__device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<RealOf<P>> (&x)[CW]) {
+// Components W CW .. of a stored spinor (w = W may be a run-time value).
+template <int P>
+__device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<RealOf<P>> (&x)[SplitOut<P>::CW]) {
   if constexpr (P == WD_F64) {
     const v2d *p = (const v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * w;
     const v2d a = p[0], b = p[64];
@@ -625,8 +625,6 @@ __device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<
     x[1] = {v.z, v.w};
   } else if constexpr (P == WD_BF16) {
     Packet<WD_BF16>::unpack(*((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w), x);
-  } else if constexpr (CW == 12) {
-    Spinor<P>::load(base, i, x);
   } else {
     const v4u v = *((const v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * w);
     const float n = Spinor<P>::scale(base, (size_t)i);
@@ -637,10 +635,10 @@ __device__ __forceinline__ void split_load(const char *base, int i, int w, cplx<
   }
 }
 
-// Stores them (FP16, CW = 4: with the site's scale m); on return x holds the
-// stored (rounded) values when NORM.
-template <int P, int W, bool NT, bool NORM, int CW>
-__device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (&x)[CW], float m = 0.f) {
+// Stores them (FP16: with the site's scale m); on return x holds the stored
+// (rounded) values when NORM.
+template <int P, int W, bool NT, bool NORM>
+__device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (&x)[SplitOut<P>::CW], float m) {
   if constexpr (P == WD_F64) {
     v2d *p = (v2d *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i) + 64 * 2 * W;
     st_policy<NT>(v2d{x[0].re, x[0].im}, p);
@@ -658,9 +656,6 @@ __device__ __forceinline__ void split_store(char *base, int i, cplx<RealOf<P>> (
       for (int j = 0; j < 4; ++j)
         x[j] = {bf16_to_f32((uint16_t)(w[j] & 0xffffu)), bf16_to_f32((uint16_t)(w[j] >> 16))};
     }
-  } else if constexpr (CW == 12) {
-    Spinor<P>::template store<NT>(base, i, x);
-    if constexpr (NORM) Spinor<P>::load(base, i, x);
   } else {
     const float inv = m > 0.f ? 1.0f / m : 0.f;
     v4u *p = (v4u *)base + chunk_base<Spinor<P>::CHUNK>((size_t)i);
